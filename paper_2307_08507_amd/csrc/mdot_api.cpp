@@ -35,6 +35,8 @@ constexpr int kChunk = 32;       // solver steps per graph launch (even: the sta
 constexpr int kBatchChunk = 16;  // engine steps per graph launch (admission granularity, even)
 constexpr int kMaxN = MDOT_MAX_N;
 constexpr int kConvBlocks = 1024; // workgroups of the FP16 conversion (MIXED)
+constexpr int kDoneInts = 2 * kMaxBatch + 2;  // done flags in mapped host memory
+static_assert(kDoneInts % 2 == 0, "the AloneOut behind the flags is aligned to 8 bytes");
 
 // Device buffers of one problem: workspace, device copy of Work + 2 state slots, parameters.
 struct ProblemBufs {
@@ -102,7 +104,8 @@ struct mdot_ctx {
     unsigned char* d_fixed = nullptr;
     State* h_state = nullptr;     // pinned
     // done flags written by the last kernel of each graph chunk (pinned, mapped, fine-grained):
-    // 2 for the single solves, then 2 x kMaxBatch for the engine; d_hdone is the device alias
+    // 2 for the single solves, then 2 x kMaxBatch for the engine, then the summary of a standalone
+    // sweep (AloneOut, at kDoneInts); d_hdone is the device alias
     int* h_done = nullptr;
     int* d_hdone = nullptr;
     int* d_seq = nullptr;     // device chunk counters: [0] single solves, [1] engine
@@ -326,9 +329,9 @@ static void pick_variant(const mdot_ctx* ctx, int code, int n, int* occ2, int* s
 }
 
 // Lay the Work struct out over pb's workspace for m rows and n columns (the workspace holds at
-// least workspace_bytes(m, n)) and upload it.
-static int bind_work(mdot_ctx* ctx, ProblemBufs& pb, int m, int n, const mdot_cost_desc* cost, double scale,
-                     const double* r, const double* c, hipStream_t stream)
+// least workspace_bytes(m, n)).
+static void lay_work(mdot_ctx* ctx, ProblemBufs& pb, int m, int n, const mdot_cost_desc* cost, double scale,
+                     const double* r, const double* c)
 {
     size_t off[32];
     workspace_bytes(m, n, off);
@@ -372,7 +375,14 @@ static int bind_work(mdot_ctx* ctx, ProblemBufs& pb, int m, int n, const mdot_co
     w.st = ctl->st;
     w.prm = &ctl->prm;
     w.bdots = ctl->bdots;
-    HIPCHK(ctx, hipMemcpyAsync(pb.d_work, &w, sizeof w, hipMemcpyHostToDevice, stream));
+}
+
+// The same, uploaded.
+static int bind_work(mdot_ctx* ctx, ProblemBufs& pb, int m, int n, const mdot_cost_desc* cost, double scale,
+                     const double* r, const double* c, hipStream_t stream)
+{
+    lay_work(ctx, pb, m, n, cost, scale, r, c);
+    HIPCHK(ctx, hipMemcpyAsync(pb.d_work, &pb.host_work, sizeof(Work), hipMemcpyHostToDevice, stream));
     return MDOT_OK;
 }
 
@@ -435,13 +445,12 @@ static int check_params(mdot_ctx* ctx, const mdot_params& prm, double target_gap
 }
 
 // Range of the raw cost (one pass) -> resolved scale; MDOT_E_COST if scale*raw leaves [0,1].
-// dpart: device buffer of 2 * tiles partials (the context's scratch unless given).
 static int resolve_scale(mdot_ctx* ctx, ProblemBufs& pb, const mdot_cost_desc* cost, double* scale_out,
-                         hipStream_t stream, double* dpart = nullptr)
+                         hipStream_t stream)
 {
     const int tiles = tiles_r(rows_of(cost)) * tiles_c(cost->n);
-    if (!dpart) dpart = ctx->d_scratch;
-    if (launch_cost_range(pb.host_work, pb.d_work, dpart, stream))
+    double* dpart = ctx->d_scratch;
+    if (launch_cost_range(pb.host_work, pb.d_work, dpart, 0, stream))
         return fail(ctx, MDOT_E_DEVICE, "cost range kernel launch failed");
     HIPCHK(ctx, hipMemcpyAsync(ctx->h_scratch, dpart, 2 * tiles * sizeof(double), hipMemcpyDeviceToHost, stream));
     HIPCHK(ctx, hipStreamSynchronize(stream));
@@ -456,8 +465,7 @@ static int resolve_scale(mdot_ctx* ctx, ProblemBufs& pb, const mdot_cost_desc* c
     if (nonfinite || !std::isfinite(lo)) return fail(ctx, MDOT_E_COST, "cost has non-finite entries");
     double scale = cost->scale;
     if (cost->kind != MDOT_COST_DENSE && scale == 0.0) scale = hi > 0.0 ? 1.0 / hi : 1.0;
-    const double slack = 1e-12;
-    if (scale * lo < -slack || scale * hi > 1.0 + slack)
+    if (!range_valid(scale, lo, hi))
         return fail(ctx, MDOT_E_COST, "scaled cost range [%g, %g] is outside [0, 1]", scale * lo, scale * hi);
     *scale_out = scale;
     return MDOT_OK;
@@ -917,7 +925,7 @@ int mdot_ctx_create(int device, void* hip_stream, size_t hbm_budget_bytes, mdot_
     ctx->budget = hbm_budget_bytes;
     bool ok = hipHostMalloc(&ctx->h_state, sizeof(State), hipHostMallocDefault) == hipSuccess &&
               hipHostMalloc(&ctx->h_prm, sizeof(DevParams), hipHostMallocDefault) == hipSuccess &&
-              hipHostMalloc(&ctx->h_done, (2 * kMaxBatch + 2) * sizeof(int), hipHostMallocMapped | hipHostMallocCoherent) ==
+              hipHostMalloc(&ctx->h_done, kDoneInts * sizeof(int) + sizeof(AloneOut), hipHostMallocMapped | hipHostMallocCoherent) ==
                   hipSuccess &&
               hipHostGetDevicePointer((void**)&ctx->d_hdone, ctx->h_done, 0) == hipSuccess &&
               hipMalloc(&ctx->d_seq, 2 * sizeof(int)) == hipSuccess && hipMemset(ctx->d_seq, 0, 2 * sizeof(int)) == hipSuccess &&
@@ -1052,53 +1060,36 @@ int mdot_solve(mdot_ctx* ctx, const mdot_cost_desc* cost, const double* r, const
     return S.status;
 }
 
-// Set up pb for a standalone sweep sequence (one LSE, or Round + certificate). pb is the
-// context's `main` (workspace allocated on demand) or its `fixed` buffers (borrowed from the
-// static array: nothing is allocated, and the cost range partials go to `dpart` in that array).
-static int standalone_setup(mdot_ctx* ctx, ProblemBufs& pb, const mdot_cost_desc* cost, const double* u,
-                            const double* v, double gamma, const double* shift, int exp64, int kind,
-                            const double* u_prev, const double* v_prev, double gamma_prev, const double* r,
-                            const double* c, double* dpart = nullptr)
+// A standalone sweep sequence on pb: one LSE (u, v -> lr_out, lc_out; round = false) or, in FP64,
+// the LSE, Round and the certificate (round = true). pb is the context's `main` (workspace
+// allocated on demand) or its `fixed` buffers (borrowed from the static array: nothing is
+// allocated); dpart holds 2 doubles per tile for the cost range. The kernels are queued back to
+// back and the host waits once, for the summary the last one writes into host memory; a second
+// time only where FP32 rows or columns left the range and the sweep is run again with FP64 exp.
+static int run_alone(mdot_ctx* ctx, ProblemBufs& pb, const mdot_cost_desc* cost, const AloneIn& in, double gamma,
+                     double gamma_prev, int exp64, bool round, const double* r, const double* c, double* dpart,
+                     double* lr_out, double* lc_out, AloneOut* res)
 {
     const int m = rows_of(cost), n = cost->n;
     if (!pb.borrowed) {
         int rc = ensure_workspace(ctx, pb, m, n, ctx->stream);
         if (rc) return rc;
+        if (!dpart) dpart = ctx->d_scratch;
     }
-    int rc = bind_work(ctx, pb, m, n, cost, cost->scale > 0 ? cost->scale : 1.0, r, c, ctx->stream);
-    if (rc) return rc;
-    double scale;
-    rc = resolve_scale(ctx, pb, cost, &scale, ctx->stream, dpart);
-    if (rc) return rc;
-    if (scale != pb.host_work.scale) {
-        rc = bind_work(ctx, pb, m, n, cost, scale, r, c, ctx->stream);
-        if (rc) return rc;
-    }
-    const Work& w = pb.host_work;
-    // rt .. lzt and the n-vectors xr, yc, errc (the vectors these sweeps read besides z and lz)
-    // start at zero: a fill kernel, since the static array keeps the previous call's contents
-    size_t off[kWsBuffers + 1];
-    workspace_bytes(m, n, off);
-    if (launch_fill(w.rt, off[12] / sizeof(double), 0.0, ctx->stream))
-        return fail(ctx, MDOT_E_DEVICE, "fill launch failed");
-    HIPCHK(ctx, hipMemcpyAsync(w.z, u, m * sizeof(double), hipMemcpyDeviceToDevice, ctx->stream));
-    HIPCHK(ctx, hipMemcpyAsync(w.z + m, v, n * sizeof(double), hipMemcpyDeviceToDevice, ctx->stream));
-    if (shift) HIPCHK(ctx, hipMemcpyAsync(w.lz, shift, m * sizeof(double), hipMemcpyDeviceToDevice, ctx->stream));
-    const bool ext = u_prev && v_prev && gamma > gamma_prev;
-    if (ext) {
-        HIPCHK(ctx, hipMemcpyAsync(w.zprev, u_prev, m * sizeof(double), hipMemcpyDeviceToDevice, ctx->stream));
-        HIPCHK(ctx, hipMemcpyAsync(w.zprev + m, v_prev, n * sizeof(double), hipMemcpyDeviceToDevice, ctx->stream));
-    }
-    DevParams& P = *ctx->h_prm;
+    const bool points = cost->kind != MDOT_COST_DENSE, choose = points && cost->scale == 0.0;
+    lay_work(ctx, pb, m, n, cost, choose ? 1.0 : cost->scale, r, c);
+    const bool ext = in.u_prev && in.v_prev && gamma > gamma_prev;
+    AloneIn vec = in;
+    if (!ext) vec.u_prev = vec.v_prev = nullptr;
+    DevParams P;
     memset(&P, 0, sizeof P);
     P.exp64_default = exp64;
     P.n = n;
     P.gamma_f = gamma;
-    HIPCHK(ctx, hipMemcpyAsync(pb.d_prm, &P, sizeof P, hipMemcpyHostToDevice, ctx->stream));
-    State& S = *ctx->h_state;
+    State S;
     memset(&S, 0, sizeof S);
-    S.standalone = kind;
-    S.sweep_mode = shift ? SM_LSE : SM_MAX;
+    S.standalone = round ? 2 : 1;
+    S.sweep_mode = SM_LSE;
     S.ls_phase = LS_STANDALONE;
     S.exp64 = exp64;
     S.exp64_stage = exp64;
@@ -1106,8 +1097,54 @@ static int standalone_setup(mdot_ctx* ctx, ProblemBufs& pb, const mdot_cost_desc
     S.gamma_prev = ext ? gamma_prev : gamma;
     S.best_ub = INFINITY;
     S.best_lb = -INFINITY;
-    HIPCHK(ctx, hipMemcpyAsync(w.st, &S, sizeof S, hipMemcpyHostToDevice, ctx->stream));
-    HIPCHK(ctx, hipStreamSynchronize(ctx->stream));  // the pinned blocks are reused later
+    const Work& w = pb.host_work;
+    Work* wd = pb.d_work;
+    hipStream_t st = ctx->stream;
+    AloneOut* dout = reinterpret_cast<AloneOut*>(ctx->d_hdone + kDoneInts);
+    volatile AloneOut* hout = reinterpret_cast<volatile AloneOut*>(ctx->h_done + kDoneInts);
+    const bool boxes = points && !choose && in.shift;
+    int where = kRangeDone, bad = launch_alone_setup(w, S, P, vec, wd, boxes, st);
+    if (choose) {
+        bad |= launch_cost_range(w, wd, dpart, 0, st);
+        bad |= launch_pick_scale(wd, dpart, st);
+    }
+    if (!in.shift) {
+        bad |= launch_row_max(w, wd, dpart, st);
+        bad |= launch_sweep(w, wd, 0, st);
+    } else if (points) {
+        if (boxes) bad |= launch_cost_range(w, wd, dpart, 1, st);
+        where = boxes ? kRangeBox : kRangeTiles;
+        bad |= launch_sweep(w, wd, 0, st);
+    } else {
+        where = kRangeTiles;
+        bad |= launch_sweep_range(w, wd, dpart, st);
+    }
+    bad |= launch_finalize(w, wd, 0, st);
+    int slot = 0;
+    if (round) {  // LSE -> R1 -> R2 -> done, the slots alternating
+        bad |= launch_decide(wd, 0, st);
+        bad |= launch_step(w, wd, 1, st);
+        bad |= launch_step(w, wd, 0, st);
+        slot = 1;
+    }
+    bad |= launch_alone_out(w, wd, slot, dpart, where, !round, exp64, lr_out, lc_out, dout, st);
+    if (bad) return fail(ctx, MDOT_E_DEVICE, "standalone sweep launch failed");
+    HIPCHK(ctx, hipStreamSynchronize(st));
+    pb.host_work.scale = hout->scale;
+    if (!hout->valid) {  // the exact range, for the message
+        double scale;
+        int rc = resolve_scale(ctx, pb, cost, &scale, st);
+        return rc ? rc : fail(ctx, MDOT_E_DEVICE, "cost range of a standalone sweep not reproduced");
+    }
+    if (hout->retry) {
+        bad = launch_sweep(w, wd, 0, st) | launch_finalize(w, wd, 0, st);
+        // the range was found valid: where it was reduced from, it still is
+        bad |= launch_alone_out(w, wd, 0, dpart, where, 1, 1, lr_out, lc_out, dout, st);
+        if (bad) return fail(ctx, MDOT_E_DEVICE, "standalone sweep launch failed");
+        HIPCHK(ctx, hipStreamSynchronize(st));
+    }
+    if (round && !hout->done) return fail(ctx, MDOT_E_DEVICE, "round/certify sweeps did not finish");
+    memcpy(res, const_cast<const AloneOut*>(hout), sizeof *res);
     return MDOT_OK;
 }
 
@@ -1121,20 +1158,10 @@ int mdot_lse2(mdot_ctx* ctx, const mdot_cost_desc* cost, const double* u, const 
     if (!(gamma >= 0.0) || !std::isfinite(gamma)) return fail(ctx, MDOT_E_ARG, "bad gamma %g", gamma);
     if (precision != MDOT_PREC_F32 && precision != MDOT_PREC_F64) return fail(ctx, MDOT_E_ARG, "bad precision");
     HIPCHK(ctx, hipSetDevice(ctx->device));
-    rc = standalone_setup(ctx, ctx->main, cost, u, v, gamma, shift, precision == MDOT_PREC_F64, 1, nullptr, nullptr, 0.0, nullptr,
-                          nullptr);
-    if (rc) return rc;
-    rc = run_steps(ctx, 1);
-    if (rc) return rc;
-    rc = read_state(ctx, ctx->main);
-    if (rc) return rc;
-    if (!ctx->h_state->done) return fail(ctx, MDOT_E_DEVICE, "standalone sweep did not finish");
-    const Work& w = ctx->main.host_work;
-    const int m = rows_of(cost), n = cost->n;
-    HIPCHK(ctx, hipMemcpyAsync(lr_out, w.lzt, m * sizeof(double), hipMemcpyDeviceToDevice, ctx->stream));
-    HIPCHK(ctx, hipMemcpyAsync(lc_out, w.lzt + m, n * sizeof(double), hipMemcpyDeviceToDevice, ctx->stream));
-    HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-    return ctx->h_state->status;
+    AloneOut out;
+    rc = run_alone(ctx, ctx->main, cost, AloneIn{u, v, shift, nullptr, nullptr}, gamma, 0.0, precision == MDOT_PREC_F64,
+                   false, nullptr, nullptr, nullptr, lr_out, lc_out, &out);
+    return rc ? rc : out.status;
 }
 
 int mdot_lse2_noalloc(mdot_ctx* ctx, const mdot_cost_desc* cost, const double* u, const double* v, double gamma,
@@ -1160,22 +1187,10 @@ int mdot_lse2_noalloc(mdot_ctx* ctx, const mdot_cost_desc* cost, const double* u
     pb.cap_n = kNoAllocMaxN;
     double* dpart =
         reinterpret_cast<double*>(ctx->d_fixed + kNoAllocCtl + ws_offset(kWsBuffers, kNoAllocMaxN, kNoAllocMaxN));
-    rc = standalone_setup(ctx, pb, cost, u, v, gamma, shift, precision == MDOT_PREC_F64, 1, nullptr, nullptr, 0.0,
-                          nullptr, nullptr, dpart);
-    if (rc) return rc;
-    // at most three steps do work (row-max pass, LSE sweep, its FP64 re-run); later steps carry
-    // the finished state over, and after an even number of steps slot 0 holds the newest state
-    const Work& w = pb.host_work;
-    for (int k = 0; k < 4; ++k)
-        if (launch_step(w, pb.d_work, k & 1, ctx->stream)) return fail(ctx, MDOT_E_DEVICE, "step launch failed");
-    rc = read_state(ctx, pb);
-    if (rc) return rc;
-    if (!ctx->h_state->done) return fail(ctx, MDOT_E_DEVICE, "standalone sweep did not finish");
-    const int m = rows_of(cost), n = cost->n;
-    HIPCHK(ctx, hipMemcpyAsync(lr_out, w.lzt, m * sizeof(double), hipMemcpyDeviceToDevice, ctx->stream));
-    HIPCHK(ctx, hipMemcpyAsync(lc_out, w.lzt + m, n * sizeof(double), hipMemcpyDeviceToDevice, ctx->stream));
-    HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-    return ctx->h_state->status;
+    AloneOut out;
+    rc = run_alone(ctx, pb, cost, AloneIn{u, v, shift, nullptr, nullptr}, gamma, 0.0, precision == MDOT_PREC_F64, false,
+                   nullptr, nullptr, dpart, lr_out, lc_out, &out);
+    return rc ? rc : out.status;
 }
 
 int mdot_round_certify(mdot_ctx* ctx, const mdot_cost_desc* cost, const double* u, const double* v, double gamma,
@@ -1188,17 +1203,34 @@ int mdot_round_certify(mdot_ctx* ctx, const mdot_cost_desc* cost, const double* 
     if (!u || !v || !r || !c || !ub || !lb || !marg_err) return fail(ctx, MDOT_E_ARG, "NULL pointer argument");
     if (!(gamma > 0.0) || !std::isfinite(gamma)) return fail(ctx, MDOT_E_ARG, "bad gamma %g", gamma);
     HIPCHK(ctx, hipSetDevice(ctx->device));
-    rc = standalone_setup(ctx, ctx->main, cost, u, v, gamma, nullptr, 1, 2, u_prev, v_prev, gamma_prev, r, c);
+    AloneOut out;
+    rc = run_alone(ctx, ctx->main, cost, AloneIn{u, v, nullptr, u_prev, v_prev}, gamma, gamma_prev, 1, true, r, c,
+                   nullptr, nullptr, nullptr, &out);
     if (rc) return rc;
-    rc = run_steps(ctx, 1);
+    *ub = out.ub;
+    *lb = out.lb;
+    *marg_err = out.me;
+    return out.status;
+}
+
+// Set-up of the sweep timing hooks: exact log-sums first (max pass + LSE pass), then a state
+// slot 0 whose LSE sweeps run with these converged shifts.
+static int bench_setup(mdot_ctx* ctx, const mdot_cost_desc* cost, const double* u, const double* v, double gamma,
+                       int exp64)
+{
+    AloneOut out;
+    int rc = run_alone(ctx, ctx->main, cost, AloneIn{u, v, nullptr, nullptr, nullptr}, gamma, 0.0, exp64, false, nullptr,
+                       nullptr, nullptr, nullptr, nullptr, &out);
     if (rc) return rc;
-    rc = read_state(ctx, ctx->main);
-    if (rc) return rc;
-    if (!ctx->h_state->done) return fail(ctx, MDOT_E_DEVICE, "round/certify sweeps did not finish");
-    *ub = ctx->h_state->best_ub;
-    *lb = ctx->h_state->best_lb;
-    *marg_err = ctx->h_state->best_me;
-    return ctx->h_state->status;
+    const Work& w = ctx->main.host_work;
+    const int mn = rows_of(cost) + cost->n;
+    HIPCHK(ctx, hipMemcpyAsync(w.lz, w.lzt, mn * sizeof(double), hipMemcpyDeviceToDevice, ctx->stream));
+    State& S = *ctx->h_state;
+    HIPCHK(ctx, hipMemcpyAsync(&S, w.st, sizeof S, hipMemcpyDeviceToHost, ctx->stream));
+    HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+    S.exp64 = exp64;
+    HIPCHK(ctx, hipMemcpyAsync(w.st, &S, sizeof S, hipMemcpyHostToDevice, ctx->stream));
+    return MDOT_OK;
 }
 
 int mdot_bench_sweep(mdot_ctx* ctx, const mdot_cost_desc* cost, const double* u, const double* v, double gamma,
@@ -1210,25 +1242,9 @@ int mdot_bench_sweep(mdot_ctx* ctx, const mdot_cost_desc* cost, const double* u,
     if (!u || !v || !ms_per_sweep || iters < 1) return fail(ctx, MDOT_E_ARG, "bad argument");
     if (precision != MDOT_PREC_F32 && precision != MDOT_PREC_F64) return fail(ctx, MDOT_E_ARG, "bad precision");
     HIPCHK(ctx, hipSetDevice(ctx->device));
-    const int exp64 = precision == MDOT_PREC_F64;
-    // exact log-sums first (max pass + LSE pass) so the timed sweeps run with converged shifts
-    rc = standalone_setup(ctx, ctx->main, cost, u, v, gamma, nullptr, exp64, 1, nullptr, nullptr, 0.0, nullptr, nullptr);
-    if (rc) return rc;
-    rc = run_steps(ctx, 1);
+    rc = bench_setup(ctx, cost, u, v, gamma, precision == MDOT_PREC_F64);
     if (rc) return rc;
     const Work& w = ctx->main.host_work;
-    const int mn = rows_of(cost) + cost->n;
-    HIPCHK(ctx, hipMemcpyAsync(w.lz, w.lzt, mn * sizeof(double), hipMemcpyDeviceToDevice, ctx->stream));
-    State& S = *ctx->h_state;
-    HIPCHK(ctx, hipMemcpyAsync(&S, w.st, sizeof S, hipMemcpyDeviceToHost, ctx->stream));
-    HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-    S.done = 0;
-    S.standalone = 1;
-    S.sweep_mode = SM_LSE;
-    S.ls_phase = LS_STANDALONE;
-    S.exp64 = exp64;
-    S.vec_action = 0;
-    HIPCHK(ctx, hipMemcpyAsync(w.st, &S, sizeof S, hipMemcpyHostToDevice, ctx->stream));
     for (int k = 0; k < 3; ++k)
         if (launch_sweep(w, ctx->main.d_work, 0, ctx->stream)) return fail(ctx, MDOT_E_DEVICE, "sweep launch failed");
     HIPCHK(ctx, hipEventRecord(ctx->t0, ctx->stream));
@@ -1254,24 +1270,9 @@ int mdot_bench_sweep_flushed(mdot_ctx* ctx, const mdot_cost_desc* cost, const do
         return fail(ctx, MDOT_E_ARG, "bad argument");
     if (precision != MDOT_PREC_F32 && precision != MDOT_PREC_F64) return fail(ctx, MDOT_E_ARG, "bad precision");
     HIPCHK(ctx, hipSetDevice(ctx->device));
-    const int exp64 = precision == MDOT_PREC_F64;
-    rc = standalone_setup(ctx, ctx->main, cost, u, v, gamma, nullptr, exp64, 1, nullptr, nullptr, 0.0, nullptr, nullptr);
-    if (rc) return rc;
-    rc = run_steps(ctx, 1);
+    rc = bench_setup(ctx, cost, u, v, gamma, precision == MDOT_PREC_F64);
     if (rc) return rc;
     const Work& w = ctx->main.host_work;
-    const int mn = rows_of(cost) + cost->n;
-    HIPCHK(ctx, hipMemcpyAsync(w.lz, w.lzt, mn * sizeof(double), hipMemcpyDeviceToDevice, ctx->stream));
-    State& S = *ctx->h_state;
-    HIPCHK(ctx, hipMemcpyAsync(&S, w.st, sizeof S, hipMemcpyDeviceToHost, ctx->stream));
-    HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-    S.done = 0;
-    S.standalone = 1;
-    S.sweep_mode = SM_LSE;
-    S.ls_phase = LS_STANDALONE;
-    S.exp64 = exp64;
-    S.vec_action = 0;
-    HIPCHK(ctx, hipMemcpyAsync(w.st, &S, sizeof S, hipMemcpyHostToDevice, ctx->stream));
     std::vector<hipEvent_t> ev(2 * iters, nullptr);
     int made = 0;
     for (; made < 2 * iters; ++made)

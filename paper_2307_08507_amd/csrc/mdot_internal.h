@@ -64,7 +64,7 @@ constexpr int kFinSmall = 0, kFinMid = 1, kFinAll = 2;
 constexpr int fin_instance(int fin_per, int nrt) { return fin_per == 8 ? kFinSmall : (nrt <= 256 ? kFinMid : kFinAll); }
 
 // What the next sweep does.
-enum SweepMode : int32_t { SM_NONE = 0, SM_LSE = 1, SM_R1 = 2, SM_R2 = 3, SM_MAX = 4 };
+enum SweepMode : int32_t { SM_NONE = 0, SM_LSE = 1, SM_R1 = 2, SM_R2 = 3 };
 // Phase of an LSE sweep.
 enum LsPhase : int32_t { LS_INIT = 0, LS_TRIAL = 1, LS_FORCE = 2, LS_STANDALONE = 3 };
 // O(n) work the vector kernel applies before the next sweep (bit mask, applied in this order).
@@ -105,7 +105,6 @@ enum Dot : int {
     D_RFP2 = 4,
     D_CGP1 = 5,  // sum_j c_j g''_j
     D_CGP2 = 6,
-    // max pass
     kNDot = 8
 };
 
@@ -193,8 +192,29 @@ struct Control {
     Work w;
     State st[2];
     DevParams prm;
-    double bdots[kFinMaxGrid * kNDot];
+    double range[4];  // standalone calls: raw cost range, and 1 where a cloud's boxes settle it
+    double bdots[kFinMaxGrid * kNDot];  // (standalone calls on points: first the partial boxes)
 };
+
+// Standalone sweeps (mdot_lse2, mdot_round_certify): the caller's vectors, and the summary the
+// last kernel writes into host memory.
+struct AloneIn {
+    const double *u, *v, *shift, *u_prev, *v_prev;  // the last three may be null
+};
+struct AloneOut {
+    int32_t valid, retry, status, done;  // valid: scaled cost in [0, 1]; retry: LSE needs FP64 exp
+    double scale, ub, lb, me;
+};
+constexpr int kBoxBlocks = 32;  // workgroups (and partial boxes) over the points of a cloud
+static_assert(kBoxBlocks * 32 <= kFinMaxGrid * kNDot, "partial boxes fit the dots array");
+// where the raw cost range of a standalone call is found
+constexpr int kRangeDone = 0, kRangeTiles = 1, kRangeBox = 2;
+// scale * raw in [0, 1] up to rounding, for raw values in [lo, hi] (NaN: non-finite entries)
+constexpr double kRangeSlack = 1e-12;
+constexpr bool range_valid(double scale, double lo, double hi)
+{
+    return scale * lo >= -kRangeSlack && scale * hi <= 1.0 + kRangeSlack;
+}
 
 // Problems in flight in one batched launch. Every item has its own Work, state slots and
 // counters, so its results do not depend on the rest of the batch.
@@ -278,7 +298,20 @@ int launch_step(const Work& hw, const Work* wd, int parity, void* stream);  // s
 int launch_sweep(const Work& hw, const Work* wd, int parity, void* stream); // the LSE sweep kernel alone
 int launch_init(const Work* wd, void* stream);                               // state + first stage
 int launch_intake(const Work* wd, double* out8, void* stream);
-int launch_cost_range(const Work& hw, const Work* wd, double* part, void* stream);
+// Range partials of every tile; box: skipped where the cloud's boxes (in the dots array) settle it.
+int launch_cost_range(const Work& hw, const Work* wd, double* part, int box, void* stream);
+// Standalone sweeps. The finalize kernel and the decide kernel of one step alone; the set-up
+// (boxes: also the point cloud's); row maxima -> shifts, with the cost range; the sweep with the
+// cost range (dense); the scale of a cloud from its range partials; verdict and outputs.
+int launch_finalize(const Work& hw, const Work* wd, int parity, void* stream);
+int launch_decide(const Work* wd, int parity, void* stream);
+int launch_alone_setup(const Work& w, const State& s, const DevParams& prm, const AloneIn& in, Work* wd, int boxes,
+                       void* stream);
+int launch_row_max(const Work& hw, const Work* wd, double* part, void* stream);
+int launch_sweep_range(const Work& hw, const Work* wd, double* part, void* stream);
+int launch_pick_scale(Work* wd, const double* part, void* stream);
+int launch_alone_out(const Work& hw, Work* wd, int slot, const double* part, int where, int lse, int e64, double* lr_out,
+                     double* lc_out, AloneOut* out, void* stream);
 int launch_finish(const Work* wd, double* u_out, double* v_out, void* stream);
 // FP16 copy of a dense FP32 (src_dtype MDOT_DT_F32) or FP64 cost; part[b] = max |C16 - C| of block b.
 int launch_to_f16(const void* src, int src_dtype, void* dst, size_t count, double* part, int nblocks, void* stream);

@@ -144,55 +144,50 @@ struct DenseCost {
                 typename std::conditional<DT == MDOT_DT_F32, float4, uint2>::type>::type;
     __amdgpu_buffer_rsrc_t rs;
     int n;
-    bool vec;
-    __device__ __forceinline__ DenseCost(const Work& w, int i0) : n(w.n), vec((w.n & 3) == 0)
+    int odd;  // 16-bit types: 2 when the tile's first row starts in the upper half of a dword
+    __device__ __forceinline__ DenseCost(const Work& w, int i0) : n(w.n), odd(0)
     {
         const char* base = (const char*)w.cost + (size_t)i0 * w.n * kBytes;
-        const size_t rem = ((size_t)w.m - i0) * w.n * kBytes;
-        rs = __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, (int)(rem > 0x7fffffffu ? 0x7fffffffu : rem),
+        size_t rem = ((size_t)w.m - i0) * w.n * kBytes;
+        if constexpr (kBytes == 2) {
+            // based at the dword that holds the first element and ending with the dword that
+            // holds the last one, so that no valid element fails the per-dword range check
+            odd = (int)((uintptr_t)base & 2);
+            base -= odd;
+            rem = (rem + odd + 3) & ~(size_t)3;
+        }
+        rs = __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, (int)(rem > 0x7ffffffcu ? 0x7ffffffcu : rem),
                                                kBufDword3);
     }
     __device__ __forceinline__ void cols(int) {}
     // row r of the tile (global row i0 + r), columns j0..j0+3; columns >= n are masked by
-    // the caller, their values are unspecified (or 0 past the end of the matrix)
+    // the caller, their values are unspecified (or 0 past the end of the matrix). The loads need
+    // dword alignment only, which every FP32 and FP64 row and every 16-bit row of even length in
+    // a matrix that starts on a dword has; the range check is per dword. Other 16-bit rows read
+    // the three dwords around their 8 bytes and shift (n = 8191 BF16 sweep 64.8 -> 48.2 us, with
+    // four 2-byte loads per lane and row before).
     __device__ __forceinline__ Raw load(int r, int j0) const
     {
-        const int off = (r * n + j0) * kBytes;
         Raw v;
         if constexpr (DT == MDOT_DT_F64) {
-            if (vec) {
-                auto a = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
-                auto b = __builtin_amdgcn_raw_buffer_load_b128(rs, off + 16, 0, 0);
-                double2 da = *(double2*)&a, db = *(double2*)&b;
-                v.x = da.x; v.y = da.y; v.z = db.x; v.w = db.y;
-            } else {
-                auto a = __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0);
-                auto b = __builtin_amdgcn_raw_buffer_load_b64(rs, off + 8, 0, 0);
-                auto c = __builtin_amdgcn_raw_buffer_load_b64(rs, off + 16, 0, 0);
-                auto d = __builtin_amdgcn_raw_buffer_load_b64(rs, off + 24, 0, 0);
-                v.x = *(double*)&a; v.y = *(double*)&b; v.z = *(double*)&c; v.w = *(double*)&d;
-            }
+            const int off = (r * n + j0) * kBytes;
+            auto a = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
+            auto b = __builtin_amdgcn_raw_buffer_load_b128(rs, off + 16, 0, 0);
+            double2 da = *(double2*)&a, db = *(double2*)&b;
+            v.x = da.x; v.y = da.y; v.z = db.x; v.w = db.y;
         } else if constexpr (DT == MDOT_DT_F32) {
-            if (vec) {
-                auto a = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
-                v = *(float4*)&a;
-            } else {
-                v.x = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0));
-                v.y = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, off + 4, 0, 0));
-                v.z = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, off + 8, 0, 0));
-                v.w = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, off + 12, 0, 0));
-            }
+            auto a = __builtin_amdgcn_raw_buffer_load_b128(rs, (r * n + j0) * kBytes, 0, 0);
+            v = *(float4*)&a;
         } else {
-            if (vec) {
+            const int off = (r * n + j0) * kBytes + odd;
+            if (((n & 1) | odd) == 0) {
                 auto a = __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0);
                 v = *(uint2*)&a;
             } else {
-                uint32_t h0 = __builtin_amdgcn_raw_buffer_load_b16(rs, off, 0, 0);
-                uint32_t h1 = __builtin_amdgcn_raw_buffer_load_b16(rs, off + 2, 0, 0);
-                uint32_t h2 = __builtin_amdgcn_raw_buffer_load_b16(rs, off + 4, 0, 0);
-                uint32_t h3 = __builtin_amdgcn_raw_buffer_load_b16(rs, off + 6, 0, 0);
-                v.x = (h0 & 0xffffu) | (h1 << 16);
-                v.y = (h2 & 0xffffu) | (h3 << 16);
+                auto a = __builtin_amdgcn_raw_buffer_load_b96(rs, off & ~3, 0, 0);
+                const uint32_t sh = (uint32_t)(off & 2) * 8;
+                v.x = __builtin_amdgcn_alignbit(a[1], a[0], sh);
+                v.y = __builtin_amdgcn_alignbit(a[2], a[1], sh);
             }
         }
         return v;
@@ -383,6 +378,19 @@ struct PointCost {
 struct TileCtx {
     int I, J, i0, j0lane, lane, wave, tid;
 };
+
+__device__ __forceinline__ TileCtx tile_ctx(const Work& w, int blk)
+{
+    TileCtx t;
+    t.tid = threadIdx.x;
+    t.lane = t.tid & 63;
+    t.wave = t.tid >> 6;
+    t.I = blk / w.nct;
+    t.J = blk % w.nct;
+    t.i0 = t.I * kBR;
+    t.j0lane = t.J * kBC + t.lane * 4;
+    return t;
+}
 
 // Scalars a kernel needs from the state: the trial and the pending vector update.
 struct SweepArgs {
@@ -645,57 +653,58 @@ __device__ __forceinline__ double rows_reduce_f64(const double* rb, int lane)
     return s;
 }
 
-// Row and column maxima of X_ij (log units), used to seed the shifts of a standalone LSE.
-template <class Cost>
-__device__ void tile_max(const Work& w, const SweepArgs& S, const TileCtx& t, double* sm)
-{
-    double* sA = sm;
-    double* sCol = sm + 5 * kBR;
-    const int m = w.m, n = w.n;
-    if (t.tid < kBR) {
-        const int i = t.i0 + t.tid;
-        sA[t.tid] = (i < m) ? (w.z[i] + S.alpha * w.p[i]) * LOG2E_D : 0.0;
+// Smallest and largest raw entry seen, in the type T the entries are exact in, and whether a
+// non-finite one was.
+template <class T>
+struct RawRange {
+    T lo = INFINITY, hi = -INFINITY;
+    bool bad = false;
+    __device__ __forceinline__ void add(T c)
+    {
+        bad |= !isfinite(c);
+        lo = lo < c ? lo : c;
+        hi = hi > c ? hi : c;
     }
-    __syncthreads();
-    const double g2 = S.gamma * w.scale * LOG2E_D;
-    Cost cost(w, t.i0);
-    const int j0 = t.j0lane;
-    cost.cols(j0);
-    double V[4], colmx[4];
-    bool ok[4];
+    // the first `cols` of a lane's four consecutive columns
+    __device__ __forceinline__ void add4(const double c[4], int cols)
+    {
+        if (cols >= 4) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        ok[k] = j0 + k < n;
-        V[k] = ok[k] ? (w.z[m + j0 + k] + S.alpha * w.p[m + j0 + k]) * LOG2E_D : 0.0;
-        colmx[k] = -INFINITY;
-    }
-    for (int rr = 0; rr < kRPW; ++rr) {
-        const int r = t.wave * kRPW + rr;
-        const int i = t.i0 + r;
-        if (i >= m) break;
-        double c[4];
-        cost.row(r, j0, c);
-        double mx = -INFINITY;
+            for (int k = 0; k < 4; ++k) add((T)c[k]);
+        } else {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const double x = ok[k] ? fma(-g2, c[k], V[k]) + sA[r] : -INFINITY;
-            mx = fmax(mx, x);
-            colmx[k] = fmax(colmx[k], x);
+            for (int k = 0; k < 3; ++k)
+                if (k < cols) add((T)c[k]);
         }
-        mx = wave_max(mx);
-        if (t.lane == 0) w.rowmin[(size_t)t.J * m + i] = mx * LN2_D;
     }
+};
+// FP32 holds every FP32, FP16 and BF16 entry exactly
+template <class Cost>
+using RangeOf = RawRange<typename std::conditional<sizeof(typename Cost::Raw) <= 16 && !std::is_same<typename Cost::Raw, int>::value,
+                                                   float, double>::type>;
+
+// The first `rows` rows of a batch, kept apart from the exponentials that follow: interleaved with
+// them it takes more registers than there are.
+template <class Cost, int RB>
+__device__ __forceinline__ void range_rows(RangeOf<Cost>& range, const Cost& cost, const typename Cost::Raw* raw, int rows,
+                                           int cols)
+{
 #pragma unroll
-    for (int k = 0; k < 4; ++k) colmx[k] *= LN2_D;
-    col_combine_store(sCol, colmx, t, 2, w.colmin + (size_t)t.I * n, n, t.J * kBC);
+    for (int r = 0; r < RB; ++r)
+        if (r < rows) {
+            double c[4];
+            cost.decode(raw[r], c);
+            range.add4(c, cols);
+        }
+    __builtin_amdgcn_sched_barrier(0);
 }
 
 // The fused LSE tile (the hot loop of every line-search trial):
 //   e_ij = exp(X_ij - s_i),  row partial sum_j e_ij,  column partial sum_i w_i e_ij,
 // with w_i = exp(s_i - S_I). Exponent argument in FP64 (log2 units), exp2 in FP32 (E64 =
-// false) or FP64 (E64 = true).
-template <class Cost, bool E64>
-__device__ void tile_lse(const Work& w, const SweepArgs& S, const TileCtx& t, double* sm)
+// false) or FP64 (E64 = true). RANGE (dense costs) adds the tile's raw entries to `range`.
+template <class Cost, bool E64, bool RANGE = false>
+__device__ void tile_lse(const Work& w, const SweepArgs& S, const TileCtx& t, double* sm, RangeOf<Cost>* range = nullptr)
 {
     double* sA = sm;
     double* sWt = sm + kBR;
@@ -735,7 +744,7 @@ __device__ void tile_lse(const Work& w, const SweepArgs& S, const TileCtx& t, do
     constexpr bool kCanStage = std::is_same<Cost, DenseCost<MDOT_DT_F32>>::value && RB < kRPW;
     bool staged = false;
     if constexpr (kCanStage) {
-        staged = cost.vec && w.nrt * w.nct > w.stage_min_tiles;
+        staged = (n & 3) == 0 && w.nrt * w.nct > w.stage_min_tiles;
         if (staged) {
 #pragma unroll
             for (int r = 0; r < RB; ++r)
@@ -801,6 +810,7 @@ __device__ void tile_lse(const Work& w, const SweepArgs& S, const TileCtx& t, do
                         if (!kRowGuard || b + r < nrows) raw[r] = cost.load(rbase + b + r, j0);
                 }
             }
+            if constexpr (RANGE) range_rows<Cost, RB>(*range, cost, raw, nrows - b, n - j0);
 #pragma unroll
             for (int r0 = 0; r0 < RB; ++r0) {
                 const int r = b + r0;
@@ -858,6 +868,7 @@ __device__ void tile_lse(const Work& w, const SweepArgs& S, const TileCtx& t, do
 #pragma unroll
                 for (int r = b - RB; r < b; ++r) myRegion[r * 64 + t.lane] = rp[r];
             }
+            if constexpr (RANGE) range_rows<Cost, RB>(*range, cost, raw, nrows - b, n - j0);
 #pragma unroll
             for (int r0 = 0; r0 < RB; ++r0) {
                 const int r = b + r0;
@@ -1098,19 +1109,18 @@ __device__ __forceinline__ bool in_range(double s, bool e64)  // shifted sum rep
 
 // Tile partials of one entry, combined (the fields a sweep mode uses):
 //   a: sum of the LSE partials (columns: each scaled by exp(S_I - M))
-//   b: min (R1, R2) or max (max pass) of the first minima array
+//   b: min of the first minima array (R1, R2)
 //   c: min of the second minima array (finite-difference variant)
 //   d, e: sums of the second and third row partials (R2)
 struct Comb {
     double a, b, c, d, e;
 };
 
-template <int OP>  // 0: fma(x, f, acc), 1: min, 2: max (red_op follows the same codes)
+template <int OP>  // 0: fma(x, f, acc), 1: min (red_op follows the same codes)
 __device__ __forceinline__ double fold_op(double acc, double x, double f)
 {
     if constexpr (OP == 0) return fma(x, f, acc);
-    else if constexpr (OP == 1) return fmin(acc, x);
-    else return fmax(acc, x);
+    else return fmin(acc, x);
 }
 
 // Lane l of an entry's L-lane group folds partials l, l + L, l + 2L, ... of the m partials at
@@ -1120,7 +1130,7 @@ template <int OP, int B = 8>
 __device__ __forceinline__ double lane_fold(const double* __restrict__ base, size_t stride, int l, int L, int m,
                                             const double* __restrict__ fac, bool use)
 {
-    double acc = (OP == 0) ? 0.0 : (OP == 1 ? INFINITY : -INFINITY);
+    double acc = (OP == 0) ? 0.0 : INFINITY;
     if (!use) return acc;
     for (int q0 = l; q0 < m; q0 += B * L) {
         double x[B], f[B];
@@ -1146,7 +1156,7 @@ __device__ __forceinline__ double lane_fold(const double* __restrict__ base, siz
 template <int OP>
 __device__ __forceinline__ double group_fold(double v, int L)
 {
-    const double id = (OP == 0) ? 0.0 : (OP == 1 ? INFINITY : -INFINITY);
+    const double id = (OP == 0) ? 0.0 : INFINITY;
     if (L >= 2) v = red_op<OP>(v, dpp_d<0x101>(id, v));
     if (L >= 4) v = red_op<OP>(v, dpp_d<0x102>(id, v));
     if (L >= 8) v = red_op<OP>(v, dpp_d<0x104>(id, v));
@@ -1172,8 +1182,6 @@ __device__ __forceinline__ Comb combine(const Work& w, int mode, int k, bool val
     Comb cb{0.0, INFINITY, INFINITY, 0.0, 0.0};
     if (mode == SM_LSE) {
         cb.a = group_fold<0>(lane_fold<0, BL>((row ? w.rowpart : w.colpart) + ix, st, l, L, np, row ? nullptr : fac, valid), L);
-    } else if (mode == SM_MAX) {
-        cb.b = group_fold<2>(lane_fold<2>((row ? w.rowmin : w.colmin) + ix, st, l, L, np, nullptr, valid), L);
     } else {
         const double* mn = (row ? w.rowmin : w.colmin) + ix;
         cb.b = group_fold<1>(lane_fold<1>(mn, st, l, L, np, nullptr, valid), L);
@@ -1227,9 +1235,7 @@ __device__ __forceinline__ void finalize_entry(const Work& w, const SweepArgs& a
     const int m = w.m, n = w.n;
     if (k < m) {  // row i = k
         const int i = k;
-        if (mode == SM_MAX) {
-            w.lz[i] = cb.b;
-        } else if (mode == SM_LSE) {
+        if (mode == SM_LSE) {
             const double sum = cb.a;
             const double l = fma(a.alpha, e.p, e.lz) + log(sum);  // shift used by the sweep
             lse_terms(w, e, g_cur, k, l, sum, e64, pre, true, v);
@@ -1250,9 +1256,7 @@ __device__ __forceinline__ void finalize_entry(const Work& w, const SweepArgs& a
         return;
     }
     const int j = k - m;  // column
-    if (mode == SM_MAX) {
-        w.lz[m + j] = cb.b;
-    } else if (mode == SM_LSE) {
+    if (mode == SM_LSE) {
         const double sum = cb.a;
         const double l = M + log(sum);
         lse_terms(w, e, g_cur, k, l, sum, e64, pre, false, v);
@@ -1413,10 +1417,6 @@ __device__ __forceinline__ void decide(State& S, const DevParams& P, const doubl
 {
     const int mode = S.sweep_mode;
     S.vec_action = 0;
-    if (mode == SM_MAX) {  // standalone LSE: the row maxima become the row shifts
-        S.sweep_mode = SM_LSE;
-        return;
-    }
     if (mode == SM_LSE) {
         // D_BAD counts range failures plus kOutrUnit per ratio outside [0.01, 100] (precond)
         const double outr = floor(sum[D_BAD] * (1.0 / kOutrUnit));
@@ -1600,8 +1600,7 @@ __device__ __forceinline__ void sweep_tiles(const Work& w, const SweepArgs& a, c
 {
     using Cost = typename CostOf<base_code(CC)>::T;
     if constexpr (!ROUND) {
-        if (mode == SM_MAX) tile_max<Cost>(w, a, t, smem);
-        else tile_lse<Cost, E64>(w, a, t, smem);
+        tile_lse<Cost, E64>(w, a, t, smem);
     } else {
         if (mode == SM_R1) tile_r1<Cost, E64>(w, a, t, smem);
         else tile_r2<Cost, E64>(w, a, t, smem);
@@ -1614,14 +1613,7 @@ template <int CC, bool ROUND>
 __device__ __forceinline__ void sweep_kernel_body(const Work& w, const SweepArgs& a, int mode, bool e64, int blk,
                                                   double* smem)
 {
-    TileCtx t;
-    t.tid = threadIdx.x;
-    t.lane = t.tid & 63;
-    t.wave = t.tid >> 6;
-    t.I = blk / w.nct;
-    t.J = blk % w.nct;
-    t.i0 = t.I * kBR;
-    t.j0lane = t.J * kBC + t.lane * 4;
+    const TileCtx t = tile_ctx(w, blk);
     if (e64) sweep_tiles<CC, true, ROUND>(w, a, t, mode, smem);
     else sweep_tiles<CC, false, ROUND>(w, a, t, mode, smem);
 }
@@ -2018,6 +2010,332 @@ __global__ void k_chunk_done(const Work* __restrict__ wp, int* out, int* seq)
     *seq = s + 1;
 }
 
+// ------------------------------------------------------------------ standalone sweeps
+// mdot_lse2 and mdot_round_certify on given potentials, with no host round trip between their
+// kernels:
+//   k_alone_setup  control block, z = (u, v), shifts, zeros (and bounds of a point cloud)
+//   k_row_max      without given shifts: row maxima of X_ij per tile, and the raw cost range
+//   k_fold_max     row maxima -> shifts; its last workgroup reduces the range
+//   sweep, k_fin   the solver's kernels (k_sweep_range where the range is still unknown)
+//   k_alone_out    range verdict, out-of-range rows, outputs, summary in host memory
+// The cost has to lie in [0, 1] after scaling, which takes every entry; its smallest and largest
+// raw value come out of a pass that reads it anyway, and outputs are written only if they do.
+// A point cloud whose bounding boxes already bound scale * distance by 1 needs no such pass.
+
+// Range of one tile over the workgroup -> part[0..1] ({lo, hi}; hi NaN with a non-finite entry).
+template <class R>
+__device__ __forceinline__ void block_range(const R& rg, double* part, int tid, double* sred)
+{
+    const double lo = wave_min((double)rg.lo), hi = wave_max((double)rg.hi);
+    const bool bad = __any(rg.bad);
+    __syncthreads();
+    if ((tid & 63) == 0) {
+        sred[tid >> 6] = lo;
+        sred[4 + (tid >> 6)] = bad ? NAN : hi;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        double a = sred[0], b = sred[4];
+        for (int q = 1; q < 4; ++q) {
+            a = fmin(a, sred[q]);
+            b = (b != b || sred[4 + q] != sred[4 + q]) ? NAN : fmax(b, sred[4 + q]);
+        }
+        part[0] = a;
+        part[1] = b;
+    }
+}
+
+// Reduce the tiles' ranges with the whole workgroup; every thread returns the result.
+__device__ __forceinline__ void reduce_range(const double* part, int ntiles, double* lo, double* hi, double* sred)
+{
+    const int tid = threadIdx.x, nw = blockDim.x >> 6;
+    double a = INFINITY, b = -INFINITY;
+    bool bad = false;
+#pragma unroll 8
+    for (int t = tid; t < ntiles; t += blockDim.x) {
+        const double2 p = ((const double2*)part)[t];
+        a = fmin(a, p.x);
+        bad |= p.y != p.y;
+        b = fmax(b, p.y);
+    }
+    a = wave_min(a);
+    b = wave_max(b);
+    bad = __any(bad);
+    if ((tid & 63) == 0) {
+        sred[tid >> 6] = a;
+        sred[16 + (tid >> 6)] = bad ? NAN : b;
+    }
+    __syncthreads();
+    a = sred[0];
+    b = sred[16];
+    for (int q = 1; q < nw; ++q) {
+        a = fmin(a, sred[q]);
+        b = (b != b || sred[16 + q] != sred[16 + q]) ? NAN : fmax(b, sred[16 + q]);
+    }
+    __syncthreads();
+    *lo = a;
+    *hi = b;
+}
+
+// Bounding boxes of the two point sets, from the kBoxBlocks partial boxes k_alone_setup left at
+// `box` ([block][set][lo, hi][8 coordinates]): true if they bound scale * distance by 1, with
+// every coordinate finite. |x - y| and the sums below round monotonically and in the order of
+// PointCost::decode, so no entry can exceed the bound.
+__device__ __forceinline__ bool box_settles(const double* box, int d, int kind, double scale)
+{
+    const int lane = threadIdx.x & 63;
+    static_assert(kBoxBlocks <= 64, "one lane per partial box");
+    double s = 0.0;
+    for (int e = 0; e < d; ++e) {
+        const bool in = lane < kBoxBlocks;
+        const double* b = box + (size_t)lane * 32;
+        const double xlo = wave_min(in ? b[e] : INFINITY), xhi = wave_max(in ? b[8 + e] : -INFINITY);
+        const double ylo = wave_min(in ? b[16 + e] : INFINITY), yhi = wave_max(in ? b[24 + e] : -INFINITY);
+        const double t = fmax(fabs(xhi - ylo), fabs(yhi - xlo));
+        s = kind == MDOT_COST_POINTS_SQEUCLID ? fma(t, t, s) : s + t;
+    }
+    return scale * s <= 1.0;  // false for NaN (a non-finite coordinate makes its box NaN)
+}
+
+__global__ void __launch_bounds__(256) k_alone_setup(Control* __restrict__ ctl, Work w, State s, DevParams prm, AloneIn in,
+                                                     int fill_blocks)
+{
+    const int tid = threadIdx.x, m = w.m, n = w.n;
+    if ((int)blockIdx.x >= fill_blocks) {  // bounding boxes of a slice of the points
+        const float* X = (const float*)w.cost;
+        const int b = blockIdx.x - fill_blocks, d = w.d;
+        __shared__ double sred[4][2];
+        double* box = ctl->bdots + (size_t)b * 32;
+        for (int set = 0; set < 2; ++set) {
+            const int cnt = set ? n : m;
+            const float* P = X + (set ? (size_t)m * d : 0);
+            for (int e = 0; e < d; ++e) {
+                float lo = INFINITY, hi = -INFINITY;
+                bool bad = false;
+                for (int i = b * 256 + tid; i < cnt; i += kBoxBlocks * 256) {
+                    const float v = P[(size_t)i * d + e];
+                    bad |= !isfinite(v);
+                    lo = fminf(lo, v);
+                    hi = fmaxf(hi, v);
+                }
+                const double l = wave_min((double)lo), h = wave_max((double)hi);
+                bad = __any(bad);
+                if ((tid & 63) == 0) {
+                    sred[tid >> 6][0] = l;
+                    sred[tid >> 6][1] = bad ? NAN : h;
+                }
+                __syncthreads();
+                if (tid == 0) {
+                    double a = sred[0][0], c = sred[0][1];
+                    bool nan = c != c;
+                    for (int q = 1; q < 4; ++q) {
+                        a = fmin(a, sred[q][0]);
+                        nan |= sred[q][1] != sred[q][1];
+                        c = fmax(c, sred[q][1]);
+                    }
+                    // a non-finite coordinate: an infinite box settles nothing
+                    box[set * 16 + e] = nan ? -INFINITY : a;
+                    box[set * 16 + 8 + e] = nan ? INFINITY : c;
+                }
+                __syncthreads();
+            }
+        }
+        return;
+    }
+    if (blockIdx.x == 0) {
+        if (tid == 0) ctl->w = w;
+        if (tid == 64) ctl->st[0] = s;
+        if (tid == 128) ctl->prm = prm;
+    }
+    const int k = blockIdx.x * 256 + tid;
+    if (k >= m + n) return;
+    const bool row = k < m;
+    const int j = k - m;
+    w.rt[k] = 0.0;
+    w.logt[k] = 0.0;
+    w.z[k] = row ? in.u[k] : in.v[j];
+    w.zprev[k] = in.u_prev ? (row ? in.u_prev[k] : in.v_prev[j]) : 0.0;
+    w.zbest[k] = 0.0;
+    w.p[k] = 0.0;
+    w.g[k] = 0.0;
+    w.lz[k] = (row && in.shift) ? in.shift[k] : 0.0;
+    w.lzt[k] = 0.0;
+    if (row) w.xr[k] = 0.0;
+    else {
+        w.yc[j] = 0.0;
+        w.errc[j] = 0.0;
+    }
+}
+
+// Row maxima of X_ij = u_i + v_j - gamma C_ij over one tile, and the tile's raw cost range. The
+// row term is added to the maximum over the columns: rounding is monotone, so it is the maximum
+// of the rounded sums (any shift near the maximum serves). Bound by the read of the cost: every row of a wave is in flight before the
+// first is used (32-byte rows eight at a time), and the lanes' maxima meet once per 16 rows, in LDS.
+// n = 16384 FP32: 191 us (5.6 TB/s); with a row per load, a wave reduction per row and the range in
+// a pass of its own it was 318 + 194 us.
+template <int CC>
+__global__ void __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4)))
+k_row_max(const Work* __restrict__ wp, double* __restrict__ part)
+{
+    using Cost = typename CostOf<CC>::T;
+    __shared__ double smem[4 * kRPW * 64];
+    const Work& w = *wp;
+    const double gamma = ctl_of(w).st[0].gamma;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int I = blockIdx.x / w.nct, J = blockIdx.x % w.nct, i0 = I * kBR, j0 = J * kBC + lane * 4;
+    const int m = w.m, n = w.n, rbase = wave * kRPW, nrows = min(kRPW, m - (i0 + rbase));
+    const double g2 = gamma * w.scale * LOG2E_D;
+    Cost cost(w, i0);
+    cost.cols(j0);
+    constexpr bool kPoints = std::is_same<typename Cost::Raw, int>::value;
+    constexpr int RB = kPoints ? 1 : (sizeof(typename Cost::Raw) <= 16 ? kRPW : kRPW / 2);
+    double V[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) V[k] = (j0 + k < n) ? w.z[m + j0 + k] * LOG2E_D : -INFINITY;
+    RangeOf<Cost> rg;
+    double* mine = smem + wave * kRPW * 64;
+    auto take = [&](int r, const double c[4]) {
+        rg.add4(c, n - j0);
+        double mx = -INFINITY;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) mx = fmax(mx, fma(-g2, c[k], V[k]));
+        mine[r * 64 + lane] = mx;
+    };
+    if constexpr (kPoints) {
+        for (int r = 0; r < nrows; ++r) {
+            double c[4];
+            cost.row(rbase + r, j0, c);
+            take(r, c);
+        }
+    } else {
+#pragma unroll
+        for (int b = 0; b < kRPW; b += RB) {
+            typename Cost::Raw raw[RB];
+#pragma unroll
+            for (int r = 0; r < RB; ++r) raw[r] = cost.load(rbase + b + r, j0);
+#pragma unroll
+            for (int r = 0; r < RB; ++r)
+                if (b + r < nrows) {
+                    double c[4];
+                    cost.decode(raw[r], c);
+                    take(b + r, c);
+                }
+        }
+    }
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    // four lanes per row, each in the order k ^ row, so that the reads hit distinct banks
+    const int rr = lane >> 2, q = lane & 3;
+    double mx = -INFINITY;
+    if (rr < nrows) {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) mx = fmax(mx, mine[rr * 64 + q * 16 + (k ^ rr)]);
+    }
+    mx = fmax(mx, dpp_d<0xb1>(-INFINITY, mx));  // quad_perm [1,0,3,2]
+    mx = fmax(mx, dpp_d<0x4e>(-INFINITY, mx));  // quad_perm [2,3,0,1]
+    if (q == 0 && rr < nrows) {
+        const int i = i0 + rbase + rr;
+        w.rowmin[(size_t)J * m + i] = fma(w.z[i], LOG2E_D, mx) * LN2_D;
+    }
+    block_range(rg, part + 2 * blockIdx.x, tid, smem);
+}
+
+// Row shifts = maxima over the column tiles, four threads per row; the last workgroup reduces the
+// cost range. A chain of loads per thread is what takes the time: with one thread per row (and 256
+// threads for the range) n = 16384 took 27 us, 12 us now.
+__global__ void __launch_bounds__(1024) k_fold_max(const Work* __restrict__ wp, const double* __restrict__ part)
+{
+    __shared__ double sred[1024];
+    const Work& w = *wp;
+    const int m = w.m, nct = w.nct, tid = threadIdx.x;
+    if (blockIdx.x == gridDim.x - 1) {
+        double lo, hi;
+        reduce_range(part, w.nrt * nct, &lo, &hi, sred);
+        if (tid == 0) {
+            ctl_of(w).range[0] = lo;
+            ctl_of(w).range[1] = hi;
+        }
+        return;
+    }
+    const int i = blockIdx.x * 256 + (tid & 255);
+    double mx = -INFINITY;
+    if (i < m) {
+#pragma unroll 8
+        for (int J = tid >> 8; J < nct; J += 4) mx = fmax(mx, w.rowmin[(size_t)J * m + i]);
+    }
+    sred[tid] = mx;
+    __syncthreads();
+    if (tid < 256 && i < m) w.lz[i] = fmax(fmax(mx, sred[tid + 256]), fmax(sred[tid + 512], sred[tid + 768]));
+}
+
+// Range of a point cloud whose scale the library chooses (1 / the largest raw value).
+__global__ void __launch_bounds__(1024) k_pick_scale(Work* __restrict__ wp, const double* __restrict__ part)
+{
+    __shared__ double sred[32];
+    double lo, hi;
+    reduce_range(part, wp->nrt * wp->nct, &lo, &hi, sred);
+    if (threadIdx.x == 0) wp->scale = hi > 0.0 ? 1.0 / hi : 1.0;
+}
+
+// The LSE sweep of a dense cost whose range is still unknown (shifts given by the caller).
+template <int CC>
+__global__ void __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4)))
+k_sweep_range(const Work* __restrict__ wp, double* __restrict__ part)
+{
+    using Cost = typename CostOf<CC>::T;
+    __shared__ double smem[kSmemAll];
+    const Work& w = *wp;
+    const State* Sp = state_slot(w, 0);
+    const SweepArgs a = args_of(Sp);
+    const TileCtx t = tile_ctx(w, blockIdx.x);
+    RangeOf<Cost> rg;
+    if (Sp->exp64 != 0) tile_lse<Cost, true, true>(w, a, t, smem, &rg);
+    else tile_lse<Cost, false, true>(w, a, t, smem, &rg);
+    block_range(rg, part + 2 * blockIdx.x, t.tid, smem);
+}
+
+// End of a standalone call: check the scaled cost range (`where` it is found), then for an LSE
+// (run with FP64 exponentials if e64) look for rows and columns out of range and copy the log-sums
+// out, or ask for the FP64 re-run, which reads state slot 0; for a certificate report the final
+// state in slot `slot`. Every workgroup forms the verdict and copies its share; the first reports.
+__global__ void __launch_bounds__(1024) k_alone_out(Work* __restrict__ wp, int slot, const double* __restrict__ part,
+                                                    int where, int lse, int e64, double* __restrict__ lr_out,
+                                                    double* __restrict__ lc_out, AloneOut* __restrict__ out)
+{
+    __shared__ double sred[32];
+    const Work& w = *wp;
+    Control& C = ctl_of(w);
+    const int tid = threadIdx.x, m = w.m, n = w.n;
+    double lo = C.range[0], hi = C.range[1];
+    const double scale = w.scale;
+    if (where == kRangeBox && C.range[2] != 0.0) lo = hi = 0.0;  // settled by the boxes
+    else if (where != kRangeDone) reduce_range(part, w.nrt * w.nct, &lo, &hi, sred);
+    const bool valid = range_valid(scale, lo, hi);
+    const State& S = C.st[slot];
+    int status = S.status, retry = 0;
+    if (lse) {
+        const bool any = __syncthreads_or(tid < w.fin_nblk && C.bdots[(size_t)tid * kNDot + D_BAD] != 0.0);
+        static_assert(kFinMaxGrid <= 1024, "one thread per finalize workgroup");
+        retry = any && !e64;
+        status = any ? MDOT_W_RANGE : MDOT_OK;
+        if (valid && !retry && lr_out) {
+            const int step = gridDim.x * 1024;
+            for (int k = blockIdx.x * 1024 + tid; k < m + n; k += step) *(k < m ? lr_out + k : lc_out + (k - m)) = w.lzt[k];
+        }
+    }
+    if (blockIdx.x == 0 && tid == 0) {
+        out->valid = valid;
+        out->retry = retry;
+        out->status = status;
+        out->scale = scale;
+        out->ub = S.best_ub;
+        out->lb = S.best_lb;
+        out->me = S.best_me;
+        out->done = S.done;
+        if (retry) C.st[0].exp64 = 1;
+    }
+}
+
 // ------------------------------------------------------------------ set-up kernels
 __global__ void k_init(const Work* __restrict__ wp)
 {
@@ -2087,11 +2405,11 @@ __global__ void k_intake(const Work* __restrict__ wp, double* out8)
 // Cost range over a dense matrix or the maximum raw point distance: out2 = {min, max} of raw
 // values (non-finite entries make max NaN).
 template <class Cost>
-__device__ void cost_range_body(const Work& w, double* mn, double* mx)
+__device__ void cost_range_body(const Work& w, int tile, double* mn, double* mx)
 {
     const int m = w.m, n = w.n;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int I = blockIdx.x / w.nct, J = blockIdx.x % w.nct;
+    const int I = tile / w.nct, J = tile % w.nct;
     const int j0 = J * kBC + lane * 4;
     Cost cost(w, I * kBR);
     cost.cols(j0);
@@ -2113,28 +2431,38 @@ __device__ void cost_range_body(const Work& w, double* mn, double* mx)
     *mx = hi;
 }
 
+// `box`: the workgroups first look at the point cloud's bounding boxes, and return if these
+// settle that the cost is in range (workgroup 0 notes it for k_alone_out).
 template <int CC>
-__global__ void __launch_bounds__(kWG) k_cost_range(const Work* __restrict__ wp, double* part)
+__global__ void __launch_bounds__(kWG) k_cost_range(const Work* __restrict__ wp, double* part, int box)
 {
     const Work w = *wp;
-    double lo, hi;
-    cost_range_body<typename CostOf<base_code(CC)>::T>(w, &lo, &hi);
+    if (box) {
+        const bool settled = box_settles(ctl_of(*wp).bdots, w.d, w.cost_kind, w.scale);
+        if (blockIdx.x == 0 && threadIdx.x == 0) ctl_of(*wp).range[2] = settled ? 1.0 : 0.0;
+        if (settled) return;
+    }
     __shared__ double s0[kWG], s1[kWG];
     const int t = threadIdx.x;
-    s0[t] = lo;
-    s1[t] = hi;
-    __syncthreads();
-    for (int h = kWG / 2; h > 0; h >>= 1) {
-        if (t < h) {
-            s0[t] = fmin(s0[t], s0[t + h]);
-            double a = s1[t], b = s1[t + h];
-            s1[t] = (a != a || b != b) ? NAN : fmax(a, b);
+    for (int tile = blockIdx.x; tile < w.nrt * w.nct; tile += gridDim.x) {
+        double lo, hi;
+        cost_range_body<typename CostOf<base_code(CC)>::T>(w, tile, &lo, &hi);
+        s0[t] = lo;
+        s1[t] = hi;
+        __syncthreads();
+        for (int h = kWG / 2; h > 0; h >>= 1) {
+            if (t < h) {
+                s0[t] = fmin(s0[t], s0[t + h]);
+                double a = s1[t], b = s1[t + h];
+                s1[t] = (a != a || b != b) ? NAN : fmax(a, b);
+            }
+            __syncthreads();
+        }
+        if (t == 0) {
+            part[2 * tile] = s0[0];
+            part[2 * tile + 1] = s1[0];
         }
         __syncthreads();
-    }
-    if (t == 0) {
-        part[2 * blockIdx.x] = s0[0];
-        part[2 * blockIdx.x + 1] = s1[0];
     }
 }
 
@@ -2237,20 +2565,28 @@ int cost_code(const Work& w)
         default: F(kOccHi + CC_PTS_L18); break;                        \
     }
 
-int launch_step(const Work& hw, const Work* wd, int parity, void* stream)
+int launch_finalize(const Work& hw, const Work* wd, int parity, void* stream)
 {
     hipStream_t s = (hipStream_t)stream;
-    const int tiles = hw.nrt * hw.nct;
-#define L_(CC) hipLaunchKernelGGL(k_sweep<CC>, dim3(tiles), dim3(kWG), 0, s, wd, parity)
-    MDOT_CC_SWITCH(cost_code(hw), L_)
-#undef L_
     const int xcd = hw.fin_L >= 16 && hw.fin_nblk % 8 == 0;
     const int fv = fin_instance(hw.fin_per, hw.nrt);
     if (fv == kFinSmall) hipLaunchKernelGGL(k_fin<kFinSmall>, dim3(hw.fin_nblk), dim3(kVecWG), 0, s, wd, parity, xcd);
     else if (fv == kFinMid) hipLaunchKernelGGL(k_fin<kFinMid>, dim3(hw.fin_nblk), dim3(kVecWG), 0, s, wd, parity, xcd);
     else hipLaunchKernelGGL(k_fin<kFinAll>, dim3(hw.fin_nblk), dim3(kVecWG), 0, s, wd, parity, xcd);
-    hipLaunchKernelGGL(k_decide, dim3(1), dim3(kDecideWG), 0, s, wd, parity);
     return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+int launch_decide(const Work* wd, int parity, void* stream)
+{
+    hipLaunchKernelGGL(k_decide, dim3(1), dim3(kDecideWG), 0, (hipStream_t)stream, wd, parity);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+int launch_step(const Work& hw, const Work* wd, int parity, void* stream)
+{
+    int rc = launch_sweep(hw, wd, parity, stream);
+    if (!rc) rc = launch_finalize(hw, wd, parity, stream);
+    return rc ? rc : launch_decide(wd, parity, stream);
 }
 
 int launch_sweep(const Work& hw, const Work* wd, int parity, void* stream)
@@ -2259,6 +2595,55 @@ int launch_sweep(const Work& hw, const Work* wd, int parity, void* stream)
 #define L_(CC) hipLaunchKernelGGL(k_sweep<CC>, dim3(tiles), dim3(kWG), 0, (hipStream_t)stream, wd, parity)
     MDOT_CC_SWITCH(cost_code(hw), L_)
 #undef L_
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+int launch_alone_setup(const Work& w, const State& s, const DevParams& prm, const AloneIn& in, Work* wd, int boxes,
+                       void* stream)
+{
+    const int fill = (w.m + w.n + 255) / 256;
+    hipLaunchKernelGGL(k_alone_setup, dim3(fill + (boxes ? kBoxBlocks : 0)), dim3(256), 0, (hipStream_t)stream,
+                       reinterpret_cast<Control*>(wd), w, s, prm, in, fill);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+int launch_row_max(const Work& hw, const Work* wd, double* part, void* stream)
+{
+    hipStream_t s = (hipStream_t)stream;
+    const int tiles = hw.nrt * hw.nct;
+#define L_(CC) hipLaunchKernelGGL(k_row_max<CC>, dim3(tiles), dim3(kWG), 0, s, wd, part)
+    MDOT_CC_SWITCH_BASE(base_code(cost_code(hw)), L_)
+#undef L_
+    hipLaunchKernelGGL(k_fold_max, dim3((hw.m + 255) / 256 + 1), dim3(1024), 0, s, wd, (const double*)part);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+int launch_sweep_range(const Work& hw, const Work* wd, double* part, void* stream)
+{
+    hipStream_t s = (hipStream_t)stream;
+    const dim3 tiles(hw.nrt * hw.nct);
+    switch (base_code(cost_code(hw))) {
+        case CC_F64: hipLaunchKernelGGL(k_sweep_range<CC_F64>, tiles, dim3(kWG), 0, s, wd, part); break;
+        case CC_F32: hipLaunchKernelGGL(k_sweep_range<CC_F32>, tiles, dim3(kWG), 0, s, wd, part); break;
+        case CC_F16: hipLaunchKernelGGL(k_sweep_range<CC_F16>, tiles, dim3(kWG), 0, s, wd, part); break;
+        case CC_BF16: hipLaunchKernelGGL(k_sweep_range<CC_BF16>, tiles, dim3(kWG), 0, s, wd, part); break;
+        default: return -1;  // point costs take their bounding boxes
+    }
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+int launch_pick_scale(Work* wd, const double* part, void* stream)
+{
+    hipLaunchKernelGGL(k_pick_scale, dim3(1), dim3(1024), 0, (hipStream_t)stream, wd, part);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+int launch_alone_out(const Work& hw, Work* wd, int slot, const double* part, int where, int lse, int e64, double* lr_out,
+                     double* lc_out, AloneOut* out, void* stream)
+{
+    const int grid = lse ? std::min(16, (hw.m + hw.n + 4095) / 4096) : 1;
+    hipLaunchKernelGGL(k_alone_out, dim3(grid), dim3(1024), 0, (hipStream_t)stream, wd, slot, part, where, lse, e64,
+                       lr_out, lc_out, out);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -2303,10 +2688,12 @@ int launch_intake(const Work* wd, double* out8, void* stream)
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-int launch_cost_range(const Work& hw, const Work* wd, double* part, void* stream)
+int launch_cost_range(const Work& hw, const Work* wd, double* part, int box, void* stream)
 {
     const int tiles = hw.nrt * hw.nct;
-#define L_(CC) hipLaunchKernelGGL(k_cost_range<CC>, dim3(tiles), dim3(kWG), 0, (hipStream_t)stream, wd, part)
+    // with boxes most calls end at the look at them: no more workgroups than are resident at once
+    const int grid = box ? std::min(tiles, 2048) : tiles;
+#define L_(CC) hipLaunchKernelGGL(k_cost_range<CC>, dim3(grid), dim3(kWG), 0, (hipStream_t)stream, wd, part, box)
     MDOT_CC_SWITCH_BASE(base_code(cost_code(hw)), L_)
 #undef L_
     return hipGetLastError() == hipSuccess ? 0 : -1;
