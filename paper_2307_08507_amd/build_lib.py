@@ -37,7 +37,10 @@ def build(verbose: bool = False) -> str:
             # kernel arguments (a few pointers and ints) are preloaded into SGPRs at dispatch, so a
             # kernel's first dependent load does not wait for a kernarg-segment fetch
             cmd += [f"--offload-arch={ARCH}", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-                    "-munsafe-fp-atomics", "-mllvm", "-amdgpu-kernarg-preload-count=16"]
+                    "-munsafe-fp-atomics", "-mllvm", "-amdgpu-kernarg-preload-count=16",
+                    # the constants of exp and log stay where they are used: hoisted out of the loop of
+                    # the resident-steps kernel they take 60 registers and spill
+                    "-mllvm", "-disable-machine-licm"]
         else:
             pass
         if verbose:

@@ -32,6 +32,10 @@ using namespace mdot;
 namespace {
 
 constexpr int kChunk = 32;       // solver steps per graph launch (even: the state slot alternates)
+constexpr int kResidentRounds = 3;    // rounds per graph launch: resident steps (once, or in schedule
+constexpr int kResidentRuns = 3;      // mode, where stages follow each other, so often), then two
+constexpr int kResidentSingles = 2;   // single steps (an even number: Round's two sweeps)
+constexpr int kResidentMax = 4096;    // steps of one resident launch (tens of milliseconds)
 constexpr int kBatchChunk = 16;  // engine steps per graph launch (admission granularity, even)
 constexpr int kMaxN = MDOT_MAX_N;
 constexpr int kConvBlocks = 1024; // workgroups of the FP16 conversion (MIXED)
@@ -102,7 +106,7 @@ struct mdot_ctx {
     // address on this device was taken at context creation
     ProblemBufs fixed;
     unsigned char* d_fixed = nullptr;
-    State* h_state = nullptr;     // pinned
+    State* h_state = nullptr;     // pinned, with a word for the resident steps' abort flag behind it
     // done flags written by the last kernel of each graph chunk (pinned, mapped, fine-grained):
     // 2 for the single solves, then 2 x kMaxBatch for the engine, then the summary of a standalone
     // sweep (AloneOut, at kDoneInts); d_hdone is the device alias
@@ -119,7 +123,12 @@ struct mdot_ctx {
     hipGraphExec_t graph = nullptr;  // captured chunk of solver steps for `main`
     // what the graph was captured with: m, n and the sweep kernel instance (cost code, which also
     // tells the point dimension classes apart)
-    int graph_m = 0, graph_n = 0, graph_code = -1;
+    int graph_m = 0, graph_n = 0, graph_code = -1, graph_steps = 0;
+    // resident steps of single solves: the GPU's compute units, the exchange memory (allocated by
+    // the first solve that takes them), and whether a wait inside them has ever run out
+    int cus = 0;
+    StepsX* d_steps = nullptr;
+    bool steps_off = false;
     // serving engine
     hipStream_t side = nullptr;     // intake of admitted solves (does not wait for the chunk in flight)
     Slot slots[kMaxBatch];
@@ -598,42 +607,75 @@ static void fill_result(const State& S, double seconds, mdot_result* res)
     res->tilde_iters = S.tilde_iters;
 }
 
-static int ensure_graph(mdot_ctx* ctx)
+// How the steps of `main` run: 0 = one step per three kernels, else resident steps with this many
+// tiles per workgroup (steps_tiles), + 8 in schedule mode. The projector and preconditioner variants
+// take the one-step kernels.
+static int steps_mode(const mdot_ctx* ctx, const mdot_params& prm)
+{
+    if (ctx->steps_off || prm.projector || prm.precond) return 0;
+    const int nt = steps_tiles(ctx->main.host_work, ctx->cus);
+    return nt ? nt + (prm.gamma_f > 0.0 ? 8 : 0) : 0;
+}
+
+static int ensure_graph(mdot_ctx* ctx, int steps)
 {
     const Work& hw = ctx->main.host_work;
     const int code = cost_code(hw);
-    if (ctx->graph && ctx->graph_m == hw.m && ctx->graph_n == hw.n && ctx->graph_code == code) return MDOT_OK;
+    if (ctx->graph && ctx->graph_m == hw.m && ctx->graph_n == hw.n && ctx->graph_code == code && ctx->graph_steps == steps)
+        return MDOT_OK;
     if (ctx->graph) {
         (void)hipGraphExecDestroy(ctx->graph);
         ctx->graph = nullptr;
+    }
+    if (steps && !ctx->d_steps) {
+        HIPCHK(ctx, hipMalloc(&ctx->d_steps, sizeof(StepsX)));
+        // on this context's stream: the default stream may not be touched while another thread captures
+        if (launch_fill(reinterpret_cast<double*>(ctx->d_steps), sizeof(StepsX) / sizeof(double), 0.0, ctx->stream))
+            return fail(ctx, MDOT_E_DEVICE, "fill launch failed");
     }
     hipStream_t cap;
     HIPCHK(ctx, hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
     hipGraph_t g = nullptr;
     hipError_t e = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal);
+    int bad = 0;
     if (e == hipSuccess) {
-        for (int k = 0; k < kChunk; ++k) launch_step(hw, ctx->main.d_work, k & 1, cap);
-        launch_chunk_done(ctx->main.d_work, ctx->d_hdone, ctx->d_seq, cap);
+        const Work* wd = ctx->main.d_work;
+        if (steps) {
+            for (int k = 0; k < kResidentRounds; ++k) {
+                for (int j = 0; j < (steps & 8 ? kResidentRuns : 1); ++j) {
+                    bad |= launch_steps(hw, wd, ctx->d_steps, steps & 7, kResidentMax, cap);
+                    bad |= launch_settle(wd, cap);
+                }
+                for (int j = 0; j < kResidentSingles; ++j) bad |= launch_step(hw, wd, j & 1, cap);
+            }
+        } else {
+            for (int k = 0; k < kChunk; ++k) bad |= launch_step(hw, wd, k & 1, cap);
+        }
+        bad |= launch_chunk_done(wd, ctx->d_hdone, ctx->d_seq, cap);
         e = hipStreamEndCapture(cap, &g);
     }
-    if (e == hipSuccess) e = hipGraphInstantiate(&ctx->graph, g, nullptr, nullptr, 0);
+    if (e == hipSuccess && !bad) e = hipGraphInstantiate(&ctx->graph, g, nullptr, nullptr, 0);
     if (g) (void)hipGraphDestroy(g);
     (void)hipStreamDestroy(cap);
-    if (e != hipSuccess) {
+    if (e != hipSuccess || bad) {
         ctx->graph = nullptr;
         return fail(ctx, MDOT_E_DEVICE, "graph capture failed: %s", hipGetErrorString(e));
     }
     ctx->graph_m = hw.m;
     ctx->graph_n = hw.n;
     ctx->graph_code = code;
+    ctx->graph_steps = steps;
     return MDOT_OK;
 }
 
-// Run solver steps of `main` until the device sets done (or max_chunks chunks have run).
-static int run_steps(mdot_ctx* ctx, int max_chunks)
+// Run solver steps of `main` until the device sets done (or at least max_steps steps have run).
+static int run_steps(mdot_ctx* ctx, const mdot_params& prm, int64_t max_steps)
 {
-    int rc = ensure_graph(ctx);
+    const int steps = steps_mode(ctx, prm);
+    int rc = ensure_graph(ctx, steps);
     if (rc) return rc;
+    const int per_chunk = steps ? kResidentRounds * kResidentSingles : kChunk;  // the least a chunk advances
+    const int max_chunks = (int)std::min<int64_t>(max_steps / per_chunk + 1, 1 << 30);
     // slot 0 holds the newest state after an even chunk; the graph's last kernel copies its
     // done flag to h_done[chunk number & 1]
     const uint64_t base = ctx->solo_seq;
@@ -651,7 +693,14 @@ static int run_steps(mdot_ctx* ctx, int max_chunks)
         ++checked;
         if (done) break;
     }
+    uint32_t* aborted = reinterpret_cast<uint32_t*>(ctx->h_state + 1);
+    *aborted = 0;
+    if (steps) HIPCHK(ctx, hipMemcpyAsync(aborted, &ctx->d_steps->abort, sizeof(uint32_t), hipMemcpyDeviceToHost, ctx->stream));
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+    if (*aborted) {
+        ctx->steps_off = true;
+        return fail(ctx, MDOT_E_DEVICE, "a wait between the workgroups of a resident solver step ran out");
+    }
     return MDOT_OK;
 }
 
@@ -920,10 +969,11 @@ int mdot_ctx_create(int device, void* hip_stream, size_t hbm_budget_bytes, mdot_
     if (hipSetDevice(device) != hipSuccess) return MDOT_E_DEVICE;
     mdot_ctx* ctx = new mdot_ctx();
     ctx->device = device;
+    if (hipDeviceGetAttribute(&ctx->cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) ctx->cus = 0;
     load_tuning(ctx);
     ctx->stream = (hipStream_t)hip_stream;
     ctx->budget = hbm_budget_bytes;
-    bool ok = hipHostMalloc(&ctx->h_state, sizeof(State), hipHostMallocDefault) == hipSuccess &&
+    bool ok = hipHostMalloc(&ctx->h_state, sizeof(State) + sizeof(uint64_t), hipHostMallocDefault) == hipSuccess &&
               hipHostMalloc(&ctx->h_prm, sizeof(DevParams), hipHostMallocDefault) == hipSuccess &&
               hipHostMalloc(&ctx->h_done, kDoneInts * sizeof(int) + sizeof(AloneOut), hipHostMallocMapped | hipHostMallocCoherent) ==
                   hipSuccess &&
@@ -989,6 +1039,7 @@ int mdot_ctx_destroy(mdot_ctx* ctx)
         if (e) (void)hipEventDestroy(e);
     if (ctx->d_batch) (void)hipFree(ctx->d_batch);
     if (ctx->d_seq) (void)hipFree(ctx->d_seq);
+    if (ctx->d_steps) (void)hipFree(ctx->d_steps);
     for (auto& e : ctx->ev)
         if (e) (void)hipEventDestroy(e);
     for (auto& e : ctx->eng_ev)
@@ -1031,8 +1082,7 @@ int mdot_solve(mdot_ctx* ctx, const mdot_cost_desc* cost, const double* r, const
     HIPCHK(ctx, hipEventRecord(ctx->t0, ctx->stream));
     // hard cap on steps: every LSE sweep is one step, each stage adds at most a few more
     const int64_t max_steps = prm.max_sweeps > 0 ? 4 * prm.max_sweeps + 4096 : (int64_t)1 << 22;
-    const int max_chunks = (int)std::min<int64_t>(max_steps / kChunk + 1, 1 << 30);
-    rc = run_steps(ctx, max_chunks);
+    rc = run_steps(ctx, prm, max_steps);
     if (rc) return rc;
     if (ctx->main.host_work.dtype != cost->dtype) {  // MIXED: paused at the switch to the exact cost
         rc = read_state(ctx, ctx->main);
@@ -1043,7 +1093,7 @@ int mdot_solve(mdot_ctx* ctx, const mdot_cost_desc* cost, const double* r, const
             static const int32_t kResume = 0;
             HIPCHK(ctx, hipMemcpyAsync(&ctx->main.host_work.st[0].done, &kResume, sizeof kResume,
                                        hipMemcpyHostToDevice, ctx->stream));
-            rc = run_steps(ctx, max_chunks);
+            rc = run_steps(ctx, prm, max_steps);
             if (rc) return rc;
         }
     }

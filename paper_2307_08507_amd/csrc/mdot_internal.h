@@ -140,6 +140,7 @@ struct State {
     double stall_best;  // smallest ||grad||_1 of the stage when it last halved, at iteration stall_k
     int64_t k, sweeps, pncg_iters, ls_trials, cg_resets, ls_failures, fallbacks, cert_sweeps;
     int64_t stall_k, prec_switches, proxy_stages, tilde_iters;
+    int32_t undecided, pad_;  // 1: the dots of the last LSE sweep are there, its decision is not taken yet
 };
 
 // Device buffers of one problem (all FP64 unless noted). (m + n)-vectors hold the m rows, then
@@ -215,6 +216,17 @@ constexpr bool range_valid(double scale, double lo, double hi)
 {
     return scale * lo >= -kRangeSlack && scale * hi <= 1.0 + kRangeSlack;
 }
+
+// Exchange memory of the resident-steps kernel (k_steps), in device memory: zeroed once.
+constexpr int kStepsMaxGrid = 256;      // workgroups
+constexpr int kStepsMaxRowTiles = 128;  // row tiles (8192 rows)
+struct StepsX {
+    uint32_t arrive, pad0[31];  // workgroups that have started (kStepsAbort: start given up)
+    uint32_t leave, pad1[31];   // workgroups that have ended; the last one clears both
+    uint32_t abort, pad2[31];   // a wait inside the steps ran into its limit (never cleared)
+    double shift[3][kStepsMaxRowTiles];   // S_I of the row tiles, three steps in turn
+    double dots[3][kStepsMaxGrid][16];    // dots of the finalize blocks, one 128-byte line each
+};
 
 // Problems in flight in one batched launch. Every item has its own Work, state slots and
 // counters, so its results do not depend on the rest of the batch.
@@ -300,6 +312,11 @@ int launch_init(const Work* wd, void* stream);                               // 
 int launch_intake(const Work* wd, double* out8, void* stream);
 // Range partials of every tile; box: skipped where the cloud's boxes (in the dots array) settle it.
 int launch_cost_range(const Work& hw, const Work* wd, double* part, int box, void* stream);
+// Resident steps: tiles per workgroup (0: not for this problem), and the launch, which runs LSE
+// steps from state slot 0 until something else is due.
+int steps_tiles(const Work& hw, int cus);
+int launch_settle(const Work* wd, void* stream);  // the decision it may have left open
+int launch_steps(const Work& hw, const Work* wd, StepsX* x, int nt, int max_steps, void* stream);
 // Standalone sweeps. The finalize kernel and the decide kernel of one step alone; the set-up
 // (boxes: also the point cloud's); row maxima -> shifts, with the cost range; the sweep with the
 // cost range (dense); the scale of a cloud from its range partials; verdict and outputs.

@@ -106,26 +106,28 @@ __device__ __forceinline__ double wave_reduce(double v)
     return readlane_d(v, 63);
 }
 __device__ __forceinline__ double wave_sum(double v) { return wave_reduce<0>(v); }
-// kNDot sums at once, stage by stage: the same operations in the same order per value as
+// N sums at once, stage by stage: the same operations in the same order per value as
 // wave_sum, with the independent chains interleaved (one after another they run at the
 // latency of the DPP moves).
-__device__ __forceinline__ void wave_sum_dots(double v[kNDot])
+template <int N>
+__device__ __forceinline__ void wave_sums(double v[N])
 {
 #pragma unroll
-    for (int d = 0; d < kNDot; ++d) v[d] += dpp_d0<0x111>(v[d]);
+    for (int d = 0; d < N; ++d) v[d] += dpp_d0<0x111>(v[d]);
 #pragma unroll
-    for (int d = 0; d < kNDot; ++d) v[d] += dpp_d0<0x112>(v[d]);
+    for (int d = 0; d < N; ++d) v[d] += dpp_d0<0x112>(v[d]);
 #pragma unroll
-    for (int d = 0; d < kNDot; ++d) v[d] += dpp_d0<0x114>(v[d]);
+    for (int d = 0; d < N; ++d) v[d] += dpp_d0<0x114>(v[d]);
 #pragma unroll
-    for (int d = 0; d < kNDot; ++d) v[d] += dpp_d0<0x118>(v[d]);
+    for (int d = 0; d < N; ++d) v[d] += dpp_d0<0x118>(v[d]);
 #pragma unroll
-    for (int d = 0; d < kNDot; ++d) v[d] += dpp_d<0x142, 0xa>(0.0, v[d]);
+    for (int d = 0; d < N; ++d) v[d] += dpp_d<0x142, 0xa>(0.0, v[d]);
 #pragma unroll
-    for (int d = 0; d < kNDot; ++d) v[d] += dpp_d<0x143, 0xc>(0.0, v[d]);
+    for (int d = 0; d < N; ++d) v[d] += dpp_d<0x143, 0xc>(0.0, v[d]);
 #pragma unroll
-    for (int d = 0; d < kNDot; ++d) v[d] = readlane_d(v[d], 63);
+    for (int d = 0; d < N; ++d) v[d] = readlane_d(v[d], 63);
 }
+__device__ __forceinline__ void wave_sum_dots(double v[kNDot]) { wave_sums<kNDot>(v); }
 __device__ __forceinline__ double wave_min(double v) { return wave_reduce<1>(v); }
 __device__ __forceinline__ double wave_max(double v) { return wave_reduce<2>(v); }
 
@@ -221,6 +223,10 @@ struct DenseCost {
     __device__ __forceinline__ void bind_rows(void*, void*) {}
     __device__ __forceinline__ void row_setup(int, int, double, double&) {}
     __device__ __forceinline__ void prepare(double, const double*) {}
+    __device__ __forceinline__ double row_fixed(int, int) { return 0.0; }
+    static __device__ __forceinline__ double row_term(double, double, double a) { return a; }
+    __device__ __forceinline__ void cols_fixed(double) {}
+    __device__ __forceinline__ void bind_cols(double, const double*) {}
     __device__ __forceinline__ void args(const Raw& raw, double g2, const double V[4], double A, double x[4]) const
     {
         double c[4];
@@ -336,6 +342,36 @@ struct PointCost {
 #pragma unroll
                 for (int e = 0; e < D; ++e) y[k][e] *= 2.0 * g2;
             }
+        }
+    }
+    // The same in parts, for a kernel that runs many sweeps at one g2: the row's coordinates and
+    // |x_r|^2 (0 for L1), the scaled columns and |y_k|^2, and the step's own terms.
+    double YY[4];
+    __device__ __forceinline__ double row_fixed(int r, int i)
+    {
+        double a = 0.0;
+        row_setup(r, i, -1.0, a);  // fma(1, |x|^2, 0)
+        return a;
+    }
+    static __device__ __forceinline__ double row_term(double g2, double xx, double a) { return KIND == 1 ? fma(-g2, xx, a) : a; }
+    __device__ __forceinline__ void cols_fixed(double g2)
+    {
+        const double zero[4] = {0.0, 0.0, 0.0, 0.0};
+        if constexpr (KIND == 1) {
+            prepare(-1.0, zero);  // W = |y|^2, y <- -2 y
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                YY[k] = W[k];
+#pragma unroll
+                for (int e = 0; e < D; ++e) y[k][e] *= -g2;  // exactly 2 g2 y: both factors of 2 are exact
+            }
+        }
+    }
+    __device__ __forceinline__ void bind_cols(double g2, const double V[4])
+    {
+        if constexpr (KIND == 1) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) W[k] = fma(-g2, YY[k], V[k]);
         }
     }
     __device__ __forceinline__ RowX lds_row(int r) const
@@ -1197,6 +1233,19 @@ __device__ __forceinline__ Comb combine(const Work& w, int mode, int k, bool val
     return cb;
 }
 
+// The line search and PNCG terms of one entry: gradient entry gnew at the trial, y its change.
+__device__ __forceinline__ void lse_dots(const Entry& e, double gnew, double y, double l, double sum, bool e64,
+                                         double v[kNDot])
+{
+    const double snew = e.logt - l;
+    v[D_PHI] += e.p * gnew;
+    v[D_NUM] += -y * snew;
+    v[D_DEN] += y * e.p;
+    v[D_SG] += snew * gnew;
+    v[D_GN] += fabs(gnew);
+    v[D_BAD] += in_range(sum, e64) ? 0.0 : 1.0;
+}
+
 // Terms of the LSE sweep's dots for entry k with trial log-sum l (row or column): the line
 // search and PNCG dots, the row-only gradient norm (Sinkhorn projector) or, with `pre`, the
 // diagonal-Hessian direction s~ = r~/r(P) - 1 (stored for the accept) and its dots.
@@ -1206,14 +1255,8 @@ __device__ __forceinline__ void lse_terms(const Work& w, const Entry& e, double 
     w.lzt[k] = l;
     const double rp = exp(l);
     const double gnew = rp - e.rt;
-    const double snew = e.logt - l;
     const double y = gnew - g_cur;
-    v[D_PHI] += e.p * gnew;
-    v[D_NUM] += -y * snew;
-    v[D_DEN] += y * e.p;
-    v[D_SG] += snew * gnew;
-    v[D_GN] += fabs(gnew);
-    v[D_BAD] += in_range(sum, e64) ? 0.0 : 1.0;
+    lse_dots(e, gnew, y, l, sum, e64, v);
     if (pre) {  // eq. (s-tilde) and the [0.01, 100] switch (Sec. 4.3)
         const double ratio = e.rt / rp;
         const double st = ratio - 1.0;
@@ -1335,15 +1378,67 @@ __device__ __forceinline__ void finish(State& S, int status)
     S.sweep_mode = SM_NONE;
 }
 
-__device__ __forceinline__ void start_line_search(State& S)
+template <class T>
+__device__ __forceinline__ void start_line_search(T& S)
 {
-    S.ls_phase = LS_TRIAL;
     S.alpha = S.alpha_prev;
     S.alo = 0.0;
     S.dlo = S.dphi0;
     S.ahi = INFINITY;
     S.dhi = 0.0;
     S.ls_trials_cur = 0;
+}
+
+template <class Q>
+__device__ __forceinline__ bool wolfe(const Q& P, double dphi0, double d)  // eq. (approximate-wolfe)
+{
+    return ((2.0 * P.c1 - 1.0) * dphi0 >= d) && (d >= P.c2 * dphi0);
+}
+
+// An accepted step's next direction: beta with the numerator of the direction this iterate takes
+// (s, or s~ under the switch), and the restart. Returns the new slope <p, g>.
+template <class T>
+__device__ __forceinline__ double next_direction(T& S, double num, double den, double sg, double phi, int reset_bits)
+{
+    const double beta = (den != 0.0) ? num / den : 0.0;  // eq. (beta_PPR_OT)
+    double pg = sg + beta * phi;                         // <s + beta p, g_new>
+    const int reset = !(pg < 0.0);
+    if (reset) {  // not a descent direction: restart with s (Alg. 2)
+        pg = sg;
+        S.cg_resets++;
+    }
+    S.alpha_acc = S.alpha;
+    S.alpha_prev = S.alpha;
+    S.beta = beta;
+    S.reset = (reset ? RS_RESET : 0) | reset_bits;
+    S.dphi0 = pg;
+    return pg;
+}
+
+// A trial that was not accepted: shrink the bracket [alpha_lo, alpha_hi] with phi'(lo) < 0 < phi'(hi),
+// then the next trial in it.
+template <class T>
+__device__ __forceinline__ void shrink_bracket(T& S, double d)
+{
+    if (d < 0.0) {
+        S.alo = S.alpha;
+        S.dlo = d;
+    } else {  // NaN (range failure in FP64 too) also lands here: step too long
+        S.ahi = S.alpha;
+        S.dhi = d;
+    }
+}
+template <class T>
+__device__ __forceinline__ void next_trial(T& S)
+{
+    if (isinf(S.ahi)) {
+        S.alpha = 2.0 * S.alpha;
+    } else {  // hybrid step: mean of the secant point and the bisection point
+        double asec = (S.alo * S.dhi - S.ahi * S.dlo) / (S.dhi - S.dlo);
+        const double amid = 0.5 * (S.alo + S.ahi);
+        if (!(asec > S.alo && asec < S.ahi)) asec = amid;
+        S.alpha = 0.5 * asec + 0.5 * amid;
+    }
 }
 
 // Scalar logic after a sweep: line search (App. B), PNCG bookkeeping (Alg. 2), stage
@@ -1463,6 +1558,7 @@ __device__ __forceinline__ void decide(State& S, const DevParams& P, const doubl
             else if (!(sg < 0.0) || S.budget_stop) end_stage(S, P, false);
             else {
                 S.tilde_iters += tilde;
+                S.ls_phase = LS_TRIAL;
                 start_line_search(S);
             }
             return;
@@ -1473,56 +1569,32 @@ __device__ __forceinline__ void decide(State& S, const DevParams& P, const doubl
         } else {
             S.ls_trials++;
             S.ls_trials_cur++;
-            accept = ((2.0 * P.c1 - 1.0) * S.dphi0 >= d) && (d >= P.c2 * S.dphi0);  // eq. (approximate-wolfe)
+            accept = wolfe(P, S.dphi0, d);
         }
         if (accept) {
             // numerator of beta with the direction this iterate takes (s, or s~ under the switch)
             const double num = tilde ? sum[D_NUMT] : sum[D_NUM], den = sum[D_DEN];
-            const double beta = (den != 0.0) ? num / den : 0.0;  // eq. (beta_PPR_OT)
-            double pg = sg + beta * sum[D_PHI];                  // <s + beta p, g_new>
-            const int reset = !(pg < 0.0);
-            if (reset) {  // not a descent direction: restart with s (Alg. 2)
-                pg = sg;
-                S.cg_resets++;
-            }
-            S.alpha_acc = S.alpha;
-            S.alpha_prev = S.alpha;
-            S.beta = beta;
-            S.reset = (reset ? RS_RESET : 0) | (tilde ? RS_TILDE : 0);
+            const double pg = next_direction(S, num, den, sg, sum[D_PHI], tilde ? RS_TILDE : 0);
             S.vec_action = VA_ACCEPT;
             S.pncg_iters++;
             S.k++;
             S.gnorm = gn;
-            S.dphi0 = pg;
             const bool stalled = stall_guard(S, gn);
             if (gn <= S.tol) end_stage(S, P, true);
             else if (S.k > P.max_pncg_iters || S.budget_stop || !(pg < 0.0) || stalled) end_stage(S, P, false);
             else {
                 S.tilde_iters += tilde;
+                S.ls_phase = LS_TRIAL;
                 start_line_search(S);
             }
             return;
         }
-        // not accepted: shrink the bracket [alpha_lo, alpha_hi] with phi'(lo) < 0 < phi'(hi)
-        if (d < 0.0) {
-            S.alo = S.alpha;
-            S.dlo = d;
-        } else {  // NaN (range failure in FP64 too) also lands here: step too long
-            S.ahi = S.alpha;
-            S.dhi = d;
-        }
+        shrink_bracket(S, d);
         if (S.budget_stop) {  // stop at the last accepted iterate
             end_stage(S, P, false);
             return;
         }
-        if (isinf(S.ahi)) {
-            S.alpha = 2.0 * S.alpha;
-        } else {  // hybrid step: mean of the secant point and the bisection point
-            double asec = (S.alo * S.dhi - S.ahi * S.dlo) / (S.dhi - S.dlo);
-            const double amid = 0.5 * (S.alo + S.ahi);
-            if (!(asec > S.alo && asec < S.ahi)) asec = amid;
-            S.alpha = 0.5 * asec + 0.5 * amid;
-        }
+        next_trial(S);
         if (S.ls_trials_cur >= P.max_ls_trials) {
             S.ls_failures++;
             if (S.alo > 0.0) {
@@ -1885,7 +1957,7 @@ __global__ void __launch_bounds__(kVecWG, V == kFinMid ? 2 : 1) k_fin(const Work
 // its vector update cleared).
 constexpr int kDecideWG = 64;
 
-__device__ __forceinline__ void decide_body(const Work& w, int parity)
+__device__ __forceinline__ void decide_body(const Work& w, int parity, int to)
 {
     const int lane = threadIdx.x;
     // Every read of this kernel is issued together: the state, the parameters, the finalize
@@ -1934,12 +2006,891 @@ __device__ __forceinline__ void decide_body(const Work& w, int parity)
     } else {
         S.vec_action = 0;
     }
-    if (lane == 0) *state_slot(w, parity ^ 1) = S;
+    S.undecided = 0;
+    if (lane == 0) *state_slot(w, to) = S;
 }
 
 __global__ void __launch_bounds__(kDecideWG) k_decide(const Work* __restrict__ wp, int parity)
 {
-    decide_body(*wp, parity);
+    decide_body(*wp, parity, parity ^ 1);
+}
+
+// The decision a resident-steps kernel left to this one, in state slot 0.
+__global__ void __launch_bounds__(kDecideWG) k_settle(const Work* __restrict__ wp)
+{
+    if (state_slot(*wp, 0)->undecided) decide_body(*wp, 0, 0);
+}
+
+// ------------------------------------------------------------------ resident steps
+// k_steps runs the LSE steps of a problem of at most 1024 tiles (n = 4096 square) inside one
+// kernel: sweep, finalize and decision of a trial, then the next trial, until the state machine
+// asks for something else (Round, the stage's end, a cap), which k_settle and the one-step kernels
+// do. What bounds a step of three kernels at these sizes is not its work but the three boundaries;
+// inside one kernel a step has two exchanges between workgroups instead, of 1 to 1.5 us each, and
+// the cost stays in registers. Per step, in solves with FP32 cost and exponentials: n = 256 14.5 ->
+// 8.2 us, n = 1024 14.8 -> 8.7, n = 4096 24.7 -> 15.5. Of the 8.2 us the sweep takes 1.5 (one wave
+// per SIMD), its set-up and partials 1.2, the first exchange 1.3, folding, log and exp of the
+// finalize block and its dots 1.7, the second exchange 1.4, the decision 1.0.
+//
+// Every workgroup holds up to four tiles (a quad of four waves takes one or two: n = 4096 is 256
+// workgroups of two quads, one per compute unit) with their rows' and columns' vector entries in
+// LDS, and does the work of finalize block blockIdx.x if there is one. Arithmetic and orders are those of
+// k_sweep, k_fin and k_decide, so the results are the same bits. Per step:
+//   1. sweep: tile partials and row-tile shifts are stored for the finalize blocks;
+//   2. the finalize blocks fold them and store log-sums and dots;
+//   3. every workgroup reads all dots, takes the decision (the same in each; anything but the
+//      next trial is left to k_settle) and reads the log-sums of its own rows and columns.
+// Values travel through memory with agent-scope loads and stores, which meet where every XCD
+// sees them. An empty slot holds kEmpty, a NaN no arithmetic produces, and a reader waits until
+// its value is there: data and flag arrive in one trip. Slots are used in turns of three. A writer
+// empties a slot, waits for that store, and then fills a slot of an earlier turn, so whoever has
+// seen that one filled finds the emptied slot empty or filled again:
+//   - a tile's partials of step s + 1 are emptied in step s - 1, after its partials of s - 1 are
+//     stored and its dots read (so the slot's last readers, in step s - 2, are through);
+//   - log-sums and dots of step s + 1 are emptied at the start of step s. Their last readers are
+//     those of step s - 2, and all dots of step s - 1 having been read, everybody is past it.
+//
+// All workgroups have to run at the same time. They meet once at the start, with a limit of
+// kStartTicks: if the GPU is shared and some cannot start, all of them leave with nothing
+// changed and the one-step kernels that follow carry on. Later waits cannot starve; they have a
+// limit all the same, after which the solve ends with an error.
+constexpr uint64_t kEmpty = 0x7ff8dead0000beefull;
+constexpr uint32_t kStepsAbort = 0x80000000u;
+constexpr uint64_t kStartTicks = 20000;      // 200 us of the 100 MHz wall clock
+constexpr uint64_t kWaitTicks = 400000000;   // 4 s
+
+template <class T>
+__device__ __forceinline__ T xload(const T* p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class T>
+__device__ __forceinline__ void xstore(T* p, T v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double empty_slot() { return __builtin_bit_cast(double, kEmpty); }
+__device__ __forceinline__ bool is_empty(double v) { return __builtin_bit_cast(uint64_t, v) == kEmpty; }
+// every memory operation of this wave before it has completed
+__device__ __forceinline__ void wave_drain() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// A bounded wait: again() after an unsuccessful look.
+struct Wait {
+    StepsX* x;
+    uint32_t n = 0;
+    uint64_t t0 = 0;
+    bool dead = false;
+    __device__ __forceinline__ explicit Wait(StepsX* x_) : x(x_) {}
+    __device__ __forceinline__ bool again()
+    {
+        if ((++n & 1023) == 0) {
+            const uint64_t t = wall_clock64();
+            if (t0 == 0) t0 = t;
+            if (t - t0 > kWaitTicks) xstore(&x->abort, 1u);
+            dead = xload(&x->abort) != 0;
+        }
+        return !dead;
+    }
+};
+
+// The steps this kernel takes: a stage's first sweep and its line-search trials.
+__device__ __forceinline__ bool steps_go(const State& S)
+{
+    return S.done == 0 && S.sweep_mode == SM_LSE && (S.ls_phase == LS_INIT || S.ls_phase == LS_TRIAL) && !S.standalone &&
+           !S.undecided && !S.budget_stop && !(S.reset & RS_TILDE);
+}
+
+// The part of State that these steps change (beside it, vec_action: the pending update is taken
+// when the kernel starts).
+struct Trial {
+    double alpha, alpha_acc, alpha_prev, beta, dphi0, alo, dlo, ahi, dhi, gnorm, stall_best;
+    int64_t k, sweeps, pncg_iters, ls_trials, cg_resets, stall_k;
+    int32_t vec_action, reset, ls_trials_cur, ls_phase, exp64;
+    template <class A, class B>
+    static __device__ __forceinline__ void copy(A& a, const B& b)
+    {
+        a.alpha = b.alpha; a.alpha_acc = b.alpha_acc; a.alpha_prev = b.alpha_prev; a.beta = b.beta;
+        a.dphi0 = b.dphi0; a.alo = b.alo; a.dlo = b.dlo; a.ahi = b.ahi; a.dhi = b.dhi;
+        a.gnorm = b.gnorm; a.stall_best = b.stall_best;
+        a.k = b.k; a.sweeps = b.sweeps; a.pncg_iters = b.pncg_iters; a.ls_trials = b.ls_trials;
+        a.cg_resets = b.cg_resets; a.stall_k = b.stall_k;
+        a.vec_action = b.vec_action; a.reset = b.reset; a.ls_trials_cur = b.ls_trials_cur;
+        a.ls_phase = b.ls_phase; a.exp64 = b.exp64;
+    }
+};
+
+// What a decision inside a stage needs besides.
+struct TrialParams {
+    double c1, c2, tol;
+    int64_t max_sweeps, max_pncg_iters, stall;
+    int32_t max_ls_trials, exp64_stage;
+    __device__ __forceinline__ void set(const DevParams& P, const State& S)
+    {
+        c1 = P.c1;
+        c2 = P.c2;
+        tol = S.tol;
+        max_sweeps = P.max_sweeps;
+        max_pncg_iters = P.max_pncg_iters;
+        max_ls_trials = P.max_ls_trials;
+        exp64_stage = S.exp64_stage;
+        stall = S.exp64_stage ? kStallF64 : kStallF32;
+    }
+};
+
+constexpr int kStepDots = D_GN + 1;  // the dots these steps need: D_PHI .. D_GN, and whether any D_BAD
+
+// decide() for a step that stays inside its stage: false, with T unchanged, where anything else
+// follows (range, budget, caps, the stage's end, a stall), which is left to it.
+__device__ __forceinline__ bool decide_trial(Trial& T, const TrialParams& P, const double* sum, bool bad)
+{
+    if (bad || (P.max_sweeps > 0 && T.sweeps + 1 >= P.max_sweeps)) return false;
+    const double gn = sum[D_GN], d = sum[D_PHI], sg = sum[D_SG];
+    if (T.ls_phase == LS_INIT) {
+        if (gn <= P.tol || !(sg < 0.0)) return false;
+        T.alpha_acc = 0.0;
+        T.beta = 0.0;
+        T.reset = RS_RESET;
+        T.vec_action = VA_ACCEPT;
+        T.k = 1;
+        T.stall_best = gn;
+        T.stall_k = 1;
+        T.dphi0 = sg;
+        T.gnorm = gn;
+        T.ls_phase = LS_TRIAL;
+        start_line_search(T);
+    } else if (wolfe(P, T.dphi0, d)) {
+        Trial t = T;
+        const double pg = next_direction(t, sum[D_NUM], sum[D_DEN], sg, d, 0);
+        t.k++;
+        if (gn <= 0.5 * t.stall_best) {
+            t.stall_best = gn;
+            t.stall_k = t.k;
+        } else if (t.k - t.stall_k >= P.stall) {
+            return false;
+        }
+        if (gn <= P.tol || t.k > P.max_pncg_iters || !(pg < 0.0)) return false;
+        t.vec_action = VA_ACCEPT;
+        t.pncg_iters++;
+        t.ls_trials++;
+        t.gnorm = gn;
+        start_line_search(t);
+        T = t;
+    } else {
+        if (T.ls_trials_cur + 1 >= P.max_ls_trials) return false;
+        shrink_bracket(T, d);
+        next_trial(T);
+        T.vec_action = 0;
+        T.ls_trials++;
+        T.ls_trials_cur++;
+    }
+    T.sweeps++;
+    T.exp64 = P.exp64_stage;
+    return true;
+}
+
+template <int NT>
+struct StepsShared {  // NT: tiles of the workgroup
+    double region[NT][4][kRowBufD];  // per tile and wave: row transpose, then its columns' values
+    double A[NT][kBR], wt[NT][kBR], s[NT][kBR], x[NT][3 * kBR], colv[NT][kBC];
+    double cz[NT][kBC], cp[NT][kBC], clt[NT][kBC];                                   // column entries
+    double rz[NT][kBR], rp[NT][kBR], rlz[NT][kBR], rlt[NT][kBR], rxx[NT][kBR];       // row entries
+    double fz[kVecWG], fp[kVecWG], flz[kVecWG], flt[kVecWG], frt[kVecWG], fg[kVecWG], fl[kVecWG];  // finalize entries
+    double fac[kStepsMaxRowTiles];
+    double red[(kStepDots + 1) * 4];
+    double y[kStepDots + 1][kStepsMaxGrid];  // the dots of all finalize blocks, and D_BAD
+    double *rowp[3], *colp[3], *logr[3], *logc[3];  // the three turns of the slots
+    Trial T;
+    TrialParams P;
+    int go, dead;
+};
+static_assert(8 * 64 <= kRowBufD, "eight rows of FP64 partials fit a wave region");
+static_assert(sizeof(StepsShared<4>) <= 160 * 1024, "LDS of one compute unit");
+
+// Where a thread stands. Its index is made opaque to the compiler wherever it is read, so that
+// nothing derived from it stays in registers from one part of a step to the next: hoisted out of
+// the step loop, addresses and masks take more registers than a tile's cost. What is the same in a wave is kept in scalar registers.
+struct Lane {
+    int t, lane, wave, q;  // thread of the quad, lane and wave of it, quad
+    __device__ __forceinline__ Lane()
+    {
+        int i = threadIdx.x;
+        asm volatile("" : "+v"(i));
+        const int wv = __builtin_amdgcn_readfirstlane(i >> 6);
+        t = i & 255;
+        lane = i & 63;
+        wave = wv & 3;
+        q = wv >> 2;
+    }
+};
+
+// One tile of a quad (all scalar): the workgroup's tile `at`.
+struct StepTile {
+    int m, n, at, I, J, i0, rbase, nrows;
+    bool has;
+    __device__ __forceinline__ void set(const Work& w, int nt, int at_)
+    {
+        const Lane me;
+        m = w.m;
+        n = w.n;
+        at = at_;
+        const int tile = blockIdx.x * nt + at;
+        has = tile < w.nrt * w.nct;
+        I = has ? tile / w.nct : 0;
+        J = has ? tile % w.nct : 0;
+        i0 = I * kBR;
+        rbase = me.wave * kRPW;
+        nrows = has ? min(kRPW, m - (i0 + rbase)) : 0;
+    }
+    __device__ __forceinline__ bool has_col(const Lane& me) const { return has && J * kBC + me.t < n; }
+    __device__ __forceinline__ bool has_row(const Lane& me) const { return has && me.t < kBR && i0 + me.t < m; }
+    // the row whose partial a lane stores (as rows_reduce_* leave them), and whether there is one
+    __device__ __forceinline__ bool has_prow(const Lane& me) const { return (me.lane & 3) == 0 && (me.lane >> 2) < nrows; }
+    __device__ __forceinline__ bool has_shift(const Lane& me) const { return has && J == 0 && me.t == 0; }
+};
+
+// The sizes the steps need, in scalar registers throughout.
+struct StepSize {
+    int m, n, nrt, nct, nvb, nvbr, Lr, L, lgLr, lgL;
+    __device__ __forceinline__ explicit StepSize(const Work& w)
+        : m(w.m), n(w.n), nrt(w.nrt), nct(w.nct), nvb(w.fin_nvb), nvbr(w.fin_nvbr), Lr(w.fin_Lr), L(w.fin_L), lgLr(w.fin_lgLr),
+          lgL(w.fin_lgL) {}
+};
+
+// The three slots of every exchanged value, in buffers that LSE steps leave unused. The log-sums'
+// third is the trial vector itself, which holds the pending step's log-sums at the start. Their
+// addresses are kept in LDS: read from the Work struct in every part of a step they cost 2 us.
+template <int NT>
+__device__ __forceinline__ void steps_slots(const Work& w, StepsShared<NT>& sh)
+{
+    sh.rowp[0] = w.rowpart; sh.rowp[1] = w.rowpart2; sh.rowp[2] = w.rowpart3;
+    sh.colp[0] = w.colpart; sh.colp[1] = w.colmin;   sh.colp[2] = w.colmin + (size_t)w.nrt * w.n;
+    sh.logr[0] = w.sdt;     sh.logr[1] = w.fpp;      sh.logr[2] = w.lzt;
+    sh.logc[0] = w.sdt + w.m; sh.logc[1] = w.gp;     sh.logc[2] = w.lzt + w.m;
+}
+template <int NT>
+__device__ __forceinline__ double* row_slot(const StepsShared<NT>& sh, const StepTile& t, const Lane& me, int b)
+{
+    return sh.rowp[b] + (size_t)t.J * t.m + (t.i0 + t.rbase) + (me.lane >> 2);
+}
+template <int NT>
+__device__ __forceinline__ double* col_slot(const StepsShared<NT>& sh, const StepTile& t, const Lane& me, int b)
+{
+    return sh.colp[b] + (size_t)t.I * t.n + t.J * kBC + me.t;
+}
+
+// A thread's entry of finalize block blockIdx.x (the first quad of the first fin_nvb workgroups),
+// as in fin_body.
+struct FinEntry {
+    bool row, valid, own;
+    int L, l, k, np;       // lanes and lane of the group, row or column, its partials
+    __device__ __forceinline__ FinEntry(const StepSize& z, const Lane& me)
+    {
+        const int vb = blockIdx.x;
+        row = vb < z.nvbr;
+        L = row ? z.Lr : z.L;
+        l = me.t & (L - 1);
+        k = row ? (vb * kVecWG + me.t) >> z.lgLr : ((vb - z.nvbr) * kVecWG + me.t) >> z.lgL;
+        np = row ? z.nct : z.nrt;
+        valid = vb < z.nvb && me.q == 0 && k < (row ? z.m : z.n);
+        own = valid && l == 0;
+    }
+    __device__ __forceinline__ int entry(const StepSize& z) const { return row ? k : z.m + k; }
+};
+
+// Empty the slots of turn b: a tile's partials, and a finalize block's results.
+template <int NT>
+__device__ __forceinline__ void clear_tile(const StepsShared<NT>& sh, StepsX* x, const StepTile& t, int b)
+{
+    const Lane me;
+    if (t.has_prow(me)) xstore(row_slot(sh, t, me, b), empty_slot());
+    if (t.has_col(me)) xstore(col_slot(sh, t, me, b), empty_slot());
+    if (t.has_shift(me)) xstore(&x->shift[b][t.I], empty_slot());
+}
+template <int NT>
+__device__ __forceinline__ void clear_fin(const StepsShared<NT>& sh, const StepSize& z, StepsX* x, int b)
+{
+    const Lane me;
+    const FinEntry f(z, me);
+    if (f.own) xstore((f.row ? sh.logr[b] : sh.logc[b]) + f.k, empty_slot());
+    if (me.q == 0 && me.t <= kStepDots) xstore(&x->dots[b][blockIdx.x][me.t], empty_slot());
+}
+
+// Entry k with the pending update of the last step (or stage) taken. The trial log-sums are read as
+// the steps will read them, since their buffer is one of the slots.
+__device__ __forceinline__ EntryIn steps_entry_in(const Work& w, const SweepArgs& a, int k)
+{
+    EntryIn in;
+    in.z = w.z[k];
+    in.p = w.p[k];
+    in.lz = w.lz[k];
+    in.logt = w.logt[k];
+    in.rt = w.rt[k];
+    in.zprev = w.zprev[k];
+    in.lzt = xload(w.lzt + k);
+    in.m = (a.va & VA_STAGE_INIT) ? *((k < w.m) ? w.r + k : w.c + (k - w.m)) : 0.0;
+    in.g = w.g[k];
+    in.sdt = 0.0;
+    return in;
+}
+
+// The vector entries of a tile.
+template <int NT>
+__device__ __forceinline__ void steps_load(const Work& w, const SweepArgs& a, StepsShared<NT>& sh, const StepTile& t)
+{
+    const Lane me;
+    if (t.has_col(me)) {
+        const int k = t.m + t.J * kBC + me.t;
+        const Entry e = entry_from(steps_entry_in(w, a, k), a, t.m, t.n, k);
+        sh.cz[t.at][me.t] = e.z;
+        sh.cp[t.at][me.t] = e.p;
+        sh.clt[t.at][me.t] = e.logt;
+    }
+    if (t.has_row(me)) {
+        const int k = t.i0 + me.t;
+        const Entry e = entry_from(steps_entry_in(w, a, k), a, t.m, t.n, k);
+        sh.rz[t.at][me.t] = e.z;
+        sh.rp[t.at][me.t] = e.p;
+        sh.rlz[t.at][me.t] = e.lz;
+        sh.rlt[t.at][me.t] = e.logt;
+    }
+}
+
+// The finalize block's entries, with the update stored as the finalize kernel does. Only when every
+// workgroup has loaded its own: they read the same vectors.
+template <int NT>
+__device__ __forceinline__ void steps_load_fin(const Work& w, const StepSize& z, const SweepArgs& a, StepsShared<NT>& sh)
+{
+    const Lane me;
+    const FinEntry f(z, me);
+    if (!f.own) return;
+    const int k = f.entry(z);
+    const EntryIn in = steps_entry_in(w, a, k);
+    const Entry e = entry_from(in, a, w.m, w.n, k);
+    sh.fg[me.t] = store_update(w, a, e, in.g, k);
+    sh.fz[me.t] = e.z;
+    sh.fp[me.t] = e.p;
+    sh.flz[me.t] = e.lz;
+    sh.flt[me.t] = e.logt;
+    sh.frt[me.t] = e.rt;
+    sh.fl[me.t] = in.lzt;
+}
+
+// Wait until every workgroup runs; false if one of them does not get to.
+__device__ __forceinline__ bool steps_meet(StepsX* x)
+{
+    uint32_t seen = __hip_atomic_fetch_add(&x->arrive, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
+    const uint64_t t0 = wall_clock64();
+    while (!(seen & kStepsAbort) && seen != gridDim.x) {
+        if (wall_clock64() - t0 > kStartTicks)  // give up, unless the last one has just come
+            __hip_atomic_compare_exchange_strong(&x->arrive, &seen, seen | kStepsAbort, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT);
+        seen = xload(&x->arrive);
+    }
+    return !(seen & kStepsAbort);
+}
+
+// What the next step does with the vectors.
+template <int NT>
+__device__ __forceinline__ SweepArgs steps_args(const StepsShared<NT>& sh)
+{
+    SweepArgs a{};
+    a.alpha = sh.T.ls_phase == LS_TRIAL ? sh.T.alpha : 0.0;
+    a.alpha_acc = sh.T.alpha_acc;
+    a.beta = sh.T.beta;
+    a.reset = sh.T.reset;
+    a.va = sh.T.vec_action;
+    return a;
+}
+
+// The pending update of a tile's entries, and its set-up: row shifts and terms, column terms (see
+// tile_lse).
+template <class Cost, int NT>
+__device__ __forceinline__ void steps_update(StepsShared<NT>& sh, const StepTile& t, double g2, double lzt_r, double lzt_c)
+{
+    const Lane me;
+    const SweepArgs a = steps_args(sh);
+    const bool acc = (a.va & VA_ACCEPT) != 0;
+    if (me.t < kBR) {
+        double s = -INFINITY, aa = -INFINITY;
+        if (t.has_row(me)) {
+            double z = sh.rz[t.at][me.t], p = sh.rp[t.at][me.t], lz = sh.rlz[t.at][me.t];
+            if (acc) {
+                z = fma(a.alpha_acc, p, z);
+                lz = lzt_r;
+                p = next_dir(a, p, sh.rlt[t.at][me.t], lz, 0.0, true);
+                sh.rz[t.at][me.t] = z;
+                sh.rp[t.at][me.t] = p;
+                sh.rlz[t.at][me.t] = lz;
+            }
+            s = fma(a.alpha, p, lz);
+            aa = Cost::row_term(g2, sh.rxx[t.at][me.t], (z - lz) * LOG2E_D);
+        }
+        sh.s[t.at][me.t] = s;
+        sh.A[t.at][me.t] = aa;
+    }
+    double vv = -INFINITY;
+    if (t.has_col(me)) {
+        double z = sh.cz[t.at][me.t], p = sh.cp[t.at][me.t];
+        if (acc) {
+            z = fma(a.alpha_acc, p, z);
+            p = next_dir(a, p, sh.clt[t.at][me.t], lzt_c, 0.0, false);
+            sh.cz[t.at][me.t] = z;
+            sh.cp[t.at][me.t] = p;
+        }
+        vv = fma(a.alpha, p, z) * LOG2E_D;
+    }
+    sh.colv[t.at][me.t] = vv;
+}
+
+// One finalize block (fin_lse_entry<8>): the pending update of its entries while the partials are
+// on their way, then fold them and store log-sums and dots.
+template <int NT>
+__device__ __forceinline__ void steps_finalize(const StepSize& z, StepsX* x, StepsShared<NT>& sh, int b, bool e64, Wait& wait)
+{
+    double M = 0.0, xs[8];
+    {
+        const Lane me;
+        if (me.q == 0) {
+            const FinEntry f(z, me);
+            const int nrt = z.nrt;
+            const size_t st = f.row ? (size_t)z.m : (size_t)z.n;
+            const double* base = (f.row ? sh.rowp[b] : sh.colp[b]) + f.k;
+            double ts[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) ts[u] = (!f.row && me.lane + 64 * u < nrt) ? xload(&x->shift[b][me.lane + 64 * u]) : -INFINITY;
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                xs[u] = (f.valid && f.l + u * f.L < f.np) ? xload(base + (size_t)(f.l + u * f.L) * st) : 0.0;
+            clear_fin(sh, z, x, b == 2 ? 0 : b + 1);
+            const SweepArgs a = steps_args(sh);
+            if (f.own && (a.va & VA_ACCEPT)) {
+                const double p = sh.fp[me.t], lz = sh.fl[me.t];
+                sh.fz[me.t] = fma(a.alpha_acc, p, sh.fz[me.t]);
+                sh.flz[me.t] = lz;
+                sh.fp[me.t] = next_dir(a, p, sh.flt[me.t], lz, 0.0, f.row);
+                sh.fg[me.t] = exp(lz) - sh.frt[me.t];
+            }
+            for (;;) {
+                bool miss = false;
+#pragma unroll
+                for (int u = 0; u < 2; ++u) miss |= is_empty(ts[u]);
+#pragma unroll
+                for (int u = 0; u < 8; ++u) miss |= is_empty(xs[u]);
+                if (!miss || !wait.again()) break;
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+                    if (is_empty(ts[u])) ts[u] = xload(&x->shift[b][me.lane + 64 * u]);
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    if (is_empty(xs[u])) xs[u] = xload(base + (size_t)(f.l + u * f.L) * st);
+            }
+            wave_drain();  // the emptied slots of the next turn
+            if (!f.row) {
+                M = wave_max(fmax(ts[0], ts[1]));
+                if (me.t < nrt) sh.fac[me.t] = exp((me.t < 64 ? ts[0] : ts[1]) - M);
+            }
+        }
+    }
+    __syncthreads();
+    {
+        const Lane me;
+        if (me.q == 0) {
+            const FinEntry f(z, me);
+            double v[kNDot];
+#pragma unroll
+            for (int d = 0; d < kNDot; ++d) v[d] = 0.0;
+            double acc = 0.0;
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (f.l + u * f.L < f.np)
+                    acc = fma(xs[u], f.row ? 1.0 : sh.fac[min(f.l + u * f.L, kStepsMaxRowTiles - 1)], acc);
+            const double sum = group_fold<0>(acc, f.L);
+            if (f.own) {
+                Entry e;
+                e.p = sh.fp[me.t];
+                e.lz = sh.flz[me.t];
+                e.logt = sh.flt[me.t];
+                e.rt = sh.frt[me.t];
+                const double lg = f.row ? fma(steps_args(sh).alpha, e.p, e.lz) + log(sum) : M + log(sum);
+                sh.fl[me.t] = lg;
+                xstore((f.row ? sh.logr[b] : sh.logc[b]) + f.k, lg);
+                const double gnew = exp(lg) - e.rt;
+                lse_dots(e, gnew, gnew - sh.fg[me.t], lg, sum, e64, v);
+            }
+            // D_BAD counts, exactly: the number of lanes with a 1
+            const double bad = (double)__popcll(__ballot(v[D_BAD] != 0.0));
+            wave_sums<kStepDots>(v);
+            if (me.lane == 0) {
+#pragma unroll
+                for (int d = 0; d < kStepDots; ++d) sh.red[d * 4 + me.wave] = v[d];
+                sh.red[kStepDots * 4 + me.wave] = bad;
+            }
+        }
+    }
+    static_assert(D_BAD == kStepDots, "the dots of a step are the first ones");
+    __syncthreads();
+    const Lane me;
+    if (me.q == 0 && me.t <= kStepDots)
+        xstore(&x->dots[b][blockIdx.x][me.t], (sh.red[me.t * 4 + 0] + sh.red[me.t * 4 + 1]) + (sh.red[me.t * 4 + 2] + sh.red[me.t * 4 + 3]));
+}
+
+// All dots, 64 blocks per wave of the first quad: ask() starts the loads, take() waits and leaves
+// them in LDS. One 128-byte line per block, read 16 bytes at a time with the agent-scope cache
+// policy (each 8-byte half is one value, looked at by itself).
+constexpr int kAgentScope = 16 | (int)0x80000000u;  // sc1 of a buffer load, and volatile
+struct StepDots {
+    static_assert((kStepDots + 1) % 2 == 0, "whole 16-byte loads");
+    static constexpr int N = (kStepDots + 1) / 2;
+    double2 y[N];
+    bool mine;
+    __device__ __forceinline__ void load(StepsX* x, int b, int vb)
+    {
+        const auto rs = __builtin_amdgcn_make_buffer_rsrc(x->dots[b], (short)0, (int)sizeof x->dots[b], kBufDword3);
+#pragma unroll
+        for (int d = 0; d < N; ++d) {
+            auto v = __builtin_amdgcn_raw_buffer_load_b128(rs, vb * (int)sizeof x->dots[b][0] + d * 16, 0, kAgentScope);
+            y[d] = *(double2*)&v;
+        }
+    }
+    __device__ __forceinline__ bool missing() const
+    {
+        bool miss = false;
+#pragma unroll
+        for (int d = 0; d < N; ++d) miss |= is_empty(y[d].x) || is_empty(y[d].y);
+        return miss;
+    }
+    __device__ __forceinline__ void ask(const StepSize& z, StepsX* x, int b)
+    {
+        const Lane me;
+#pragma unroll
+        for (int d = 0; d < N; ++d) y[d] = make_double2(0.0, 0.0);
+        mine = me.q == 0 && me.wave * 64 < z.nvb;
+        if (mine && me.t < z.nvb) load(x, b, me.t);
+    }
+    template <int NT>
+    __device__ __forceinline__ void take(const StepSize& z, StepsX* x, StepsShared<NT>& sh, int b, Wait& wait)
+    {
+        if (!mine) return;
+        const Lane me;
+        while (missing() && wait.again()) load(x, b, me.t);
+#pragma unroll
+        for (int d = 0; d < N; ++d) {
+            sh.y[2 * d][me.t] = y[d].x;
+            sh.y[2 * d + 1][me.t] = y[d].y;
+        }
+    }
+};
+
+// The decision, in the first wave.
+template <int NT>
+__device__ __forceinline__ void steps_decide(const StepSize& z, StepsShared<NT>& sh, bool more)
+{
+    const int nvb = z.nvb;
+    const Lane me;
+    if ((me.q | me.wave) != 0) return;
+    double v[kStepDots];
+    bool bad = false;
+#pragma unroll
+    for (int d = 0; d < kStepDots; ++d) v[d] = 0.0;
+    for (int u = 0; u * 64 < nvb; ++u) {
+#pragma unroll
+        for (int d = 0; d < kStepDots; ++d) v[d] += sh.y[d][u * 64 + me.lane];
+        bad |= sh.y[kStepDots][u * 64 + me.lane] != 0.0;
+    }
+    wave_sums<kStepDots>(v);
+    Trial t = sh.T;
+    const bool decided = decide_trial(t, sh.P, v, __any(bad));
+    if (me.lane == 0) {
+        sh.T = t;
+        sh.go = decided ? more : -1;
+    }
+}
+
+// Make a register value opaque to the compiler, word by word.
+template <class T>
+__device__ __forceinline__ void opaque(T& v)
+{
+    uint32_t d[sizeof(T) / 4];
+    __builtin_memcpy(d, &v, sizeof(T));
+#pragma unroll
+    for (unsigned i = 0; i < sizeof(T) / 4; ++i) asm volatile("" : "+v"(d[i]));
+    __builtin_memcpy(&v, d, sizeof(T));
+}
+
+template <class Cost, int TP>
+struct TileCosts {
+    Cost c[TP];
+};
+template <class Cost, int TP>
+__device__ __forceinline__ TileCosts<Cost, TP> tile_costs(const Work& w, const StepTile* t)
+{
+    if constexpr (TP == 1) return {{Cost(w, t[0].i0)}};
+    else return {{Cost(w, t[0].i0), Cost(w, t[1].i0)}};
+}
+
+// NQ quads of TP tiles each.
+template <int CC, int NQ, int TP>
+__global__ void __launch_bounds__(256 * NQ) k_steps(const Work* __restrict__ wp, StepsX* __restrict__ x, int max_steps)
+{
+    using Cost = typename CostOf<CC>::T;
+    using Raw = typename Cost::Raw;
+    constexpr bool kPoints = std::is_same<Raw, int>::value;
+    // the tiles' cost entries stay in registers, at most 128 of the 256 a thread has; else the rows
+    // are read again in every step, RB at a time
+    constexpr bool kHold = !kPoints && sizeof(Raw) * TP <= 32;
+    constexpr int RB = kHold ? kRPW : (sizeof(Raw) <= 16 ? kRPW / 2 : kRPW / 4);
+    __shared__ StepsShared<NQ * TP> sh;
+
+    if (!steps_go(*state_slot(*wp, 0))) return;  // the same in every workgroup
+
+    const Work& w = *wp;
+    const StepSize z(w);
+    State* const S0 = state_slot(w, 0);
+    const SweepArgs a0 = args_of(S0);  // the pending update
+    const bool fin_wg = (int)blockIdx.x < z.nvb;
+    const double g2 = S0->gamma * w.scale * LOG2E_D;
+    if (threadIdx.x == 0) {
+        Trial::copy(sh.T, *S0);
+        sh.T.vec_action = 0;
+        sh.P.set(params_of(*wp), *S0);
+        sh.dead = 0;
+        steps_slots(w, sh);
+    }
+    __syncthreads();
+    StepTile t[TP];
+    {
+        const Lane me;
+#pragma unroll
+        for (int u = 0; u < TP; ++u) t[u].set(w, NQ * TP, me.q * TP + u);
+    }
+    TileCosts<Cost, TP> cost = tile_costs<Cost, TP>(w, t);
+    Raw raw[kHold ? TP : 1][RB];
+    double lzt_r[TP], lzt_c[TP];  // trial log-sums of this thread's rows and columns
+#pragma unroll
+    for (int u = 0; u < TP; ++u) {
+        const Lane me;
+        Cost& c = cost.c[u];
+        const int j0 = t[u].J * kBC + me.lane * 4;
+        c.cols(j0);
+        c.bind_rows(sh.x[t[u].at], sh.x[t[u].at] + 2 * kBR);
+        if (me.t < kBR) sh.rxx[t[u].at][me.t] = c.row_fixed(me.t, t[u].i0 + me.t);
+        c.cols_fixed(g2);
+        if constexpr (kHold) {
+#pragma unroll
+            for (int r = 0; r < RB; ++r) raw[u][r] = c.load(t[u].rbase + r, j0);
+        }
+        lzt_r[u] = lzt_c[u] = 0.0;
+        steps_load(w, a0, sh, t[u]);
+        clear_tile(sh, x, t[u], 0);
+        clear_tile(sh, x, t[u], 1);
+    }
+    if (fin_wg) clear_fin(sh, z, x, 0);
+
+    wave_drain();
+    __syncthreads();
+    if (threadIdx.x == 0) sh.go = steps_meet(x);
+    __syncthreads();
+    const bool started = sh.go != 0;
+    if (started && fin_wg) steps_load_fin(w, z, a0, sh);
+
+    int last = 0;  // turn of the step that ended last
+    for (int step = 0, b = 0; started; ++step, b = b == 2 ? 0 : b + 1) {
+        // ---- pending update and tile set-up
+#pragma unroll
+        for (int u = 0; u < TP; ++u) steps_update<Cost>(sh, t[u], g2, lzt_r[u], lzt_c[u]);
+        __syncthreads();
+        const bool e64 = __builtin_amdgcn_readfirstlane(sh.T.exp64) != 0;
+        double SI[TP];
+        {
+            const Lane me;
+#pragma unroll
+            for (int u = 0; u < TP; ++u) SI[u] = wave_max(sh.s[t[u].at][me.lane]);
+            // the weights of this wave's rows, kRPW lanes per tile
+            const int u = TP > 1 ? (me.lane / kRPW) % TP : 0, r = me.wave * kRPW + me.lane % kRPW, at = me.q * TP + u;
+            if (me.lane < TP * kRPW) sh.wt[at][r] = exp(sh.s[at][r] - (u == 0 ? SI[0] : SI[TP - 1]));
+        }
+#pragma unroll
+        for (int u = 0; u < TP; ++u) {
+            // ---- sweep (tile_lse, with the tile's own state)
+            double rs = 0.0, col64[4] = {0, 0, 0, 0};
+            const Lane me;
+            Cost& c = cost.c[u];
+            const double* A = sh.A[t[u].at] + t[u].rbase;
+            const double* wts = sh.wt[t[u].at] + t[u].rbase;
+            double* region = sh.region[t[u].at][me.wave];
+            double V[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) V[k] = sh.colv[t[u].at][me.lane * 4 + k];
+            c.bind_cols(g2, V);
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if constexpr (kHold && TP > 1) {
+                // or the entries' conversions to FP64 move out of the step loop, at two registers
+                // each (with one tile that is welcome: there are registers for it)
+#pragma unroll
+                for (int r = 0; r < RB; ++r) opaque(raw[u][r]);
+            }
+            if (t[u].has) {
+                if (!e64) {
+                    float col32[4] = {0, 0, 0, 0};
+                    float rp[kRPW];
+#pragma unroll
+                    for (int b0 = 0; b0 < kRPW; b0 += RB) {
+                        if constexpr (!kHold) {
+#pragma unroll
+                            for (int r = 0; r < RB; ++r) raw[0][r] = c.load(t[u].rbase + b0 + r, t[u].J * kBC + me.lane * 4);
+                        }
+#pragma unroll
+                        for (int r0 = 0; r0 < RB; ++r0) {
+                            const int r = b0 + r0;
+                            double xa[4];
+                            if constexpr (kPoints) c.args(t[u].rbase + r, g2, V, A[r], xa);
+                            else c.args(raw[kHold ? u : 0][r0], g2, V, A[r], xa);
+                            const float wt = (float)wts[r];
+                            float e[4];
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) e[k] = __builtin_amdgcn_exp2f((float)xa[k]);
+                            rp[r] = (e[0] + e[1]) + (e[2] + e[3]);
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) col32[k] = fmaf(wt, e[k], col32[k]);
+                            if ((r & 7) == 7) {
+#pragma unroll
+                                for (int k = 0; k < 4; ++k) {
+                                    col64[k] += (double)col32[k];
+                                    col32[k] = 0.f;
+                                }
+                            }
+                        }
+                    }
+                    rs = rows_reduce_f32(rp, (float*)region, me.lane);
+                } else {
+                    double c9 = kExp2C9;
+                    asm volatile("" : "+v"(c9));
+#pragma unroll
+                    for (int b0 = 0; b0 < kRPW; b0 += RB) {
+                        if constexpr (!kHold) {
+#pragma unroll
+                            for (int r = 0; r < RB; ++r) raw[0][r] = c.load(t[u].rbase + b0 + r, t[u].J * kBC + me.lane * 4);
+                        }
+#pragma unroll
+                        for (int r0 = 0; r0 < RB; ++r0) {
+                            const int r = b0 + r0;
+                            if (r < t[u].nrows) {
+                                double xa[4], e[4];
+                                if constexpr (kPoints) c.args(t[u].rbase + r, g2, V, A[r], xa);
+                                else c.args(raw[kHold ? u : 0][r0], g2, V, A[r], xa);
+                                const double wt = wts[r];
+                                exp2_f64x4(xa, e, c9);
+                                region[(r & 7) * 64 + me.lane] = (e[0] + e[1]) + (e[2] + e[3]);
+#pragma unroll
+                                for (int k = 0; k < 4; ++k) col64[k] = fma(wt, e[k], col64[k]);
+                            }
+                            if ((r & 7) == 7) {  // eight rows' partials are there: lanes of these rows sum them
+                                __builtin_amdgcn_wave_barrier();
+                                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                                const int rr = me.lane >> 2, hq = me.lane & 3;
+                                if ((rr >> 3) == (r >> 3)) {
+                                    const double* src = region + (rr & 7) * 64 + hq * 16;
+#pragma unroll
+                                    for (int k = 0; k < 16; ++k) rs += src[k ^ rr];
+                                }
+                                __builtin_amdgcn_wave_barrier();
+                                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                            }
+                        }
+                    }
+                    rs += dpp_d<0xb1>(0.0, rs);  // quad_perm [1,0,3,2]
+                    rs += dpp_d<0x4e>(0.0, rs);  // quad_perm [2,3,0,1]
+                }
+            }
+            // ---- publish the row partials; the slots of this turn were emptied before
+            if (u == 0) wave_drain();
+            if (t[u].has_prow(me)) xstore(row_slot(sh, t[u], me, b), rs);
+            if (t[u].has_shift(me)) xstore(&x->shift[b][t[u].I], SI[u]);
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+            for (int k = 0; k < 4; ++k) region[me.lane * 4 + k] = col64[k];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < TP; ++u) {  // and the column partials
+            const Lane me;
+            if (t[u].has_col(me)) {
+                const double* r0 = sh.region[t[u].at][0] + me.t;
+                const double c0 = r0[0], c1 = r0[kRowBufD], c2 = r0[2 * kRowBufD], c3 = r0[3 * kRowBufD];
+                xstore(col_slot(sh, t[u], me, b), (c0 + c1) + (c2 + c3));
+            }
+        }
+        // ---- finalize, decide
+        Wait wait(x);
+        if (fin_wg) steps_finalize(z, x, sh, b, e64, wait);
+        // the dots and this thread's log-sums are asked for first and looked at after the work that
+        // need not wait for them
+        StepDots dots;
+        dots.ask(z, x, b);
+#pragma unroll
+        for (int u = 0; u < TP; ++u) {
+            const Lane me;
+            lzt_r[u] = t[u].has_row(me) ? xload(sh.logr[b] + t[u].i0 + me.t) : 0.0;
+            lzt_c[u] = t[u].has_col(me) ? xload(sh.logc[b] + t[u].J * kBC + me.t) : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < TP; ++u) clear_tile(sh, x, t[u], b == 0 ? 2 : b - 1);  // the turn of the step after the next
+        dots.take(z, x, sh, b, wait);
+        if (z.nvb > 64) __syncthreads();  // uniform in the grid
+        steps_decide(z, sh, step + 1 < max_steps);
+        for (;;) {
+            bool miss = false;
+#pragma unroll
+            for (int u = 0; u < TP; ++u) miss |= is_empty(lzt_c[u]) || is_empty(lzt_r[u]);
+            if (!miss || !wait.again()) break;
+#pragma unroll
+            for (int u = 0; u < TP; ++u) {
+                const Lane me;
+                if (is_empty(lzt_c[u])) lzt_c[u] = xload(sh.logc[b] + t[u].J * kBC + me.t);
+                if (is_empty(lzt_r[u])) lzt_r[u] = xload(sh.logr[b] + t[u].i0 + me.t);
+            }
+        }
+        if (wait.dead) sh.dead = 1;
+        __syncthreads();
+        last = b;
+        if (sh.go <= 0 || sh.dead) break;
+    }
+
+    // ---- what the one-step kernels go on from
+    const Lane me;
+    if (started) {
+        if (fin_wg && !sh.dead) {
+            const FinEntry f(z, me);
+            if (f.own) {
+                const int k = f.entry(z);
+                w.z[k] = sh.fz[me.t];
+                w.p[k] = sh.fp[me.t];
+                w.lz[k] = sh.flz[me.t];
+                w.g[k] = sh.fg[me.t];
+                if (last != 2) xstore(w.lzt + k, sh.fl[me.t]);
+            }
+        }
+        if (blockIdx.x == 0 && me.q == 0 && sh.go < 0 && me.t < z.nvb) {  // the dots of the decision left open
+            double* bd = bdots_of(*wp) + (size_t)me.t * kNDot;
+#pragma unroll
+            for (int d = 0; d < kNDot; ++d) bd[d] = d <= kStepDots ? sh.y[d][me.t] : 0.0;
+        }
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            Trial::copy(*S0, sh.T);
+            S0->undecided = sh.go < 0;
+            if (sh.dead) {
+                S0->done = 1;
+                S0->status = MDOT_E_DEVICE;
+            }
+        }
+    }
+    if (threadIdx.x == 0 &&
+        __hip_atomic_fetch_add(&x->leave, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == gridDim.x) {
+        xstore(&x->leave, 0u);
+        xstore(&x->arrive, 0u);
+    }
 }
 
 // ------------------------------------------------------------------ batched kernels
@@ -1988,7 +2939,7 @@ __global__ void __launch_bounds__(kVecWG, V == kFinMid ? 2 : 1) k_fin_batch(cons
 
 __global__ void __launch_bounds__(kDecideWG) k_decide_batch(const BatchDesc* __restrict__ bd, int parity)
 {
-    for (int b = blockIdx.x; b < bd->nitems; b += gridDim.x) decide_body(*bd->items[b], parity);
+    for (int b = blockIdx.x; b < bd->nitems; b += gridDim.x) decide_body(*bd->items[b], parity, parity ^ 1);
 }
 
 // End-of-chunk done flags, written straight into pinned host memory (a stream-ordered copy
@@ -2595,6 +3546,55 @@ int launch_sweep(const Work& hw, const Work* wd, int parity, void* stream)
 #define L_(CC) hipLaunchKernelGGL(k_sweep<CC>, dim3(tiles), dim3(kWG), 0, (hipStream_t)stream, wd, parity)
     MDOT_CC_SWITCH(cost_code(hw), L_)
 #undef L_
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+// Tiles per workgroup of the resident-steps kernel for hw on a GPU of `cus` compute units, 0 if it
+// does not apply: at most one workgroup per unit, one finalize block each. Up to one tile per unit
+// the workgroup is one quad; two tiles take two quads, four take two quads of two tiles (as four
+// quads of 16 waves, with 128 registers a thread, the cost does not fit them). Sizes past 8192 have a
+// finalize layout of their own, clouds of more than 3 coordinates more registers per column.
+int steps_tiles(const Work& hw, int cus)
+{
+    const int tiles = hw.nrt * hw.nct, most = std::min(cus, kStepsMaxGrid);
+    if (hw.fin_per != 8 || hw.nrt > kStepsMaxRowTiles || hw.fin_nvb > most) return 0;
+    if (hw.cost_kind != MDOT_COST_DENSE && hw.d > 3) return 0;
+    if (tiles <= most) return 1;
+    if (tiles <= 2 * most) return 2;
+    return tiles <= 4 * most ? 4 : 0;
+}
+
+template <int CC>
+static void launch_steps_as(int nt, int grid, const Work* wd, StepsX* x, int max_steps, hipStream_t s)
+{
+    if (nt == 1) hipLaunchKernelGGL((k_steps<CC, 1, 1>), dim3(grid), dim3(256), 0, s, wd, x, max_steps);
+    else if (nt == 2) hipLaunchKernelGGL((k_steps<CC, 2, 1>), dim3(grid), dim3(512), 0, s, wd, x, max_steps);
+    else hipLaunchKernelGGL((k_steps<CC, 2, 2>), dim3(grid), dim3(512), 0, s, wd, x, max_steps);
+}
+
+int launch_steps(const Work& hw, const Work* wd, StepsX* x, int nt, int max_steps, void* stream)
+{
+    const int tiles = hw.nrt * hw.nct, grid = std::max((tiles + nt - 1) / nt, hw.fin_nvb);
+    hipStream_t s = (hipStream_t)stream;
+#define L_(CC) launch_steps_as<CC>(nt, grid, wd, x, max_steps, s)
+    switch (base_code(cost_code(hw))) {
+        case CC_F64: L_(CC_F64); break;
+        case CC_F32: L_(CC_F32); break;
+        case CC_F16: L_(CC_F16); break;
+        case CC_BF16: L_(CC_BF16); break;
+        case CC_PTS_SQ: L_(CC_PTS_SQ); break;
+        case CC_PTS_L1: L_(CC_PTS_L1); break;
+        case CC_PTS_SQ2: L_(CC_PTS_SQ2); break;
+        case CC_PTS_L12: L_(CC_PTS_L12); break;
+        default: return -1;
+    }
+#undef L_
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+int launch_settle(const Work* wd, void* stream)
+{
+    hipLaunchKernelGGL(k_settle, dim3(1), dim3(kDecideWG), 0, (hipStream_t)stream, wd);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
