@@ -933,6 +933,97 @@ __device__ void tile_lse(const Work& w, const SweepArgs& S, const TileCtx& t, do
     if (t.tid == 0) w.tshift[t.I] = SI;
 }
 
+// Row reductions of the Round tiles. A wave leaves B rows of NS sums, then NM minima, per lane in
+// its LDS region (slot (quantity * B + row) at kRoundPad apart) and reduces them all at once, four
+// lanes per slot: one write and about three operations per row and quantity, where a reduction
+// across the lanes of each by itself takes 18. The sums are added in the same balanced tree over
+// the lanes as wave_sum. Returns slot (lane >> 2)'s value in all four of its lanes. With the rows'
+// loads issued four rows ahead as well, n = 4096 FP32: R1 41 -> 31.5 us, R2 47 -> 44 us. (With the
+// column values in registers, at 166 VGPRs and three waves per SIMD, R1 33.5 and R2 38 us, but the LSE
+// path shares the kernel and needs four.)
+constexpr int kRoundPad = 65;       // doubles: the four lanes' reads of 16 slots hit distinct banks
+constexpr int kRoundSlots = 10;     // per wave
+constexpr int kRoundRegion = kRoundSlots * kRoundPad;
+// The Round tiles lay their LDS out as five per-row arrays, five per-column arrays (a lane reads its
+// four columns' values of a row when it needs them: in registers, with those of the other arrays, they
+// do not fit the cap) and the waves' regions.
+constexpr int kRoundAt = 5 * kBR + 5 * kBC;
+static_assert(kRoundAt + 4 * kRoundRegion <= kSmemAll, "LDS for the Round tiles");
+template <int NS, int NM, int B>
+__device__ __forceinline__ double round_reduce(const double* region, int lane)
+{
+    static_assert((NS + NM) * B <= kRoundSlots, "one slot per row and quantity");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    const int slot = min(lane >> 2, (NS + NM) * B - 1);
+    const double* src = region + slot * kRoundPad + (lane & 3) * 16;
+    const bool sum = slot < NS * B;
+    double v[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) v[k] = src[k];
+#pragma unroll
+    for (int w = 1; w < 16; w *= 2)
+#pragma unroll
+        for (int k = 0; k < 16; k += 2 * w) {
+            const double a = v[k] + v[k + w], b = fmin(v[k], v[k + w]);
+            v[k] = NS == 0 ? b : (sum ? a : b);
+        }
+    double r = v[0];
+    const double x1 = dpp_d<0xb1>(0.0, r);  // quad_perm [1,0,3,2]
+    r = (NS == 0 || !sum) ? fmin(r, x1) : r + x1;
+    const double x2 = dpp_d<0x4e>(0.0, r);  // quad_perm [2,3,0,1]
+    r = (NS == 0 || !sum) ? fmin(r, x2) : r + x2;
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    return r;
+}
+
+// The exponentials of one row's four entries (log2 arguments).
+template <bool E64>
+__device__ __forceinline__ void exp2x4(const double x[4], double e[4])
+{
+    if constexpr (E64) {
+        exp2_f64x4(x, e, kExp2C9);
+    } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) e[k] = (double)__builtin_amdgcn_exp2f((float)x[k]);
+    }
+}
+
+// The four consecutive per-column values of a lane.
+__device__ __forceinline__ void cols4(const double* col, int lane, double v[4])
+{
+    const double2 a = ((const double2*)col)[2 * lane], b = ((const double2*)col)[2 * lane + 1];
+    v[0] = a.x; v[1] = a.y; v[2] = b.x; v[3] = b.y;
+}
+
+// Rows of a Round tile, B at a time, the next B being loaded meanwhile (points: read when needed).
+template <class Cost, int B>
+struct RoundRows {
+    typename Cost::Raw raw[B], next[B];
+    static constexpr bool kPoints = std::is_same<typename Cost::Raw, int>::value;
+    __device__ __forceinline__ void ask(const Cost& cost, int r, int j0)
+    {
+        if constexpr (!kPoints) {
+#pragma unroll
+            for (int u = 0; u < B; ++u) next[u] = cost.load(r + u, j0);
+        }
+    }
+    __device__ __forceinline__ void take(const Cost& cost, int r, int j0)
+    {
+        if constexpr (!kPoints) {
+#pragma unroll
+            for (int u = 0; u < B; ++u) raw[u] = next[u];
+            ask(cost, r + B, j0);
+        }
+    }
+    __device__ __forceinline__ void get(const Cost& cost, int r, int j0, int u, double c[4]) const
+    {
+        if constexpr (kPoints) cost.row(r + u, j0, c);
+        else cost.decode(raw[u], c);
+    }
+};
+
 // Round pass 1 (Alg. 3, first half): column sums of F = D(x) P and the column c-transform
 // g'_j = min_i (C_ij - f_i); also the row c-transform f''_i = min_j (C_ij - g_j), for the
 // two potential sets (u, v)/gamma and their finite differences along the annealing path.
@@ -967,7 +1058,8 @@ __device__ void tile_r1(const Work& w, const SweepArgs& S, const TileCtx& t, dou
     }
     {
         const int j = t.J * kBC + t.tid;
-        double vv = 0.0, g1 = INFINITY, g2v = INFINITY;
+        // padding columns: v = -inf makes their exponentials 0, g = -inf their differences +inf
+        double vv = -INFINITY, g1 = -INFINITY, g2v = -INFINITY;
         if (j < n) {
             const Entry e = entry_after(w, S, m + j);
             vv = e.z * LOG2E_D;
@@ -981,16 +1073,6 @@ __device__ void tile_r1(const Work& w, const SweepArgs& S, const TileCtx& t, dou
     __syncthreads();
     const double SI = wave_max(sS[t.lane]);  // S_I = max_i s_i over the kBR (= 64) rows
     const int j0 = t.j0lane;
-    double V[4], G1[4], G2[4];
-    bool ok[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        ok[k] = j0 + k < n;
-        V[k] = sCol[t.lane * 4 + k];
-        G1[k] = sCol[kBC + t.lane * 4 + k];
-        G2[k] = sCol[2 * kBC + t.lane * 4 + k];
-    }
-    __syncthreads();
     if (t.tid < kBR) sWt[t.tid] = exp(sS[t.tid] - SI) * sX[t.tid];
     __syncthreads();
     Cost cost(w, t.i0);
@@ -999,32 +1081,50 @@ __device__ void tile_r1(const Work& w, const SweepArgs& S, const TileCtx& t, dou
     double cm1[4] = {INFINITY, INFINITY, INFINITY, INFINITY}, cm2[4] = {INFINITY, INFINITY, INFINITY, INFINITY};
     const double sc = w.scale;
     const int rbase = t.wave * kRPW;
-    for (int rr = 0; rr < kRPW; ++rr) {
-        const int ir = rbase + rr;
-        const int i = t.i0 + ir;
-        if (i >= m) break;
-        double c[4];
-        cost.row(ir, j0, c);
-        const double A = sA[ir], wt = sWt[ir], f1 = sF1[ir], f2 = sF2[ir];
-        double rm1 = INFINITY, rm2 = INFINITY;
+    const int nrows = min(kRPW, m - (t.i0 + rbase));
+    constexpr int B = sizeof(typename Cost::Raw) > 16 ? 2 : 4;
+    double* region = sm + kRoundAt + t.wave * kRoundRegion;
+    RoundRows<Cost, B> rows;
+    rows.ask(cost, rbase, j0);
+#pragma unroll 1
+    for (int b = 0; b < nrows; b += B) {
+        rows.take(cost, rbase + b, j0);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            if (!ok[k]) continue;
-            double e = exp2_sel<E64>(fma(-g2, c[k], V[k]) + A);
-            col64[k] = fma(wt, e, col64[k]);
-            double cv = sc * c[k];
-            cm1[k] = fmin(cm1[k], cv - f1);
-            cm2[k] = fmin(cm2[k], cv - f2);
-            rm1 = fmin(rm1, cv - G1[k]);
-            rm2 = fmin(rm2, cv - G2[k]);
+        for (int u = 0; u < B; ++u) {
+            if (b + u >= nrows) break;
+            const int ir = rbase + b + u;
+            double c[4], x[4], e[4], V[4];
+            rows.get(cost, rbase + b, j0, u, c);
+            cols4(sCol, t.lane, V);
+            const double A = sA[ir], wt = sWt[ir];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) x[k] = fma(-g2, c[k], V[k]) + A;
+            exp2x4<E64>(x, e);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) col64[k] = fma(wt, e[k], col64[k]);
+            __builtin_amdgcn_sched_barrier(0);  // rows (and their halves) mixed with each other spill
+            const double f1 = sF1[ir], f2 = sF2[ir];
+            double G1[4], G2[4], rm1 = INFINITY, rm2 = INFINITY;
+            cols4(sCol + kBC, t.lane, G1);
+            cols4(sCol + 2 * kBC, t.lane, G2);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const double cv = sc * c[k];
+                cm1[k] = fmin(cm1[k], cv - f1);
+                cm2[k] = fmin(cm2[k], cv - f2);
+                rm1 = fmin(rm1, cv - G1[k]);
+                rm2 = fmin(rm2, cv - G2[k]);
+            }
+            region[u * kRoundPad + t.lane] = rm1;
+            region[(B + u) * kRoundPad + t.lane] = rm2;
+            __builtin_amdgcn_sched_barrier(0);
         }
-        rm1 = wave_min(rm1);
-        rm2 = wave_min(rm2);
-        if (t.lane == 0) {
-            w.rowmin[(size_t)t.J * m + i] = rm1;
-            w.rowmin[(size_t)(w.nct + t.J) * m + i] = rm2;
-        }
+        const double v = round_reduce<0, 2, B>(region, t.lane);
+        const int slot = t.lane >> 2, u = slot % B;
+        if ((t.lane & 3) == 0 && slot < 2 * B && b + u < nrows)
+            w.rowmin[(size_t)(slot < B ? t.J : w.nct + t.J) * m + t.i0 + rbase + b + u] = v;
     }
+    __syncthreads();
     col_combine_store(sCol, col64, t, 0, w.colpart + (size_t)t.I * n, n, t.J * kBC);
     col_combine_store(sCol, cm1, t, 1, w.colmin + (size_t)t.I * n, n, t.J * kBC);
     col_combine_store(sCol, cm2, t, 1, w.colmin + (size_t)(w.nrt + t.I) * n, n, t.J * kBC);
@@ -1057,68 +1157,86 @@ __device__ void tile_r2(const Work& w, const SweepArgs& S, const TileCtx& t, dou
         sA[t.tid] = aa; sF1[t.tid] = f1; sF2[t.tid] = f2;
     }
     {
+        // Padding columns add exact zeros to the sums and +inf to the minima.
         const int j = t.J * kBC + t.tid;
-        double vv = 0.0;
-        if (j < n) vv = entry_after(w, S, m + j).z * LOG2E_D;
-        sCol[t.tid] = vv;
+        const bool ok = j < n;
+        sCol[t.tid] = ok ? entry_after(w, S, m + j).z * LOG2E_D : -INFINITY;
+        sCol[kBC + t.tid] = ok ? w.yc[j] : 0.0;
+        sCol[2 * kBC + t.tid] = ok ? w.errc[j] : 0.0;
+        sCol[3 * kBC + t.tid] = ok ? w.gp[j] : -INFINITY;
+        sCol[4 * kBC + t.tid] = ok ? w.gp[n + j] : -INFINITY;
     }
     __syncthreads();
     // V is the same as in pass 1, so every exp below is bit-identical to pass 1's and the
     // implicit plan F' = D(x) P D(y) is one matrix across both passes; y is applied in FP64.
     const int j0 = t.j0lane;
-    double V[4], Y[4], GP1[4], GP2[4], EC[4];
-    bool ok[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        int j = j0 + k;
-        ok[k] = j < n;
-        V[k] = sCol[t.lane * 4 + k];
-        Y[k] = ok[k] ? w.yc[j] : 0.0;
-        GP1[k] = ok[k] ? w.gp[j] : INFINITY;
-        GP2[k] = ok[k] ? w.gp[n + j] : INFINITY;
-        EC[k] = ok[k] ? w.errc[j] : 0.0;
-    }
-    __syncthreads();
     Cost cost(w, t.i0);
     cost.cols(j0);
     double cm1[4] = {INFINITY, INFINITY, INFINITY, INFINITY}, cm2[4] = {INFINITY, INFINITY, INFINITY, INFINITY};
     const double sc = w.scale;
     const int rbase = t.wave * kRPW;
-    for (int rr = 0; rr < kRPW; ++rr) {
-        const int ir = rbase + rr;
-        const int i = t.i0 + ir;
-        if (i >= m) break;
-        double c[4];
-        cost.row(ir, j0, c);
-        const double A = sA[ir], f1 = sF1[ir], f2 = sF2[ir];
-        double s0 = 0.0, s1 = 0.0, s2 = 0.0, rm1 = INFINITY, rm2 = INFINITY;
+    const int nrows = min(kRPW, m - (t.i0 + rbase));
+    constexpr int B = sizeof(typename Cost::Raw) > 16 ? 2 : 4, H = 2;  // rows loaded, and reduced, at a time
+    double* region = sm + kRoundAt + t.wave * kRoundRegion;
+    RoundRows<Cost, B> rows;
+    rows.ask(cost, rbase, j0);
+#pragma unroll 1
+    for (int b = 0; b < nrows; b += B) {
+        rows.take(cost, rbase + b, j0);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            if (!ok[k]) continue;
-            double cv = sc * c[k];
-            double e = exp2_sel<E64>(fma(-g2, c[k], V[k]) + A) * Y[k];
-            s0 += e;
-            s1 = fma(e, cv, s1);
-            s2 = fma(cv, EC[k], s2);
-            rm1 = fmin(rm1, cv - GP1[k]);
-            rm2 = fmin(rm2, cv - GP2[k]);
-            cm1[k] = fmin(cm1[k], cv - f1);
-            cm2[k] = fmin(cm2[k], cv - f2);
-        }
-        s0 = wave_sum(s0);
-        s1 = wave_sum(s1);
-        s2 = wave_sum(s2);
-        rm1 = wave_min(rm1);
-        rm2 = wave_min(rm2);
-        if (t.lane == 0) {
-            const size_t o = (size_t)t.J * m + i;
-            w.rowpart[o] = s0;
-            w.rowpart2[o] = s1;
-            w.rowpart3[o] = s2;
-            w.rowmin[o] = rm1;
-            w.rowmin[(size_t)(w.nct + t.J) * m + i] = rm2;
+        for (int h = 0; h < B; h += H) {
+            if (b + h >= nrows) break;
+#pragma unroll
+            for (int u = 0; u < H; ++u) {
+                if (b + h + u >= nrows) break;
+                const int ir = rbase + b + h + u;
+                double c[4], x[4], e[4], V[4], Y[4], EC[4];
+                rows.get(cost, rbase + b, j0, h + u, c);
+                cols4(sCol, t.lane, V);
+                const double A = sA[ir];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) x[k] = fma(-g2, c[k], V[k]) + A;
+                exp2x4<E64>(x, e);
+                cols4(sCol + kBC, t.lane, Y);
+                cols4(sCol + 2 * kBC, t.lane, EC);
+                double s0 = 0.0, s1 = 0.0, s2 = 0.0;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const double cv = sc * c[k];
+                    const double ey = e[k] * Y[k];
+                    s0 += ey;
+                    s1 = fma(ey, cv, s1);
+                    s2 = fma(cv, EC[k], s2);
+                }
+                region[u * kRoundPad + t.lane] = s0;
+                region[(H + u) * kRoundPad + t.lane] = s1;
+                region[(2 * H + u) * kRoundPad + t.lane] = s2;
+                __builtin_amdgcn_sched_barrier(0);
+                const double f1 = sF1[ir], f2 = sF2[ir];
+                double GP1[4], GP2[4], rm1 = INFINITY, rm2 = INFINITY;
+                cols4(sCol + 3 * kBC, t.lane, GP1);
+                cols4(sCol + 4 * kBC, t.lane, GP2);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const double cv = sc * c[k];
+                    rm1 = fmin(rm1, cv - GP1[k]);
+                    rm2 = fmin(rm2, cv - GP2[k]);
+                    cm1[k] = fmin(cm1[k], cv - f1);
+                    cm2[k] = fmin(cm2[k], cv - f2);
+                }
+                region[(3 * H + u) * kRoundPad + t.lane] = rm1;
+                region[(4 * H + u) * kRoundPad + t.lane] = rm2;
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            const double v = round_reduce<3, 2, H>(region, t.lane);
+            const int slot = t.lane >> 2, d = slot / H, r = b + h + slot % H;
+            if ((t.lane & 3) == 0 && d < 5 && r < nrows) {
+                double* dst = d == 0 ? w.rowpart : (d == 1 ? w.rowpart2 : (d == 2 ? w.rowpart3 : w.rowmin));
+                dst[(size_t)(d == 4 ? w.nct + t.J : t.J) * m + t.i0 + rbase + r] = v;
+            }
         }
     }
+    __syncthreads();
     col_combine_store(sCol, cm1, t, 1, w.colmin + (size_t)t.I * n, n, t.J * kBC);
     col_combine_store(sCol, cm2, t, 1, w.colmin + (size_t)(w.nrt + t.I) * n, n, t.J * kBC);
 }
