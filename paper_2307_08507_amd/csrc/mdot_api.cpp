@@ -124,8 +124,8 @@ struct mdot_ctx {
     // what the graph was captured with: m, n and the sweep kernel instance (cost code, which also
     // tells the point dimension classes apart)
     int graph_m = 0, graph_n = 0, graph_code = -1, graph_steps = 0;
-    // resident steps of single solves: the GPU's compute units, the exchange memory (allocated by
-    // the first solve that takes them), and whether a wait inside them has ever run out
+    // resident steps and sweeps: the GPU's compute units, the exchange memory, and whether a wait
+    // inside them has ever run out
     int cus = 0;
     StepsX* d_steps = nullptr;
     bool steps_off = false;
@@ -627,12 +627,6 @@ static int ensure_graph(mdot_ctx* ctx, int steps)
         (void)hipGraphExecDestroy(ctx->graph);
         ctx->graph = nullptr;
     }
-    if (steps && !ctx->d_steps) {
-        HIPCHK(ctx, hipMalloc(&ctx->d_steps, sizeof(StepsX)));
-        // on this context's stream: the default stream may not be touched while another thread captures
-        if (launch_fill(reinterpret_cast<double*>(ctx->d_steps), sizeof(StepsX) / sizeof(double), 0.0, ctx->stream))
-            return fail(ctx, MDOT_E_DEVICE, "fill launch failed");
-    }
     hipStream_t cap;
     HIPCHK(ctx, hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
     hipGraph_t g = nullptr;
@@ -978,7 +972,9 @@ int mdot_ctx_create(int device, void* hip_stream, size_t hbm_budget_bytes, mdot_
               hipHostMalloc(&ctx->h_done, kDoneInts * sizeof(int) + sizeof(AloneOut), hipHostMallocMapped | hipHostMallocCoherent) ==
                   hipSuccess &&
               hipHostGetDevicePointer((void**)&ctx->d_hdone, ctx->h_done, 0) == hipSuccess &&
-              hipMalloc(&ctx->d_seq, 2 * sizeof(int)) == hipSuccess && hipMemset(ctx->d_seq, 0, 2 * sizeof(int)) == hipSuccess &&
+              // the exchange memory of the resident kernels, with the chunk counters behind it
+              hipMalloc(&ctx->d_steps, sizeof(StepsX) + 2 * sizeof(int)) == hipSuccess &&
+              hipMemset(ctx->d_steps, 0, sizeof(StepsX) + 2 * sizeof(int)) == hipSuccess &&
               hipHostMalloc(&ctx->h_batch[0], sizeof(BatchDesc), hipHostMallocDefault) == hipSuccess &&
               hipHostMalloc(&ctx->h_batch[1], sizeof(BatchDesc), hipHostMallocDefault) == hipSuccess &&
               hipHostMalloc(&ctx->h_states, kMaxBatch * sizeof(State), hipHostMallocDefault) == hipSuccess &&
@@ -991,6 +987,7 @@ int mdot_ctx_create(int device, void* hip_stream, size_t hbm_budget_bytes, mdot_
               hipEventCreateWithFlags(&ctx->eng_ev[0], hipEventDisableTiming) == hipSuccess &&
               hipEventCreateWithFlags(&ctx->eng_ev[1], hipEventDisableTiming) == hipSuccess &&
               hipEventCreate(&ctx->t0) == hipSuccess && hipEventCreate(&ctx->t1) == hipSuccess;
+    ctx->d_seq = reinterpret_cast<int*>(ctx->d_steps + 1);
     for (int k = 0; ok && k < kMaxBatch; ++k) {
         ok = hipEventCreateWithFlags(&ctx->ret_ev[k], hipEventDisableTiming) == hipSuccess;
         ctx->free_hs.push_back(kMaxBatch - 1 - k);
@@ -1038,7 +1035,6 @@ int mdot_ctx_destroy(mdot_ctx* ctx)
     for (auto& e : ctx->ret_ev)
         if (e) (void)hipEventDestroy(e);
     if (ctx->d_batch) (void)hipFree(ctx->d_batch);
-    if (ctx->d_seq) (void)hipFree(ctx->d_seq);
     if (ctx->d_steps) (void)hipFree(ctx->d_steps);
     for (auto& e : ctx->ev)
         if (e) (void)hipEventDestroy(e);
@@ -1116,6 +1112,7 @@ int mdot_solve(mdot_ctx* ctx, const mdot_cost_desc* cost, const double* r, const
 // allocated); dpart holds 2 doubles per tile for the cost range. The kernels are queued back to
 // back and the host waits once, for the summary the last one writes into host memory; a second
 // time only where FP32 rows or columns left the range and the sweep is run again with FP64 exp.
+// An LSE that fits the resident layout is one kernel, if all of its workgroups get to run at once.
 static int run_alone(mdot_ctx* ctx, ProblemBufs& pb, const mdot_cost_desc* cost, const AloneIn& in, double gamma,
                      double gamma_prev, int exp64, bool round, const double* r, const double* c, double* dpart,
                      double* lr_out, double* lc_out, AloneOut* res)
@@ -1152,6 +1149,32 @@ static int run_alone(mdot_ctx* ctx, ProblemBufs& pb, const mdot_cost_desc* cost,
     hipStream_t st = ctx->stream;
     AloneOut* dout = reinterpret_cast<AloneOut*>(ctx->d_hdone + kDoneInts);
     volatile AloneOut* hout = reinterpret_cast<volatile AloneOut*>(ctx->h_done + kDoneInts);
+    const int nt = (round || !lr_out || ctx->steps_off) ? 0 : steps_tiles(w, ctx->cus);
+    if (lse_resident(nt)) {
+        LseArgs A;
+        A.w = w;
+        A.in = vec;
+        A.gamma = gamma;
+        A.e64 = exp64;
+        A.choose = choose;
+        A.lr_out = lr_out;
+        A.lc_out = lc_out;
+        A.out = dout;
+        hout->done = 0;
+        hout->retry = 0;
+        if (launch_lse(A, ctx->d_steps, nt, st)) return fail(ctx, MDOT_E_DEVICE, "standalone sweep launch failed");
+        HIPCHK(ctx, hipStreamSynchronize(st));
+        if (hout->retry) ctx->steps_off = true;  // a wait ran out: the kernels from here on
+        else if (hout->done && hout->valid) {
+            memcpy(res, const_cast<const AloneOut*>(hout), sizeof *res);
+            return MDOT_OK;
+        } else if (hout->done) {  // the exact range, for the message
+            double scale;
+            int rc = bind_work(ctx, pb, m, n, cost, choose ? 1.0 : cost->scale, r, c, st);
+            if (!rc) rc = resolve_scale(ctx, pb, cost, &scale, st);
+            return rc ? rc : fail(ctx, MDOT_E_DEVICE, "cost range of a standalone sweep not reproduced");
+        }
+    }
     const bool boxes = points && !choose && in.shift;
     int where = kRangeDone, bad = launch_alone_setup(w, S, P, vec, wd, boxes, st);
     if (choose) {

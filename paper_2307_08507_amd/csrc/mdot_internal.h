@@ -226,6 +226,7 @@ struct StepsX {
     uint32_t abort, pad2[31];   // a wait inside the steps ran into its limit (never cleared)
     double shift[3][kStepsMaxRowTiles];   // S_I of the row tiles, three steps in turn
     double dots[3][kStepsMaxGrid][16];    // dots of the finalize blocks, one 128-byte line each
+    double range[4 * kStepsMaxGrid][2];   // standalone LSE: raw cost range of the tiles
 };
 
 // Problems in flight in one batched launch. Every item has its own Work, state slots and
@@ -317,6 +318,17 @@ int launch_cost_range(const Work& hw, const Work* wd, double* part, int box, voi
 int steps_tiles(const Work& hw, int cus);
 int launch_settle(const Work* wd, void* stream);  // the decision it may have left open
 int launch_steps(const Work& hw, const Work* wd, StepsX* x, int nt, int max_steps, void* stream);
+// Arguments of the resident standalone LSE (k_lse).
+struct LseArgs {
+    Work w;
+    AloneIn in;
+    double gamma;
+    int32_t e64, choose;  // choose: a cloud whose scale is 1 / its largest raw value
+    double *lr_out, *lc_out;
+    AloneOut* out;  // device alias of host memory, cleared by the caller
+};
+bool lse_resident(int nt);  // nt: steps_tiles
+int launch_lse(const LseArgs& a, StepsX* x, int nt, void* stream);
 // Standalone sweeps. The finalize kernel and the decide kernel of one step alone; the set-up
 // (boxes: also the point cloud's); row maxima -> shifts, with the cost range; the sweep with the
 // cost range (dense); the scale of a cloud from its range partials; verdict and outputs.

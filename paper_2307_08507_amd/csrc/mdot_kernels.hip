@@ -570,7 +570,8 @@ __device__ __forceinline__ void fma4_sc(double q[4], const double f[4], double c
     q[0] = r0; q[1] = r1; q[2] = r2; q[3] = r3;
 }
 
-// exp2_f64 of four arguments at once (the same operations in the same order per value).
+// exp2_f64 of four arguments at once (the same operations in the same order per value; exp2_f64 itself
+// is what the CPU test of the coefficients reads).
 __device__ __forceinline__ void exp2_f64x4(const double x[4], double e[4], double c9)
 {
     constexpr double kShift = 0x1.8p52;
@@ -598,13 +599,6 @@ __device__ __forceinline__ void exp2_f64x4(const double x[4], double e[4], doubl
         const double p = fma(q[i], f[i], 1.0);
         e[i] = __hiloint2double(__double2hiint(p) + (int)(k[i] << 20), __double2loint(p));
     }
-}
-
-template <bool E64>
-__device__ __forceinline__ double exp2_sel(double x)
-{
-    if constexpr (E64) return exp2_f64(x, kExp2C9);
-    else return (double)__builtin_amdgcn_exp2f((float)x);
 }
 
 // Column combine: per-wave column values (4 per lane) -> one value per column of the tile.
@@ -2174,7 +2168,7 @@ __global__ void __launch_bounds__(kDecideWG) k_settle(const Work* __restrict__ w
 // limit all the same, after which the solve ends with an error.
 constexpr uint64_t kEmpty = 0x7ff8dead0000beefull;
 constexpr uint32_t kStepsAbort = 0x80000000u;
-constexpr uint64_t kStartTicks = 20000;      // 200 us of the 100 MHz wall clock
+constexpr uint64_t kStartTicks = 5000;       // 50 us of the 100 MHz wall clock
 constexpr uint64_t kWaitTicks = 400000000;   // 4 s
 
 template <class T>
@@ -2493,10 +2487,10 @@ __device__ __forceinline__ void steps_load_fin(const Work& w, const StepSize& z,
     sh.fl[me.t] = in.lzt;
 }
 
-// Wait until every workgroup runs; false if one of them does not get to.
-__device__ __forceinline__ bool steps_meet(StepsX* x)
+// Wait until every workgroup has announced itself; false if one of them does not get to run.
+__device__ __forceinline__ bool steps_wait_all(StepsX* x)
 {
-    uint32_t seen = __hip_atomic_fetch_add(&x->arrive, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
+    uint32_t seen = xload(&x->arrive);
     const uint64_t t0 = wall_clock64();
     while (!(seen & kStepsAbort) && seen != gridDim.x) {
         if (wall_clock64() - t0 > kStartTicks)  // give up, unless the last one has just come
@@ -2505,6 +2499,20 @@ __device__ __forceinline__ bool steps_meet(StepsX* x)
         seen = xload(&x->arrive);
     }
     return !(seen & kStepsAbort);
+}
+__device__ __forceinline__ bool steps_meet(StepsX* x)
+{
+    __hip_atomic_fetch_add(&x->arrive, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return steps_wait_all(x);
+}
+// The last workgroup to end clears both counts for the next kernel.
+__device__ __forceinline__ void steps_leave(StepsX* x)
+{
+    if (threadIdx.x == 0 &&
+        __hip_atomic_fetch_add(&x->leave, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == gridDim.x) {
+        xstore(&x->leave, 0u);
+        xstore(&x->arrive, 0u);
+    }
 }
 
 // What the next step does with the vectors.
@@ -2746,17 +2754,153 @@ __device__ __forceinline__ TileCosts<Cost, TP> tile_costs(const Work& w, const S
     else return {{Cost(w, t[0].i0), Cost(w, t[1].i0)}};
 }
 
+// How the tiles' cost is held: in registers where it takes at most 128 of the 256 a thread has, else
+// the rows are read again in every sweep, RB at a time.
+template <class Cost, int TP>
+struct StepKind {
+    using Raw = typename Cost::Raw;
+    static constexpr bool kPoints = std::is_same<Raw, int>::value;
+    static constexpr bool kHold = !kPoints && sizeof(Raw) * TP <= 32;
+    static constexpr int RB = kHold ? kRPW : (sizeof(Raw) <= 16 ? kRPW / 2 : kRPW / 4);
+    static constexpr int kTiles = kHold ? TP : 1;  // tiles' worth of rows in registers
+};
+
+// The sweep of the workgroup's tiles (tile_lse, with the tiles' own state) from the set-up in LDS:
+// weights, exponentials, and the partials stored in turn b's slots, which were emptied before.
+template <class Cost, int NQ, int TP, class K = StepKind<Cost, TP>>
+__device__ __forceinline__ void steps_sweep(StepsShared<NQ * TP>& sh, StepsX* x, const StepTile (&t)[TP], Cost* cost,
+                                            typename Cost::Raw (&raw)[K::kTiles][K::RB], double g2, bool e64, int b)
+{
+    double SI[TP];
+    {
+        const Lane me;
+#pragma unroll
+        for (int u = 0; u < TP; ++u) SI[u] = wave_max(sh.s[t[u].at][me.lane]);
+        // the weights of this wave's rows, kRPW lanes per tile
+        const int u = TP > 1 ? (me.lane / kRPW) % TP : 0, r = me.wave * kRPW + me.lane % kRPW, at = me.q * TP + u;
+        if (me.lane < TP * kRPW) sh.wt[at][r] = exp(sh.s[at][r] - (u == 0 ? SI[0] : SI[TP - 1]));
+    }
+#pragma unroll
+    for (int u = 0; u < TP; ++u) {
+        // ---- sweep (tile_lse, with the tile's own state)
+        double rs = 0.0, col64[4] = {0, 0, 0, 0};
+        const Lane me;
+        Cost& c = cost[u];
+        const double* A = sh.A[t[u].at] + t[u].rbase;
+        const double* wts = sh.wt[t[u].at] + t[u].rbase;
+        double* region = sh.region[t[u].at][me.wave];
+        double V[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) V[k] = sh.colv[t[u].at][me.lane * 4 + k];
+        c.bind_cols(g2, V);
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if constexpr (K::kHold && TP > 1) {
+            // or the entries' conversions to FP64 move out of the step loop, at two registers
+            // each (with one tile that is welcome: there are registers for it)
+#pragma unroll
+            for (int r = 0; r < K::RB; ++r) opaque(raw[u][r]);
+        }
+        if (t[u].has) {
+            if (!e64) {
+                float col32[4] = {0, 0, 0, 0};
+                float rp[kRPW];
+#pragma unroll
+                for (int b0 = 0; b0 < kRPW; b0 += K::RB) {
+                    if constexpr (!K::kHold) {
+#pragma unroll
+                        for (int r = 0; r < K::RB; ++r) raw[0][r] = c.load(t[u].rbase + b0 + r, t[u].J * kBC + me.lane * 4);
+                    }
+#pragma unroll
+                    for (int r0 = 0; r0 < K::RB; ++r0) {
+                        const int r = b0 + r0;
+                        double xa[4];
+                        if constexpr (K::kPoints) c.args(t[u].rbase + r, g2, V, A[r], xa);
+                        else c.args(raw[K::kHold ? u : 0][r0], g2, V, A[r], xa);
+                        const float wt = (float)wts[r];
+                        float e[4];
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) e[k] = __builtin_amdgcn_exp2f((float)xa[k]);
+                        rp[r] = (e[0] + e[1]) + (e[2] + e[3]);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) col32[k] = fmaf(wt, e[k], col32[k]);
+                        if ((r & 7) == 7) {
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) {
+                                col64[k] += (double)col32[k];
+                                col32[k] = 0.f;
+                            }
+                        }
+                    }
+                }
+                rs = rows_reduce_f32(rp, (float*)region, me.lane);
+            } else {
+                double c9 = kExp2C9;
+                asm volatile("" : "+v"(c9));
+#pragma unroll
+                for (int b0 = 0; b0 < kRPW; b0 += K::RB) {
+                    if constexpr (!K::kHold) {
+#pragma unroll
+                        for (int r = 0; r < K::RB; ++r) raw[0][r] = c.load(t[u].rbase + b0 + r, t[u].J * kBC + me.lane * 4);
+                    }
+#pragma unroll
+                    for (int r0 = 0; r0 < K::RB; ++r0) {
+                        const int r = b0 + r0;
+                        if (r < t[u].nrows) {
+                            double xa[4], e[4];
+                            if constexpr (K::kPoints) c.args(t[u].rbase + r, g2, V, A[r], xa);
+                            else c.args(raw[K::kHold ? u : 0][r0], g2, V, A[r], xa);
+                            const double wt = wts[r];
+                            exp2_f64x4(xa, e, c9);
+                            region[(r & 7) * 64 + me.lane] = (e[0] + e[1]) + (e[2] + e[3]);
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) col64[k] = fma(wt, e[k], col64[k]);
+                        }
+                        if ((r & 7) == 7) {  // eight rows' partials are there: lanes of these rows sum them
+                            __builtin_amdgcn_wave_barrier();
+                            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                            const int rr = me.lane >> 2, hq = me.lane & 3;
+                            if ((rr >> 3) == (r >> 3)) {
+                                const double* src = region + (rr & 7) * 64 + hq * 16;
+#pragma unroll
+                                for (int k = 0; k < 16; ++k) rs += src[k ^ rr];
+                            }
+                            __builtin_amdgcn_wave_barrier();
+                            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                        }
+                    }
+                }
+                rs += dpp_d<0xb1>(0.0, rs);  // quad_perm [1,0,3,2]
+                rs += dpp_d<0x4e>(0.0, rs);  // quad_perm [2,3,0,1]
+            }
+        }
+        // ---- publish the row partials; the slots of this turn were emptied before
+        if (u == 0) wave_drain();
+        if (t[u].has_prow(me)) xstore(row_slot(sh, t[u], me, b), rs);
+        if (t[u].has_shift(me)) xstore(&x->shift[b][t[u].I], SI[u]);
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+        for (int k = 0; k < 4; ++k) region[me.lane * 4 + k] = col64[k];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < TP; ++u) {  // and the column partials
+        const Lane me;
+        if (t[u].has_col(me)) {
+            const double* r0 = sh.region[t[u].at][0] + me.t;
+            const double c0 = r0[0], c1 = r0[kRowBufD], c2 = r0[2 * kRowBufD], c3 = r0[3 * kRowBufD];
+            xstore(col_slot(sh, t[u], me, b), (c0 + c1) + (c2 + c3));
+        }
+    }
+}
+
 // NQ quads of TP tiles each.
 template <int CC, int NQ, int TP>
 __global__ void __launch_bounds__(256 * NQ) k_steps(const Work* __restrict__ wp, StepsX* __restrict__ x, int max_steps)
 {
     using Cost = typename CostOf<CC>::T;
-    using Raw = typename Cost::Raw;
-    constexpr bool kPoints = std::is_same<Raw, int>::value;
-    // the tiles' cost entries stay in registers, at most 128 of the 256 a thread has; else the rows
-    // are read again in every step, RB at a time
-    constexpr bool kHold = !kPoints && sizeof(Raw) * TP <= 32;
-    constexpr int RB = kHold ? kRPW : (sizeof(Raw) <= 16 ? kRPW / 2 : kRPW / 4);
+    using K = StepKind<Cost, TP>;
     __shared__ StepsShared<NQ * TP> sh;
 
     if (!steps_go(*state_slot(*wp, 0))) return;  // the same in every workgroup
@@ -2782,7 +2926,7 @@ __global__ void __launch_bounds__(256 * NQ) k_steps(const Work* __restrict__ wp,
         for (int u = 0; u < TP; ++u) t[u].set(w, NQ * TP, me.q * TP + u);
     }
     TileCosts<Cost, TP> cost = tile_costs<Cost, TP>(w, t);
-    Raw raw[kHold ? TP : 1][RB];
+    typename Cost::Raw raw[K::kTiles][K::RB];
     double lzt_r[TP], lzt_c[TP];  // trial log-sums of this thread's rows and columns
 #pragma unroll
     for (int u = 0; u < TP; ++u) {
@@ -2793,9 +2937,9 @@ __global__ void __launch_bounds__(256 * NQ) k_steps(const Work* __restrict__ wp,
         c.bind_rows(sh.x[t[u].at], sh.x[t[u].at] + 2 * kBR);
         if (me.t < kBR) sh.rxx[t[u].at][me.t] = c.row_fixed(me.t, t[u].i0 + me.t);
         c.cols_fixed(g2);
-        if constexpr (kHold) {
+        if constexpr (K::kHold) {
 #pragma unroll
-            for (int r = 0; r < RB; ++r) raw[u][r] = c.load(t[u].rbase + r, j0);
+            for (int r = 0; r < K::RB; ++r) raw[u][r] = c.load(t[u].rbase + r, j0);
         }
         lzt_r[u] = lzt_c[u] = 0.0;
         steps_load(w, a0, sh, t[u]);
@@ -2818,128 +2962,7 @@ __global__ void __launch_bounds__(256 * NQ) k_steps(const Work* __restrict__ wp,
         for (int u = 0; u < TP; ++u) steps_update<Cost>(sh, t[u], g2, lzt_r[u], lzt_c[u]);
         __syncthreads();
         const bool e64 = __builtin_amdgcn_readfirstlane(sh.T.exp64) != 0;
-        double SI[TP];
-        {
-            const Lane me;
-#pragma unroll
-            for (int u = 0; u < TP; ++u) SI[u] = wave_max(sh.s[t[u].at][me.lane]);
-            // the weights of this wave's rows, kRPW lanes per tile
-            const int u = TP > 1 ? (me.lane / kRPW) % TP : 0, r = me.wave * kRPW + me.lane % kRPW, at = me.q * TP + u;
-            if (me.lane < TP * kRPW) sh.wt[at][r] = exp(sh.s[at][r] - (u == 0 ? SI[0] : SI[TP - 1]));
-        }
-#pragma unroll
-        for (int u = 0; u < TP; ++u) {
-            // ---- sweep (tile_lse, with the tile's own state)
-            double rs = 0.0, col64[4] = {0, 0, 0, 0};
-            const Lane me;
-            Cost& c = cost.c[u];
-            const double* A = sh.A[t[u].at] + t[u].rbase;
-            const double* wts = sh.wt[t[u].at] + t[u].rbase;
-            double* region = sh.region[t[u].at][me.wave];
-            double V[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) V[k] = sh.colv[t[u].at][me.lane * 4 + k];
-            c.bind_cols(g2, V);
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            if constexpr (kHold && TP > 1) {
-                // or the entries' conversions to FP64 move out of the step loop, at two registers
-                // each (with one tile that is welcome: there are registers for it)
-#pragma unroll
-                for (int r = 0; r < RB; ++r) opaque(raw[u][r]);
-            }
-            if (t[u].has) {
-                if (!e64) {
-                    float col32[4] = {0, 0, 0, 0};
-                    float rp[kRPW];
-#pragma unroll
-                    for (int b0 = 0; b0 < kRPW; b0 += RB) {
-                        if constexpr (!kHold) {
-#pragma unroll
-                            for (int r = 0; r < RB; ++r) raw[0][r] = c.load(t[u].rbase + b0 + r, t[u].J * kBC + me.lane * 4);
-                        }
-#pragma unroll
-                        for (int r0 = 0; r0 < RB; ++r0) {
-                            const int r = b0 + r0;
-                            double xa[4];
-                            if constexpr (kPoints) c.args(t[u].rbase + r, g2, V, A[r], xa);
-                            else c.args(raw[kHold ? u : 0][r0], g2, V, A[r], xa);
-                            const float wt = (float)wts[r];
-                            float e[4];
-#pragma unroll
-                            for (int k = 0; k < 4; ++k) e[k] = __builtin_amdgcn_exp2f((float)xa[k]);
-                            rp[r] = (e[0] + e[1]) + (e[2] + e[3]);
-#pragma unroll
-                            for (int k = 0; k < 4; ++k) col32[k] = fmaf(wt, e[k], col32[k]);
-                            if ((r & 7) == 7) {
-#pragma unroll
-                                for (int k = 0; k < 4; ++k) {
-                                    col64[k] += (double)col32[k];
-                                    col32[k] = 0.f;
-                                }
-                            }
-                        }
-                    }
-                    rs = rows_reduce_f32(rp, (float*)region, me.lane);
-                } else {
-                    double c9 = kExp2C9;
-                    asm volatile("" : "+v"(c9));
-#pragma unroll
-                    for (int b0 = 0; b0 < kRPW; b0 += RB) {
-                        if constexpr (!kHold) {
-#pragma unroll
-                            for (int r = 0; r < RB; ++r) raw[0][r] = c.load(t[u].rbase + b0 + r, t[u].J * kBC + me.lane * 4);
-                        }
-#pragma unroll
-                        for (int r0 = 0; r0 < RB; ++r0) {
-                            const int r = b0 + r0;
-                            if (r < t[u].nrows) {
-                                double xa[4], e[4];
-                                if constexpr (kPoints) c.args(t[u].rbase + r, g2, V, A[r], xa);
-                                else c.args(raw[kHold ? u : 0][r0], g2, V, A[r], xa);
-                                const double wt = wts[r];
-                                exp2_f64x4(xa, e, c9);
-                                region[(r & 7) * 64 + me.lane] = (e[0] + e[1]) + (e[2] + e[3]);
-#pragma unroll
-                                for (int k = 0; k < 4; ++k) col64[k] = fma(wt, e[k], col64[k]);
-                            }
-                            if ((r & 7) == 7) {  // eight rows' partials are there: lanes of these rows sum them
-                                __builtin_amdgcn_wave_barrier();
-                                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                                const int rr = me.lane >> 2, hq = me.lane & 3;
-                                if ((rr >> 3) == (r >> 3)) {
-                                    const double* src = region + (rr & 7) * 64 + hq * 16;
-#pragma unroll
-                                    for (int k = 0; k < 16; ++k) rs += src[k ^ rr];
-                                }
-                                __builtin_amdgcn_wave_barrier();
-                                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                            }
-                        }
-                    }
-                    rs += dpp_d<0xb1>(0.0, rs);  // quad_perm [1,0,3,2]
-                    rs += dpp_d<0x4e>(0.0, rs);  // quad_perm [2,3,0,1]
-                }
-            }
-            // ---- publish the row partials; the slots of this turn were emptied before
-            if (u == 0) wave_drain();
-            if (t[u].has_prow(me)) xstore(row_slot(sh, t[u], me, b), rs);
-            if (t[u].has_shift(me)) xstore(&x->shift[b][t[u].I], SI[u]);
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-#pragma unroll
-            for (int k = 0; k < 4; ++k) region[me.lane * 4 + k] = col64[k];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int u = 0; u < TP; ++u) {  // and the column partials
-            const Lane me;
-            if (t[u].has_col(me)) {
-                const double* r0 = sh.region[t[u].at][0] + me.t;
-                const double c0 = r0[0], c1 = r0[kRowBufD], c2 = r0[2 * kRowBufD], c3 = r0[3 * kRowBufD];
-                xstore(col_slot(sh, t[u], me, b), (c0 + c1) + (c2 + c3));
-            }
-        }
+        steps_sweep<Cost, NQ, TP>(sh, x, t, cost.c, raw, g2, e64, b);
         // ---- finalize, decide
         Wait wait(x);
         if (fin_wg) steps_finalize(z, x, sh, b, e64, wait);
@@ -3004,11 +3027,302 @@ __global__ void __launch_bounds__(256 * NQ) k_steps(const Work* __restrict__ wp,
             }
         }
     }
-    if (threadIdx.x == 0 &&
-        __hip_atomic_fetch_add(&x->leave, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == gridDim.x) {
-        xstore(&x->leave, 0u);
-        xstore(&x->arrive, 0u);
+    steps_leave(x);
+}
+
+// ------------------------------------------------------------------ resident standalone LSE
+// mdot_lse2 of a problem of one or two tiles per workgroup, as one kernel: load the vectors
+// and the cost, row maxima (where no shifts are given) with the cost range, sweep, finalize, again
+// with FP64 exponentials where FP32 rows or columns left the range, outputs. As six kernels (n = 256)
+// it is bound by their boundaries, and the cost is read twice; here the tiles are loaded once and the
+// workgroups exchange row maxima, partials and dots as in k_steps. Same arithmetic, same bits.
+// out->done stays 0 if the workgroups could not meet, and out->retry is set if a wait ran out; the
+// caller then takes the kernels.
+
+// Raw entries of row r of the tile (columns j0 ..): held, or recomputed from points.
+template <class Cost, class K>
+__device__ __forceinline__ void lse_row(const Cost& c, const StepTile& t, typename Cost::Raw (&raw)[K::kTiles][K::RB], int u,
+                                        int r, int j0, double e[4])
+{
+    static_assert(K::kPoints || K::kHold, "the cost is read once");
+    if constexpr (K::kPoints) c.row(t.rbase + r, j0, e);
+    else c.decode(raw[u][r], e);
+}
+
+// Row i's shift: the largest of its tiles' maxima, as they arrive.
+__device__ __forceinline__ double lse_shift(const Work& w, const StepSize& z, int i, Wait& wait)
+{
+    double mx = -INFINITY;
+    for (int J0 = 0; J0 < z.nct; J0 += 8) {
+        double v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = J0 + k < z.nct ? xload(w.rowmin + (size_t)(J0 + k) * z.m + i) : -INFINITY;
+        for (;;) {
+            bool miss = false;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) miss |= is_empty(v[k]);
+            if (!miss || !wait.again()) break;
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                if (is_empty(v[k])) v[k] = xload(w.rowmin + (size_t)(J0 + k) * z.m + i);
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k) mx = fmax(mx, v[k]);
     }
+    return mx;
+}
+
+// Cost range over all tiles, as they arrive, with the whole workgroup.
+template <int NT>
+__device__ __forceinline__ void lse_range(StepsX* x, StepsShared<NT>& sh, int ntiles, int nq, Wait& wait, double* lo, double* hi)
+{
+    double a = INFINITY, b = -INFINITY;
+    bool bad = false;
+    for (int i = threadIdx.x; i < ntiles; i += 256 * nq) {
+        double p = xload(&x->range[i][0]), q = xload(&x->range[i][1]);
+        while ((is_empty(p) || is_empty(q)) && wait.again()) {
+            p = xload(&x->range[i][0]);
+            q = xload(&x->range[i][1]);
+        }
+        a = fmin(a, p);
+        bad |= q != q;
+        b = fmax(b, q);
+    }
+    a = wave_min(a);
+    b = wave_max(b);
+    const int wv = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) {
+        sh.y[0][wv] = a;
+        sh.y[1][wv] = b;
+    }
+    bad = __syncthreads_or(bad);
+    a = sh.y[0][0];
+    b = sh.y[1][0];
+    for (int q = 1; q < 4 * nq; ++q) {
+        a = fmin(a, sh.y[0][q]);
+        b = fmax(b, sh.y[1][q]);
+    }
+    __syncthreads();
+    *lo = a;
+    *hi = bad ? NAN : b;
+}
+
+template <int CC, int NQ, int TP>
+__global__ void __launch_bounds__(256 * NQ) k_lse(LseArgs A, StepsX* __restrict__ x)
+{
+    using Cost = typename CostOf<CC>::T;
+    using K = StepKind<Cost, TP>;
+    __shared__ StepsShared<NQ * TP> sh;
+
+    const Work& w = A.w;
+    const StepSize z(w);
+    const bool fin_wg = (int)blockIdx.x < z.nvb;
+    if (threadIdx.x == 0) {
+        sh.T = Trial{};
+        sh.T.ls_phase = LS_STANDALONE;
+        sh.dead = 0;
+        steps_slots(w, sh);
+    }
+    __syncthreads();
+    StepTile t[TP];
+    {
+        const Lane me;
+#pragma unroll
+        for (int u = 0; u < TP; ++u) t[u].set(w, NQ * TP, me.q * TP + u);
+    }
+    // ---- empty the slots, announce this workgroup, load
+    const int ntiles = z.nrt * z.nct;
+#pragma unroll
+    for (int u = 0; u < TP; ++u) {
+        const Lane me;
+        clear_tile(sh, x, t[u], 0);
+        clear_tile(sh, x, t[u], 1);
+        if (t[u].has_prow(me))
+            xstore(w.rowmin + (size_t)t[u].J * z.m + (t[u].i0 + t[u].rbase) + (me.lane >> 2), empty_slot());
+        if (t[u].has && me.t < 2) xstore(&x->range[t[u].I * z.nct + t[u].J][me.t], empty_slot());
+    }
+    if (fin_wg) clear_fin(sh, z, x, 0);
+    wave_drain();
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_fetch_add(&x->arrive, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    TileCosts<Cost, TP> cost = tile_costs<Cost, TP>(w, t);
+    typename Cost::Raw raw[K::kTiles][K::RB];
+#pragma unroll
+    for (int u = 0; u < TP; ++u) {
+        const Lane me;
+        Cost& c = cost.c[u];
+        const int j0 = t[u].J * kBC + me.lane * 4;
+        c.cols(j0);
+        c.bind_rows(sh.x[t[u].at], sh.x[t[u].at] + 2 * kBR);
+        if (me.t < kBR) sh.rxx[t[u].at][me.t] = c.row_fixed(me.t, t[u].i0 + me.t);
+        if constexpr (K::kHold) {
+#pragma unroll
+            for (int r = 0; r < K::RB; ++r) raw[u][r] = c.load(t[u].rbase + r, j0);
+        }
+        if (t[u].has_col(me)) sh.cz[t[u].at][me.t] = A.in.v[t[u].J * kBC + me.t];
+        if (t[u].has_row(me)) sh.rz[t[u].at][me.t] = A.in.u[t[u].i0 + me.t];
+    }
+    if (fin_wg) {
+        const Lane me;
+        const FinEntry f(z, me);
+        if (f.own) sh.fp[me.t] = sh.flz[me.t] = sh.flt[me.t] = sh.frt[me.t] = sh.fg[me.t] = 0.0;
+    }
+    if (threadIdx.x == 0) sh.go = steps_wait_all(x);
+    __syncthreads();
+    const bool started = sh.go != 0;
+    Wait wait(x);
+    if (started) {
+        double scale = w.scale;
+        // ---- cost range of the tiles; the scale first, where it follows from the range
+#pragma unroll
+        for (int u = 0; u < TP; ++u) {
+            const Lane me;
+            const int j0 = t[u].J * kBC + me.lane * 4;
+            RangeOf<Cost> rg;
+#pragma unroll
+            for (int r = 0; r < kRPW; ++r)
+                if (r < t[u].nrows) {
+                    double e[4];
+                    lse_row<Cost, K>(cost.c[u], t[u], raw, u, r, j0, e);
+                    rg.add4(e, t[u].n - j0);
+                }
+            const double lo = wave_min((double)rg.lo), hi = wave_max((double)rg.hi);
+            const bool bad = __any(rg.bad);
+            if (me.lane == 0) {
+                sh.y[0][t[u].at * 4 + me.wave] = lo;
+                sh.y[1][t[u].at * 4 + me.wave] = bad ? NAN : hi;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < TP; ++u) {
+            const Lane me;
+            if (t[u].has && me.t == 0) {
+                const double *lo = sh.y[0] + t[u].at * 4, *hi = sh.y[1] + t[u].at * 4;
+                double a = lo[0], c = hi[0];
+#pragma unroll
+                for (int q = 1; q < 4; ++q) {
+                    a = fmin(a, lo[q]);
+                    c = (c != c || hi[q] != hi[q]) ? NAN : fmax(c, hi[q]);
+                }
+                double* dst = x->range[t[u].I * z.nct + t[u].J];
+                xstore(dst, a);
+                xstore(dst + 1, c);
+            }
+        }
+        __syncthreads();
+        if (A.choose) {
+            double lo, hi;
+            lse_range(x, sh, ntiles, NQ, wait, &lo, &hi);
+            scale = hi > 0.0 ? 1.0 / hi : 1.0;
+        }
+        const double g2 = A.gamma * scale * LOG2E_D;
+        // ---- row shifts: given, or the maxima of X_ij over the columns (k_row_max, k_fold_max)
+        if (A.in.shift) {
+#pragma unroll
+            for (int u = 0; u < TP; ++u) {
+                const Lane me;
+                if (t[u].has_row(me)) sh.rlz[t[u].at][me.t] = A.in.shift[t[u].i0 + me.t];
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < TP; ++u) {
+                const Lane me;
+                double* region = sh.region[t[u].at][me.wave];
+                const int j0 = t[u].J * kBC + me.lane * 4;
+                double V[4], mx = -INFINITY;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) V[k] = j0 + k < t[u].n ? sh.cz[t[u].at][me.lane * 4 + k] * LOG2E_D : -INFINITY;
+#pragma unroll
+                for (int r = 0; r < kRPW; ++r) {
+                    if (r < t[u].nrows) {
+                        double e[4], m = -INFINITY;
+                        lse_row<Cost, K>(cost.c[u], t[u], raw, u, r, j0, e);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) m = fmax(m, fma(-g2, e[k], V[k]));
+                        region[(r & 7) * 64 + me.lane] = m;
+                    }
+                    if ((r & 7) == 7) {
+                        __builtin_amdgcn_wave_barrier();
+                        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                        const int rr = me.lane >> 2, hq = me.lane & 3;
+                        if ((rr >> 3) == (r >> 3)) {
+                            const double* src = region + (rr & 7) * 64 + hq * 16;
+#pragma unroll
+                            for (int k = 0; k < 16; ++k) mx = fmax(mx, src[k ^ rr]);
+                        }
+                        __builtin_amdgcn_wave_barrier();
+                        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                    }
+                }
+                mx = fmax(mx, dpp_d<0xb1>(-INFINITY, mx));
+                mx = fmax(mx, dpp_d<0x4e>(-INFINITY, mx));
+                if (t[u].has_prow(me)) {
+                    const int i = t[u].rbase + (me.lane >> 2);
+                    xstore(w.rowmin + (size_t)t[u].J * z.m + t[u].i0 + i, fma(sh.rz[t[u].at][i], LOG2E_D, mx) * LN2_D);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < TP; ++u) {
+                const Lane me;
+                if (t[u].has_row(me)) sh.rlz[t[u].at][me.t] = lse_shift(w, z, t[u].i0 + me.t, wait);
+            }
+        }
+        if (fin_wg) {
+            const Lane me;
+            const FinEntry f(z, me);
+            if (f.own && f.row) sh.flz[me.t] = A.in.shift ? A.in.shift[f.k] : lse_shift(w, z, f.k, wait);
+        }
+        // ---- tile set-up (steps_update with z = (u, v), p = 0)
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < TP; ++u) {
+            const Lane me;
+            cost.c[u].cols_fixed(g2);
+            if (me.t < kBR) {
+                const bool hr = t[u].has_row(me);
+                const double lz = hr ? sh.rlz[t[u].at][me.t] : 0.0, zz = hr ? sh.rz[t[u].at][me.t] : 0.0;
+                sh.s[t[u].at][me.t] = hr ? lz : -INFINITY;
+                sh.A[t[u].at][me.t] = hr ? Cost::row_term(g2, sh.rxx[t[u].at][me.t], (zz - lz) * LOG2E_D) : -INFINITY;
+            }
+            sh.colv[t[u].at][me.t] = t[u].has_col(me) ? sh.cz[t[u].at][me.t] * LOG2E_D : -INFINITY;
+        }
+        __syncthreads();
+        // ---- sweep, at most twice
+        bool e64 = A.e64 != 0, any = false;
+        for (int b = 0;; ++b) {
+            steps_sweep<Cost, NQ, TP>(sh, x, t, cost.c, raw, g2, e64, b);
+            if (fin_wg) steps_finalize(z, x, sh, b, e64, wait);
+            StepDots dots;
+            dots.ask(z, x, b);
+            dots.take(z, x, sh, b, wait);
+            __syncthreads();
+            any = false;
+            for (int i = threadIdx.x; i < z.nvb; i += blockDim.x) any |= sh.y[kStepDots][i] != 0.0;
+            any = __syncthreads_or(any);
+            if (!any || e64) break;
+            e64 = true;
+        }
+        // ---- outputs, if every entry of the scaled cost lies in [0, 1]
+        if (fin_wg || blockIdx.x == 0) {
+            double lo, hi;
+            lse_range(x, sh, ntiles, NQ, wait, &lo, &hi);
+            const bool dead = __syncthreads_or(wait.dead), valid = range_valid(scale, lo, hi);
+            if (fin_wg && valid && !dead) {
+                const Lane me;
+                const FinEntry f(z, me);
+                if (f.own) (f.row ? A.lr_out : A.lc_out)[f.k] = sh.fl[me.t];
+            }
+            if (dead && threadIdx.x == 0) A.out->retry = 1;
+            if (blockIdx.x == 0 && threadIdx.x == 0 && !dead) {
+                A.out->valid = valid;
+                A.out->status = any ? MDOT_W_RANGE : MDOT_OK;
+                A.out->scale = scale;
+                A.out->done = 1;
+            }
+        }
+    }
+    steps_leave(x);
 }
 
 // ------------------------------------------------------------------ batched kernels
@@ -3695,6 +4009,40 @@ int launch_steps(const Work& hw, const Work* wd, StepsX* x, int nt, int max_step
     const int tiles = hw.nrt * hw.nct, grid = std::max((tiles + nt - 1) / nt, hw.fin_nvb);
     hipStream_t s = (hipStream_t)stream;
 #define L_(CC) launch_steps_as<CC>(nt, grid, wd, x, max_steps, s)
+    switch (base_code(cost_code(hw))) {
+        case CC_F64: L_(CC_F64); break;
+        case CC_F32: L_(CC_F32); break;
+        case CC_F16: L_(CC_F16); break;
+        case CC_BF16: L_(CC_BF16); break;
+        case CC_PTS_SQ: L_(CC_PTS_SQ); break;
+        case CC_PTS_L1: L_(CC_PTS_L1); break;
+        case CC_PTS_SQ2: L_(CC_PTS_SQ2); break;
+        case CC_PTS_L12: L_(CC_PTS_L12); break;
+        default: return -1;
+    }
+#undef L_
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+template <int CC>
+static void launch_lse_as(int nt, int grid, const LseArgs& a, StepsX* x, hipStream_t s)
+{
+    if (nt == 1) hipLaunchKernelGGL((k_lse<CC, 1, 1>), dim3(grid), dim3(256), 0, s, a, x);
+    else hipLaunchKernelGGL((k_lse<CC, 2, 1>), dim3(grid), dim3(512), 0, s, a, x);
+}
+
+// Up to two tiles per workgroup (n about 2900) one kernel is faster: 17 to 27 us, where the six
+// kernels take 27 us at n = 256 and the host queues each. With four the compute units hold one
+// workgroup of two waves per SIMD and nothing overlaps its exchanges: n = 4096 with shifts 42 us,
+// 34 us as kernels.
+bool lse_resident(int nt) { return nt == 1 || nt == 2; }
+
+int launch_lse(const LseArgs& a, StepsX* x, int nt, void* stream)
+{
+    const Work& hw = a.w;
+    const int tiles = hw.nrt * hw.nct, grid = std::max((tiles + nt - 1) / nt, hw.fin_nvb);
+    hipStream_t s = (hipStream_t)stream;
+#define L_(CC) launch_lse_as<CC>(nt, grid, a, x, s)
     switch (base_code(cost_code(hw))) {
         case CC_F64: L_(CC_F64); break;
         case CC_F32: L_(CC_F32); break;

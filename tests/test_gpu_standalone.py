@@ -97,3 +97,53 @@ def test_rows_starting_on_any_element(ctx, dtype, m, n, offset):
         assert rc == 0
         np.testing.assert_allclose(lr, lr_o, rtol=0, atol=2e-6)
         np.testing.assert_allclose(lc, lc_o, rtol=0, atol=2e-6)
+
+
+# one kernel for the whole call up to two tiles per workgroup (more finalize blocks than tile
+# workgroups among the sizes), several kernels beyond, against FP64 torch.
+# F64: FP64 throughout, sums in another order: |d log-sum| <= 1e-11. F32: 2e-6 as in the parity tests.
+@pytest.mark.parametrize("m,n", [(64, 64), (70, 4000), (2048, 2048), (2100, 2049), (2880, 3000), (4096, 4096), (8192, 1000)])
+@pytest.mark.parametrize("dtype,prec", [(torch.float64, "f64"), (torch.float32, "f64"), (torch.float32, "f32"),
+                                        (torch.float16, "f32")])
+@pytest.mark.parametrize("shift", [False, True])
+def test_layouts_of_the_resident_sweep(ctx, m, n, dtype, prec, shift):
+    print(f"layout {m}x{n} {dtype} {prec} shift={shift}", flush=True)
+    C = torch.rand(m, n, device="cuda", dtype=torch.float64).to(dtype)
+    rc, lr, lc, u, v = _lse(ctx, M.dense_cost(C), m, n, shift, prec)
+    X = dev(u)[:, None] + dev(v)[None, :] - 20.0 * C.double()
+    assert rc == 0
+    tol = 1e-11 if prec == "f64" else 2e-6
+    np.testing.assert_allclose(lr, torch.logsumexp(X, 1).cpu().numpy(), rtol=0, atol=tol)
+    np.testing.assert_allclose(lc, torch.logsumexp(X, 0).cpu().numpy(), rtol=0, atol=tol)
+
+
+@pytest.mark.parametrize("n", [200, 2200, 4000])
+def test_fp32_range_is_retried_in_fp64(ctx, n):
+    # predictions 60 nats (86 binary orders) below the row sums: the FP32 sums overflow their range
+    # and the call runs the sweep again with FP64 exponentials
+    C = torch.rand(n, n, device="cuda", dtype=torch.float32)
+    rng = np.random.default_rng(n)
+    u, v = rng.standard_normal(n) * 0.3 - np.log(n), rng.standard_normal(n) * 0.3
+    X = dev(u)[:, None] + dev(v)[None, :] - 20.0 * C.double()
+    want = torch.logsumexp(X, 1)
+    lr, lc = torch.empty_like(want), torch.empty_like(want)
+    print(f"retry n={n}", flush=True)
+    assert ctx.lse2(M.dense_cost(C), dev(u), dev(v), 20.0, lr, lc, shift=want - 60.0) == 0
+    np.testing.assert_allclose(lr.cpu().numpy(), want.cpu().numpy(), rtol=0, atol=1e-11)
+    np.testing.assert_allclose(lc.cpu().numpy(), torch.logsumexp(X, 0).cpu().numpy(), rtol=0, atol=1e-11)
+
+
+def test_scale_chosen_by_the_library(ctx):
+    for n, d in ((300, 2), (2300, 3)):
+        rng = np.random.default_rng(d)
+        X, Y = rng.standard_normal((n, d)).astype(np.float32), rng.standard_normal((n, d)).astype(np.float32)
+        XY = dev(np.concatenate([X.ravel(), Y.ravel()]), torch.float32)
+        a, b = dev(X)[:, None], dev(Y)[None]
+        raw = ((a - b) ** 2).sum(-1)
+        for shift in (False, True):
+            print(f"chosen scale n={n} d={d} shift={shift}", flush=True)
+            rc, lr, lc, u, v = _lse(ctx, M.point_cost(XY, n, d, "sqeuclid"), n, n, shift, "f64")
+            X2 = dev(u)[:, None] + dev(v)[None, :] - 20.0 * raw / raw.max()
+            assert rc == 0
+            np.testing.assert_allclose(lr, torch.logsumexp(X2, 1).cpu().numpy(), rtol=0, atol=1e-11)
+            np.testing.assert_allclose(lc, torch.logsumexp(X2, 0).cpu().numpy(), rtol=0, atol=1e-11)
