@@ -162,37 +162,55 @@ struct DenseCost {
                                                kBufDword3);
     }
     __device__ __forceinline__ void cols(int) {}
-    // row r of the tile (global row i0 + r), columns j0..j0+3; columns >= n are masked by
-    // the caller, their values are unspecified (or 0 past the end of the matrix). The loads need
-    // dword alignment only, which every FP32 and FP64 row and every 16-bit row of even length in
-    // a matrix that starts on a dword has; the range check is per dword. Other 16-bit rows read
-    // the three dwords around their 8 bytes and shift (n = 8191 BF16 sweep 64.8 -> 48.2 us, with
-    // four 2-byte loads per lane and row before).
-    __device__ __forceinline__ Raw load(int r, int j0) const
+    // rows r .. r + B - 1 of the tile (global row i0 + r), columns j0..j0+3; columns >= n are masked
+    // by the caller, their values are unspecified (or 0 past the end of the matrix), and so are rows
+    // past the end. The loads need dword alignment only, which every FP32 and FP64 row and every
+    // 16-bit row of even length in a matrix that starts on a dword has; the range check is per dword.
+    // Other 16-bit rows read the three dwords around their 8 bytes and shift, all loads of the batch
+    // before the first shift (one branch per row instead makes every row wait for its own load).
+    // n = 8191 BF16 sweep: 64.8 us with four 2-byte loads per lane and row, 35.4 us so; 32 us at 8192.
+    // FP32 and FP64 rows from `rows` on may be left out.
+    template <int B>
+    __device__ __forceinline__ void load(int r, int j0, Raw* v, int rows = B) const
     {
-        Raw v;
+        auto at = [&](int u) { return ((r + u) * n + j0) * kBytes + odd; };
         if constexpr (DT == MDOT_DT_F64) {
-            const int off = (r * n + j0) * kBytes;
-            auto a = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
-            auto b = __builtin_amdgcn_raw_buffer_load_b128(rs, off + 16, 0, 0);
-            double2 da = *(double2*)&a, db = *(double2*)&b;
-            v.x = da.x; v.y = da.y; v.z = db.x; v.w = db.y;
+#pragma unroll
+            for (int u = 0; u < B; ++u) {
+                if (u >= rows) continue;
+                auto a = __builtin_amdgcn_raw_buffer_load_b128(rs, at(u), 0, 0);
+                auto b = __builtin_amdgcn_raw_buffer_load_b128(rs, at(u) + 16, 0, 0);
+                double2 da = *(double2*)&a, db = *(double2*)&b;
+                v[u].x = da.x; v[u].y = da.y; v[u].z = db.x; v[u].w = db.y;
+            }
         } else if constexpr (DT == MDOT_DT_F32) {
-            auto a = __builtin_amdgcn_raw_buffer_load_b128(rs, (r * n + j0) * kBytes, 0, 0);
-            v = *(float4*)&a;
+#pragma unroll
+            for (int u = 0; u < B; ++u) {
+                if (u >= rows) continue;
+                auto a = __builtin_amdgcn_raw_buffer_load_b128(rs, at(u), 0, 0);
+                v[u] = *(float4*)&a;
+            }
+        } else if (((n & 1) | odd) == 0) {
+#pragma unroll
+            for (int u = 0; u < B; ++u) {
+                auto a = __builtin_amdgcn_raw_buffer_load_b64(rs, at(u), 0, 0);
+                v[u] = *(uint2*)&a;
+            }
         } else {
-            const int off = (r * n + j0) * kBytes + odd;
-            if (((n & 1) | odd) == 0) {
-                auto a = __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0);
-                v = *(uint2*)&a;
-            } else {
-                auto a = __builtin_amdgcn_raw_buffer_load_b96(rs, off & ~3, 0, 0);
-                const uint32_t sh = (uint32_t)(off & 2) * 8;
-                v.x = __builtin_amdgcn_alignbit(a[1], a[0], sh);
-                v.y = __builtin_amdgcn_alignbit(a[2], a[1], sh);
+            uint32_t d[B][3];
+#pragma unroll
+            for (int u = 0; u < B; ++u) {
+                auto a = __builtin_amdgcn_raw_buffer_load_b96(rs, at(u) & ~3, 0, 0);
+                d[u][0] = a[0]; d[u][1] = a[1]; d[u][2] = a[2];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < B; ++u) {
+                const uint32_t sh = (uint32_t)(at(u) & 2) * 8;
+                v[u].x = __builtin_amdgcn_alignbit(d[u][1], d[u][0], sh);
+                v[u].y = __builtin_amdgcn_alignbit(d[u][2], d[u][1], sh);
             }
         }
-        return v;
     }
     // Direct-to-LDS load of row r (FP32, n % 4 == 0): lane l's 16 bytes land at lds + 16 l.
     __device__ __forceinline__ void stage(int r, int j0, void* lds) const
@@ -217,7 +235,12 @@ struct DenseCost {
             c[2] = __uint_as_float(v.y << 16); c[3] = __uint_as_float(v.y & 0xffff0000u);
         }
     }
-    __device__ __forceinline__ void row(int r, int j0, double c[4]) const { decode(load(r, j0), c); }
+    __device__ __forceinline__ void row(int r, int j0, double c[4]) const
+    {
+        Raw v;
+        load<1>(r, j0, &v);
+        decode(v, c);
+    }
     // LSE exponent arguments (log2 units) of one row for this lane's 4 columns:
     // x_k = -g2 C_ik + V_k + A, with g2 = gamma * scale * log2(e).
     __device__ __forceinline__ void bind_rows(void*, void*) {}
@@ -293,7 +316,12 @@ struct PointCost {
         }
     }
     __device__ __forceinline__ void row(int r, int, double c[4]) const { decode(xrow(r), c); }
-    __device__ __forceinline__ Raw load(int r, int) const { return r; }
+    template <int B>
+    __device__ __forceinline__ void load(int r, int, Raw* v, int = B) const
+    {
+#pragma unroll
+        for (int u = 0; u < B; ++u) v[u] = r + u;
+    }
     // LSE tile set-up: sX (and sX2 for D = 8) = kBR float4 rows of LDS; thread r < kBR stores row
     // r's coordinates and, for squared distances, folds -g2 |x_r|^2 into the row term a.
     __device__ __forceinline__ void bind_rows(void* lds, void* lds_hi)
@@ -764,9 +792,7 @@ __device__ void tile_lse(const Work& w, const SweepArgs& S, const TileCtx& t, do
     // than there are, and each row stays behind its own branch.
     constexpr bool kRowGuard = E64 || sizeof(typename Cost::Raw) > 16;
     typename Cost::Raw raw[RB];
-#pragma unroll
-    for (int r = 0; r < RB; ++r)
-        if (!kRowGuard || r < nrows) raw[r] = cost.load(rbase + r, j0);
+    cost.template load<RB>(rbase, j0, raw, kRowGuard ? nrows : RB);
     // FP32 rows with n % 4 == 0 and more tiles than stay resident at once: the second batch
     // goes straight to the wave's LDS region, so all 16 rows of the wave are in flight from the
     // start without holding registers. With a single round of workgroups (n <= ~5800) the
@@ -834,11 +860,7 @@ __device__ void tile_lse(const Work& w, const SweepArgs& S, const TileCtx& t, do
                         __builtin_amdgcn_wave_barrier();
                     }
                 }
-                if (!staged) {
-#pragma unroll
-                    for (int r = 0; r < RB; ++r)
-                        if (!kRowGuard || b + r < nrows) raw[r] = cost.load(rbase + b + r, j0);
-                }
+                if (!staged) cost.template load<RB>(rbase + b, j0, raw, kRowGuard ? nrows - b : RB);
             }
             if constexpr (RANGE) range_rows<Cost, RB>(*range, cost, raw, nrows - b, n - j0);
 #pragma unroll
@@ -887,11 +909,7 @@ __device__ void tile_lse(const Work& w, const SweepArgs& S, const TileCtx& t, do
                         __builtin_amdgcn_wave_barrier();
                     }
                 }
-                if (!staged) {
-#pragma unroll
-                    for (int r = 0; r < RB; ++r)
-                        if (!kRowGuard || b + r < nrows) raw[r] = cost.load(rbase + b + r, j0);
-                }
+                if (!staged) cost.template load<RB>(rbase + b, j0, raw, kRowGuard ? nrows - b : RB);
                 // the region no longer holds staged rows: park the previous batch's partials
                 // (the compiler barrier keeps these FP64 stores after the float4 reads above)
                 asm volatile("" ::: "memory");
@@ -999,8 +1017,7 @@ struct RoundRows {
     __device__ __forceinline__ void ask(const Cost& cost, int r, int j0)
     {
         if constexpr (!kPoints) {
-#pragma unroll
-            for (int u = 0; u < B; ++u) next[u] = cost.load(r + u, j0);
+            cost.template load<B>(r, j0, next);
         }
     }
     __device__ __forceinline__ void take(const Cost& cost, int r, int j0)
@@ -2808,8 +2825,7 @@ __device__ __forceinline__ void steps_sweep(StepsShared<NQ * TP>& sh, StepsX* x,
 #pragma unroll
                 for (int b0 = 0; b0 < kRPW; b0 += K::RB) {
                     if constexpr (!K::kHold) {
-#pragma unroll
-                        for (int r = 0; r < K::RB; ++r) raw[0][r] = c.load(t[u].rbase + b0 + r, t[u].J * kBC + me.lane * 4);
+                        c.template load<K::RB>(t[u].rbase + b0, t[u].J * kBC + me.lane * 4, raw[0]);
                     }
 #pragma unroll
                     for (int r0 = 0; r0 < K::RB; ++r0) {
@@ -2840,8 +2856,7 @@ __device__ __forceinline__ void steps_sweep(StepsShared<NQ * TP>& sh, StepsX* x,
 #pragma unroll
                 for (int b0 = 0; b0 < kRPW; b0 += K::RB) {
                     if constexpr (!K::kHold) {
-#pragma unroll
-                        for (int r = 0; r < K::RB; ++r) raw[0][r] = c.load(t[u].rbase + b0 + r, t[u].J * kBC + me.lane * 4);
+                        c.template load<K::RB>(t[u].rbase + b0, t[u].J * kBC + me.lane * 4, raw[0]);
                     }
 #pragma unroll
                     for (int r0 = 0; r0 < K::RB; ++r0) {
@@ -2938,8 +2953,7 @@ __global__ void __launch_bounds__(256 * NQ) k_steps(const Work* __restrict__ wp,
         if (me.t < kBR) sh.rxx[t[u].at][me.t] = c.row_fixed(me.t, t[u].i0 + me.t);
         c.cols_fixed(g2);
         if constexpr (K::kHold) {
-#pragma unroll
-            for (int r = 0; r < K::RB; ++r) raw[u][r] = c.load(t[u].rbase + r, j0);
+            c.template load<K::RB>(t[u].rbase, j0, raw[u]);
         }
         lzt_r[u] = lzt_c[u] = 0.0;
         steps_load(w, a0, sh, t[u]);
@@ -3156,8 +3170,7 @@ __global__ void __launch_bounds__(256 * NQ) k_lse(LseArgs A, StepsX* __restrict_
         c.bind_rows(sh.x[t[u].at], sh.x[t[u].at] + 2 * kBR);
         if (me.t < kBR) sh.rxx[t[u].at][me.t] = c.row_fixed(me.t, t[u].i0 + me.t);
         if constexpr (K::kHold) {
-#pragma unroll
-            for (int r = 0; r < K::RB; ++r) raw[u][r] = c.load(t[u].rbase + r, j0);
+            c.template load<K::RB>(t[u].rbase, j0, raw[u]);
         }
         if (t[u].has_col(me)) sh.cz[t[u].at][me.t] = A.in.v[t[u].J * kBC + me.t];
         if (t[u].has_row(me)) sh.rz[t[u].at][me.t] = A.in.u[t[u].i0 + me.t];
@@ -3594,8 +3607,7 @@ k_row_max(const Work* __restrict__ wp, double* __restrict__ part)
 #pragma unroll
         for (int b = 0; b < kRPW; b += RB) {
             typename Cost::Raw raw[RB];
-#pragma unroll
-            for (int r = 0; r < RB; ++r) raw[r] = cost.load(rbase + b + r, j0);
+            cost.template load<RB>(rbase + b, j0, raw);
 #pragma unroll
             for (int r = 0; r < RB; ++r)
                 if (b + r < nrows) {
