@@ -37,9 +37,12 @@ constexpr int kResidentRuns = 3;      // mode, where stages follow each other, s
 constexpr int kResidentSingles = 2;   // single steps (an even number: Round's two sweeps)
 constexpr int kResidentMax = 4096;    // steps of one resident launch (tens of milliseconds)
 constexpr int kBatchChunk = 16;  // engine steps per graph launch (admission granularity, even)
+// Where all solves in flight take resident steps, a chunk is at most this many of them (the solves
+// wait for the slowest) and the single steps: about as long as kBatchChunk steps of three kernels.
+constexpr int kBatchResident = 30;
 constexpr int kMaxN = MDOT_MAX_N;
 constexpr int kConvBlocks = 1024; // workgroups of the FP16 conversion (MIXED)
-constexpr int kDoneInts = 2 * kMaxBatch + 2;  // done flags in mapped host memory
+constexpr int kDoneInts = 4 * kMaxBatch + 2;  // done flags and step counts in mapped host memory
 static_assert(kDoneInts % 2 == 0, "the AloneOut behind the flags is aligned to 8 bytes");
 
 // Device buffers of one problem: workspace, device copy of Work + 2 state slots, parameters.
@@ -83,6 +86,8 @@ struct Slot {
     const double* r = nullptr;
     const double* c = nullptr;
     int64_t resumed_at = -1;  // engine chunks up to this sequence number ran the paused state
+    bool resident = false;    // resident steps know its variant
+    int steps = 0;            // solver steps taken, by the chunks read back
 };
 
 }  // namespace
@@ -128,6 +133,7 @@ struct mdot_ctx {
     // inside them has ever run out
     int cus = 0;
     StepsX* d_steps = nullptr;
+    StepsX* d_bsteps = nullptr;  // the same for the engine, one per item, from its first resident chunk on
     bool steps_off = false;
     // serving engine
     hipStream_t side = nullptr;     // intake of admitted solves (does not wait for the chunk in flight)
@@ -146,10 +152,11 @@ struct mdot_ctx {
     // replaced batch graphs, destroyed once the last chunk launched from them has been read back
     std::vector<std::pair<hipGraphExec_t, int64_t>> graveyard;
     // what the batch graph was captured with: its sweep instances and their tile ranges, the
-    // finalize grid and finalize instance
+    // finalize grid and finalize instance, the resident steps' instance and grid
     int bgraph_ncodes = 0, bgraph_code[kMaxCodes] = {}, bgraph_begin[kMaxCodes + 1] = {};
     int bgraph_fin = -1;
     int bgraph_fin_v = -1;
+    int bgraph_steps_nt = 0, bgraph_steps_code = 0, bgraph_steps_blocks = 0;
     int batch_fin_v = kFinSmall;  // the finalize instance the batch needs (fin_instance)
     // engine chunks in flight: the next chunk is launched before the previous one's done flags
     // are read; each remembers the slots and tickets it advanced, in descriptor order
@@ -159,6 +166,7 @@ struct mdot_ctx {
     int64_t eng_seq = 0;              // engine chunks launched so far
     int64_t chunk_seq[2] = {0, 0};    // sequence number of the chunk in each buffer
     int chunk_m[2] = {0, 0};
+    bool chunk_resident[2] = {false, false};
     int chunk_slot[2][kMaxBatch];
     uint64_t chunk_ticket[2][kMaxBatch];
     uint64_t next_ticket = 1;
@@ -613,7 +621,8 @@ static void fill_result(const State& S, double seconds, mdot_result* res)
 static int steps_mode(const mdot_ctx* ctx, const mdot_params& prm)
 {
     if (ctx->steps_off || prm.projector || prm.precond) return 0;
-    const int nt = steps_tiles(ctx->main.host_work, ctx->cus);
+    const Work* hw = &ctx->main.host_work;
+    const int nt = steps_tiles(&hw, 1, ctx->cus);
     return nt ? nt + (prm.gamma_f > 0.0 ? 8 : 0) : 0;
 }
 
@@ -715,6 +724,7 @@ static int rebuild_batch(mdot_ctx* ctx)
     BatchDesc& B = *ctx->h_batch[hbuf];
     memset(&B, 0, sizeof B);
     int nf = 0, m = 0;
+    bool resident = !ctx->steps_off;
     const Work* hw[kMaxBatch];
     for (int s = 0; s < kMaxBatch; ++s) {  // items in slot order (the done flags follow it)
         const Slot& sl = ctx->slots[s];
@@ -723,6 +733,7 @@ static int rebuild_batch(mdot_ctx* ctx)
         B.items[m] = sl.pb.d_work;
         B.fin_prefix[m] = nf;
         nf += sl.pb.host_work.fin_nblk;
+        resident &= sl.resident;
         ++m;
     }
     B.nitems = m;
@@ -784,6 +795,20 @@ static int rebuild_batch(mdot_ctx* ctx)
     B.ngroups = ng;
     B.grp_prefix[ng] = nt;
     B.total_tiles = nt;
+    if (resident && m > 0) B.steps_nt = steps_tiles(hw, m, ctx->cus);
+    if (B.steps_nt && !ctx->d_bsteps) {
+        if (hipMalloc(&ctx->d_bsteps, kMaxBatch * sizeof(StepsX)) == hipSuccess) {
+            HIPCHK(ctx, hipMemsetAsync(ctx->d_bsteps, 0, kMaxBatch * sizeof(StepsX), ctx->stream));
+        } else {
+            (void)hipGetLastError();
+            ctx->d_bsteps = nullptr;
+            B.steps_nt = 0;
+        }
+    }
+    if (B.steps_nt) {
+        B.steps_code = base_code_of(*hw[0]);
+        for (int a = 0; a < m; ++a) B.steps_prefix[a + 1] = B.steps_prefix[a] + steps_blocks(*hw[a], B.steps_nt);
+    }
     // stream order puts the upload behind the chunk in flight, which still reads the old one
     HIPCHK(ctx, hipMemcpyAsync(ctx->d_batch, &B, sizeof B, hipMemcpyHostToDevice, ctx->stream));
     HIPCHK(ctx, hipEventRecord(ctx->batch_ev[hbuf], ctx->stream));
@@ -801,7 +826,9 @@ static int ensure_batch_graph(mdot_ctx* ctx)
     const BatchDesc& hb = *ctx->h_batch[ctx->hb_cur];
     const int fin = std::max(1, hb.total_fin);
     const int fin_v = ctx->batch_fin_v;
-    bool same = ctx->bgraph && ctx->bgraph_ncodes == hb.ncodes && ctx->bgraph_fin == fin && ctx->bgraph_fin_v == fin_v;
+    bool same = ctx->bgraph && ctx->bgraph_ncodes == hb.ncodes && ctx->bgraph_fin == fin && ctx->bgraph_fin_v == fin_v &&
+                ctx->bgraph_steps_nt == hb.steps_nt && ctx->bgraph_steps_blocks == hb.steps_prefix[hb.nitems] &&
+                ctx->bgraph_steps_code == hb.steps_code;
     for (int c = 0; same && c < hb.ncodes; ++c)
         same = ctx->bgraph_code[c] == hb.code[c] && ctx->bgraph_begin[c + 1] == hb.code_begin[c + 1];
     if (same) return MDOT_OK;
@@ -812,12 +839,17 @@ static int ensure_batch_graph(mdot_ctx* ctx)
     hipStream_t cap;
     HIPCHK(ctx, hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
     hipGraph_t g = nullptr;
+    int bad = 0;
     hipError_t e = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
-        for (int k = 0; k < kBatchChunk; ++k) launch_step_batch(hb, ctx->d_batch, k & 1, fin, fin_v, cap);
+        // resident: as many steps as a stage allows, then Round's two sweeps where its end has come
+        if (hb.steps_nt) bad |= launch_steps_batch(hb, ctx->d_batch, ctx->d_bsteps, kBatchResident, cap);
+        for (int k = 0; k < (hb.steps_nt ? kResidentSingles : kBatchChunk); ++k)
+            bad |= launch_step_batch(hb, ctx->d_batch, k & 1, fin, fin_v, cap);
         launch_gather_done(ctx->d_batch, ctx->d_hdone + 2, ctx->d_seq + 1, cap);
         e = hipStreamEndCapture(cap, &g);
     }
+    if (e == hipSuccess && bad) e = hipErrorLaunchFailure;
     if (e == hipSuccess) e = hipGraphInstantiate(&ctx->bgraph, g, nullptr, nullptr, 0);
     if (g) (void)hipGraphDestroy(g);
     (void)hipStreamDestroy(cap);
@@ -832,6 +864,9 @@ static int ensure_batch_graph(mdot_ctx* ctx)
     }
     ctx->bgraph_fin = fin;
     ctx->bgraph_fin_v = fin_v;
+    ctx->bgraph_steps_nt = hb.steps_nt;
+    ctx->bgraph_steps_code = hb.steps_code;
+    ctx->bgraph_steps_blocks = hb.steps_prefix[hb.nitems];
     return MDOT_OK;
 }
 
@@ -883,6 +918,10 @@ static int collect_retired(mdot_ctx* ctx, bool wait, int* collected)
         if (e != hipSuccess) return fail(ctx, MDOT_E_DEVICE, "retirement event failed: %s", hipGetErrorString(e));
         mdot_result res;
         fill_result(ctx->h_states[rt.hs], 0.0, &res);
+        if (ctx->h_states[rt.hs].status == MDOT_E_DEVICE) {  // a wait between resident workgroups ran out
+            ctx->steps_off = true;
+            ctx->batch_dirty = true;
+        }
         ctx->finished[rt.ticket] = res;
         ctx->bytes_in_use -= bufs_bytes(rt.pb);
         pool_put(ctx, rt.pb);
@@ -1036,6 +1075,7 @@ int mdot_ctx_destroy(mdot_ctx* ctx)
         if (e) (void)hipEventDestroy(e);
     if (ctx->d_batch) (void)hipFree(ctx->d_batch);
     if (ctx->d_steps) (void)hipFree(ctx->d_steps);
+    if (ctx->d_bsteps) (void)hipFree(ctx->d_bsteps);
     for (auto& e : ctx->ev)
         if (e) (void)hipEventDestroy(e);
     for (auto& e : ctx->eng_ev)
@@ -1149,7 +1189,8 @@ static int run_alone(mdot_ctx* ctx, ProblemBufs& pb, const mdot_cost_desc* cost,
     hipStream_t st = ctx->stream;
     AloneOut* dout = reinterpret_cast<AloneOut*>(ctx->d_hdone + kDoneInts);
     volatile AloneOut* hout = reinterpret_cast<volatile AloneOut*>(ctx->h_done + kDoneInts);
-    const int nt = (round || !lr_out || ctx->steps_off) ? 0 : steps_tiles(w, ctx->cus);
+    const Work* hw = &w;
+    const int nt = (round || !lr_out || ctx->steps_off) ? 0 : steps_tiles(&hw, 1, ctx->cus);
     if (lse_resident(nt)) {
         LseArgs A;
         A.w = w;
@@ -1473,6 +1514,8 @@ int mdot_submit(mdot_ctx* ctx, const mdot_cost_desc* cost, const double* r, cons
     sl.r = r;
     sl.c = c;
     sl.resumed_at = -1;
+    sl.resident = !prm.projector && !prm.precond;
+    sl.steps = 0;
     ctx->bytes_in_use += sl.footprint;
     ctx->batch_dirty = true;
     *ticket = sl.ticket;
@@ -1480,15 +1523,21 @@ int mdot_submit(mdot_ctx* ctx, const mdot_cost_desc* cost, const double* r, cons
 }
 
 // Read back an engine chunk: retire the solves it finished (their slots may already hold newer
-// solves, admitted after the chunk was launched: those are told apart by the ticket).
-static int process_chunk(mdot_ctx* ctx, int buf)
+// solves, admitted after the chunk was launched: those are told apart by the ticket). *least: the
+// fewest steps a solve still running has taken in it.
+static int process_chunk(mdot_ctx* ctx, int buf, int* least)
 {
     HIPCHK(ctx, hipEventSynchronize(ctx->eng_ev[buf]));
     bury_graphs(ctx, ctx->chunk_seq[buf]);
     const int* done = ctx->h_done + 2 + buf * kMaxBatch;
+    const int* steps = done + 2 * kMaxBatch;
+    *least = kBatchChunk;
     for (int m = 0; m < ctx->chunk_m[buf]; ++m) {
         Slot& sl = ctx->slots[ctx->chunk_slot[buf][m]];
-        if (!done[m] || !sl.used || sl.ticket != ctx->chunk_ticket[buf][m]) continue;
+        if (!sl.used || sl.ticket != ctx->chunk_ticket[buf][m]) continue;
+        if (!done[m]) *least = std::min(*least, steps[m] - sl.steps);
+        sl.steps = steps[m];
+        if (!done[m]) continue;
         if (done[m] == 2) {  // MIXED: paused at the switch to the exact cost
             // the chunk launched before the resume below still reports the pause: skip it
             if (ctx->chunk_seq[buf] <= sl.resumed_at) continue;
@@ -1518,7 +1567,9 @@ int mdot_run(mdot_ctx* ctx, int steps, int* n_done)
     int rc = collect_retired(ctx, false, &completed);
     if (rc) return rc;
     const int chunks = std::max(1, (steps + kBatchChunk - 1) / kBatchChunk);
-    for (int ch = 0; ch < chunks; ++ch) {
+    // a resident chunk is short of its steps where a stage ends early: more chunks make up for it
+    int owed = 0, least = 0;
+    for (int ch = 0; ch < chunks || owed > 0; ++ch) {
         int active = 0;
         for (const Slot& sl : ctx->slots) active += sl.used;
         if (active == 0 && ctx->eng_pending < 0) break;
@@ -1538,19 +1589,21 @@ int mdot_run(mdot_ctx* ctx, int steps, int* n_done)
                 ++m;
             }
             ctx->chunk_m[buf] = m;
+            ctx->chunk_resident[buf] = ctx->bgraph_steps_nt != 0;
             ctx->chunk_seq[buf] = ++ctx->eng_seq;
             // the graph's last kernel writes this chunk's done flags to host buffer `buf` (engine
             // chunks alternate buffers in launch order, as the device counter does)
             HIPCHK(ctx, hipGraphLaunch(ctx->bgraph, ctx->stream));
             HIPCHK(ctx, hipEventRecord(ctx->eng_ev[buf], ctx->stream));
             if (ctx->eng_pending >= 0) {
-                rc = process_chunk(ctx, ctx->eng_pending);
+                rc = process_chunk(ctx, ctx->eng_pending, &least);
                 if (rc) return rc;
+                if (ctx->chunk_resident[ctx->eng_pending]) owed += kBatchChunk - least;
             }
             ctx->eng_pending = buf;
             ctx->eng_next = buf ^ 1;
         } else {  // nothing left to advance: read the last chunk back
-            rc = process_chunk(ctx, ctx->eng_pending);
+            rc = process_chunk(ctx, ctx->eng_pending, &least);
             if (rc) return rc;
             ctx->eng_pending = -1;
         }

@@ -257,6 +257,10 @@ struct BatchDesc {
     int32_t ncodes;
     int32_t code[kMaxCodes];
     int32_t code_begin[kMaxCodes + 1];
+    // Resident steps of all items in one kernel: tiles per workgroup (0: not all of them fit), their
+    // cost type, and the workgroups of item b: [steps_prefix[b], steps_prefix[b + 1]).
+    int32_t steps_nt, steps_code;
+    int32_t steps_prefix[kMaxBatch + 1];
 };
 
 // Workspace layout of one problem (the vectors of Work, in the order bind_work assigns them):
@@ -313,11 +317,14 @@ int launch_init(const Work* wd, void* stream);                               // 
 int launch_intake(const Work* wd, double* out8, void* stream);
 // Range partials of every tile; box: skipped where the cloud's boxes (in the dots array) settle it.
 int launch_cost_range(const Work& hw, const Work* wd, double* part, int box, void* stream);
-// Resident steps: tiles per workgroup (0: not for this problem), and the launch, which runs LSE
-// steps from state slot 0 until something else is due.
-int steps_tiles(const Work& hw, int cus);
+// Resident steps: tiles per workgroup of one launch for these problems (0: not for them), and the
+// launch, which runs LSE steps from state slot 0 until something else is due.
+int steps_tiles(const Work* const* hw, int count, int cus);
 int launch_settle(const Work* wd, void* stream);  // the decision it may have left open
 int launch_steps(const Work& hw, const Work* wd, StepsX* x, int nt, int max_steps, void* stream);
+int steps_blocks(const Work& hw, int nt);  // workgroups of such a launch
+// The same for the problems of a batch (x: one StepsX per item), with the decisions left open.
+int launch_steps_batch(const BatchDesc& hb, const BatchDesc* bd, StepsX* x, int max_steps, void* stream);
 // Arguments of the resident standalone LSE (k_lse).
 struct LseArgs {
     Work w;
@@ -347,6 +354,7 @@ int launch_to_f16(const void* src, int src_dtype, void* dst, size_t count, doubl
 // Batched step over a BatchDesc in device memory: one sweep launch per kernel instance of the
 // host copy hb (instance hb.code[c] over its tile range), then fin_grid = total_fin finalize
 // workgroups and the decisions.
+int base_code_of(const Work& hw);  // cost_code without the occupancy variant
 int cost_code_of(int cost_kind, int dtype);
 // The instance of a point cost code for dimension d (planar for d <= 2, the general one for
 // d = 3, the 8-coordinate one for 4 <= d <= 8); other codes are returned unchanged.
@@ -357,7 +365,8 @@ int cost_code(const Work& hw);
 // fin_v: the finalize instance (fin_instance) the largest problem in flight needs
 int launch_step_batch(const BatchDesc& hb, const BatchDesc* bd, int parity, int fin_grid, int fin_v, void* stream);
 // End-of-chunk done flags into host-visible memory: chunk number *seq (a device counter, advanced
-// here) writes out[(seq & 1) * kMaxBatch + item] (batch) or out[seq & 1] (single problem).
+// here) writes out[(seq & 1) * kMaxBatch + item] (batch, and the steps the solve has taken so far
+// 2 kMaxBatch entries behind) or out[seq & 1] (single problem).
 int launch_gather_done(const BatchDesc* bd, int* out, int* seq, void* stream);
 int launch_chunk_done(const Work* wd, int* out, int* seq, void* stream);
 

@@ -2163,7 +2163,7 @@ __global__ void __launch_bounds__(kDecideWG) k_settle(const Work* __restrict__ w
 //
 // Every workgroup holds up to four tiles (a quad of four waves takes one or two: n = 4096 is 256
 // workgroups of two quads, one per compute unit) with their rows' and columns' vector entries in
-// LDS, and does the work of finalize block blockIdx.x if there is one. Arithmetic and orders are those of
+// LDS, and does the work of the finalize block of its own number if there is one. Arithmetic and orders are those of
 // k_sweep, k_fin and k_decide, so the results are the same bits. Per step:
 //   1. sweep: tile partials and row-tile shifts are stored for the finalize blocks;
 //   2. the finalize blocks fold them and store log-sums and dots;
@@ -2356,13 +2356,13 @@ struct Lane {
 struct StepTile {
     int m, n, at, I, J, i0, rbase, nrows;
     bool has;
-    __device__ __forceinline__ void set(const Work& w, int nt, int at_)
+    __device__ __forceinline__ void set(const Work& w, int blk, int nt, int at_)
     {
         const Lane me;
         m = w.m;
         n = w.n;
         at = at_;
-        const int tile = blockIdx.x * nt + at;
+        const int tile = blk * nt + at;
         has = tile < w.nrt * w.nct;
         I = has ? tile / w.nct : 0;
         J = has ? tile % w.nct : 0;
@@ -2377,11 +2377,12 @@ struct StepTile {
     __device__ __forceinline__ bool has_shift(const Lane& me) const { return has && J == 0 && me.t == 0; }
 };
 
-// The sizes the steps need, in scalar registers throughout.
+// The sizes the steps need, in scalar registers throughout, and which of the problem's workgroups
+// this is.
 struct StepSize {
-    int m, n, nrt, nct, nvb, nvbr, Lr, L, lgLr, lgL;
-    __device__ __forceinline__ explicit StepSize(const Work& w)
-        : m(w.m), n(w.n), nrt(w.nrt), nct(w.nct), nvb(w.fin_nvb), nvbr(w.fin_nvbr), Lr(w.fin_Lr), L(w.fin_L), lgLr(w.fin_lgLr),
+    int blk, nblk, m, n, nrt, nct, nvb, nvbr, Lr, L, lgLr, lgL;
+    __device__ __forceinline__ StepSize(const Work& w, int blk_, int nblk_)
+        : blk(blk_), nblk(nblk_), m(w.m), n(w.n), nrt(w.nrt), nct(w.nct), nvb(w.fin_nvb), nvbr(w.fin_nvbr), Lr(w.fin_Lr), L(w.fin_L), lgLr(w.fin_lgLr),
           lgL(w.fin_lgL) {}
 };
 
@@ -2407,14 +2408,14 @@ __device__ __forceinline__ double* col_slot(const StepsShared<NT>& sh, const Ste
     return sh.colp[b] + (size_t)t.I * t.n + t.J * kBC + me.t;
 }
 
-// A thread's entry of finalize block blockIdx.x (the first quad of the first fin_nvb workgroups),
+// A thread's entry of its workgroup's finalize block (the first quad of the first fin_nvb workgroups),
 // as in fin_body.
 struct FinEntry {
     bool row, valid, own;
     int L, l, k, np;       // lanes and lane of the group, row or column, its partials
     __device__ __forceinline__ FinEntry(const StepSize& z, const Lane& me)
     {
-        const int vb = blockIdx.x;
+        const int vb = z.blk;
         row = vb < z.nvbr;
         L = row ? z.Lr : z.L;
         l = me.t & (L - 1);
@@ -2441,7 +2442,7 @@ __device__ __forceinline__ void clear_fin(const StepsShared<NT>& sh, const StepS
     const Lane me;
     const FinEntry f(z, me);
     if (f.own) xstore((f.row ? sh.logr[b] : sh.logc[b]) + f.k, empty_slot());
-    if (me.q == 0 && me.t <= kStepDots) xstore(&x->dots[b][blockIdx.x][me.t], empty_slot());
+    if (me.q == 0 && me.t <= kStepDots) xstore(&x->dots[b][z.blk][me.t], empty_slot());
 }
 
 // Entry k with the pending update of the last step (or stage) taken. The trial log-sums are read as
@@ -2505,11 +2506,11 @@ __device__ __forceinline__ void steps_load_fin(const Work& w, const StepSize& z,
 }
 
 // Wait until every workgroup has announced itself; false if one of them does not get to run.
-__device__ __forceinline__ bool steps_wait_all(StepsX* x)
+__device__ __forceinline__ bool steps_wait_all(const StepSize& z, StepsX* x)
 {
     uint32_t seen = xload(&x->arrive);
     const uint64_t t0 = wall_clock64();
-    while (!(seen & kStepsAbort) && seen != gridDim.x) {
+    while (!(seen & kStepsAbort) && seen != (uint32_t)z.nblk) {
         if (wall_clock64() - t0 > kStartTicks)  // give up, unless the last one has just come
             __hip_atomic_compare_exchange_strong(&x->arrive, &seen, seen | kStepsAbort, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                  __HIP_MEMORY_SCOPE_AGENT);
@@ -2517,16 +2518,16 @@ __device__ __forceinline__ bool steps_wait_all(StepsX* x)
     }
     return !(seen & kStepsAbort);
 }
-__device__ __forceinline__ bool steps_meet(StepsX* x)
+__device__ __forceinline__ bool steps_meet(const StepSize& z, StepsX* x)
 {
     __hip_atomic_fetch_add(&x->arrive, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return steps_wait_all(x);
+    return steps_wait_all(z, x);
 }
 // The last workgroup to end clears both counts for the next kernel.
-__device__ __forceinline__ void steps_leave(StepsX* x)
+__device__ __forceinline__ void steps_leave(const StepSize& z, StepsX* x)
 {
     if (threadIdx.x == 0 &&
-        __hip_atomic_fetch_add(&x->leave, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == gridDim.x) {
+        __hip_atomic_fetch_add(&x->leave, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == (uint32_t)z.nblk) {
         xstore(&x->leave, 0u);
         xstore(&x->arrive, 0u);
     }
@@ -2674,7 +2675,7 @@ __device__ __forceinline__ void steps_finalize(const StepSize& z, StepsX* x, Ste
     __syncthreads();
     const Lane me;
     if (me.q == 0 && me.t <= kStepDots)
-        xstore(&x->dots[b][blockIdx.x][me.t], (sh.red[me.t * 4 + 0] + sh.red[me.t * 4 + 1]) + (sh.red[me.t * 4 + 2] + sh.red[me.t * 4 + 3]));
+        xstore(&x->dots[b][z.blk][me.t], (sh.red[me.t * 4 + 0] + sh.red[me.t * 4 + 1]) + (sh.red[me.t * 4 + 2] + sh.red[me.t * 4 + 3]));
 }
 
 // All dots, 64 blocks per wave of the first quad: ask() starts the loads, take() waits and leaves
@@ -2910,21 +2911,47 @@ __device__ __forceinline__ void steps_sweep(StepsShared<NQ * TP>& sh, StepsX* x,
     }
 }
 
-// NQ quads of TP tiles each.
+// The item a workgroup of a batched launch belongs to: the largest b with prefix[b] <= g.
+__device__ __forceinline__ int batch_item(const int32_t* prefix, int nitems, int g)
+{
+    int lo = 0, hi = nitems - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (prefix[mid] <= g) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
+// NQ quads of TP tiles each, for one problem (wp), or for the problems in flight (bd): each has its
+// own workgroups and its own exchange memory, and they go on independently of each other.
 template <int CC, int NQ, int TP>
-__global__ void __launch_bounds__(256 * NQ) k_steps(const Work* __restrict__ wp, StepsX* __restrict__ x, int max_steps)
+__global__ void __launch_bounds__(256 * NQ) k_steps(const Work* __restrict__ wp, const BatchDesc* __restrict__ bd,
+                                                    StepsX* __restrict__ x, int max_steps)
 {
     using Cost = typename CostOf<CC>::T;
     using K = StepKind<Cost, TP>;
     __shared__ StepsShared<NQ * TP> sh;
 
-    if (!steps_go(*state_slot(*wp, 0))) return;  // the same in every workgroup
+    int blk = blockIdx.x, nblk = gridDim.x;
+    if (bd) {
+        const int item = batch_item(bd->steps_prefix, bd->nitems, blk), first = bd->steps_prefix[item];
+        nblk = bd->steps_prefix[item + 1] - first;
+        blk -= first;
+        wp = bd->items[item];
+        x += item;
+    }
+    State* const S0 = state_slot(*wp, 0);
+    if (!steps_go(*S0)) return;  // the same in every workgroup
 
-    const Work& w = *wp;
-    const StepSize z(w);
-    State* const S0 = state_slot(w, 0);
+    // Work never changes while a kernel runs. Said so, its fields are read as scalars, which the
+    // compiler otherwise gives up for a pointer that comes out of memory (+40 registers).
+    uint64_t wa = reinterpret_cast<uint64_t>(wp);
+    asm volatile("" : "+s"(wa));
+    const Work& w = *(const Work*)(const __attribute__((address_space(4))) Work*)wa;
+    const StepSize z(w, blk, nblk);
     const SweepArgs a0 = args_of(S0);  // the pending update
-    const bool fin_wg = (int)blockIdx.x < z.nvb;
+    const bool fin_wg = z.blk < z.nvb;
     const double g2 = S0->gamma * w.scale * LOG2E_D;
     if (threadIdx.x == 0) {
         Trial::copy(sh.T, *S0);
@@ -2938,7 +2965,7 @@ __global__ void __launch_bounds__(256 * NQ) k_steps(const Work* __restrict__ wp,
     {
         const Lane me;
 #pragma unroll
-        for (int u = 0; u < TP; ++u) t[u].set(w, NQ * TP, me.q * TP + u);
+        for (int u = 0; u < TP; ++u) t[u].set(w, z.blk, NQ * TP, me.q * TP + u);
     }
     TileCosts<Cost, TP> cost = tile_costs<Cost, TP>(w, t);
     typename Cost::Raw raw[K::kTiles][K::RB];
@@ -2964,7 +2991,7 @@ __global__ void __launch_bounds__(256 * NQ) k_steps(const Work* __restrict__ wp,
 
     wave_drain();
     __syncthreads();
-    if (threadIdx.x == 0) sh.go = steps_meet(x);
+    if (threadIdx.x == 0) sh.go = steps_meet(z, x);
     __syncthreads();
     const bool started = sh.go != 0;
     if (started && fin_wg) steps_load_fin(w, z, a0, sh);
@@ -3027,12 +3054,12 @@ __global__ void __launch_bounds__(256 * NQ) k_steps(const Work* __restrict__ wp,
                 if (last != 2) xstore(w.lzt + k, sh.fl[me.t]);
             }
         }
-        if (blockIdx.x == 0 && me.q == 0 && sh.go < 0 && me.t < z.nvb) {  // the dots of the decision left open
+        if (z.blk == 0 && me.q == 0 && sh.go < 0 && me.t < z.nvb) {  // the dots of the decision left open
             double* bd = bdots_of(*wp) + (size_t)me.t * kNDot;
 #pragma unroll
             for (int d = 0; d < kNDot; ++d) bd[d] = d <= kStepDots ? sh.y[d][me.t] : 0.0;
         }
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
+        if (z.blk == 0 && threadIdx.x == 0) {
             Trial::copy(*S0, sh.T);
             S0->undecided = sh.go < 0;
             if (sh.dead) {
@@ -3041,7 +3068,7 @@ __global__ void __launch_bounds__(256 * NQ) k_steps(const Work* __restrict__ wp,
             }
         }
     }
-    steps_leave(x);
+    steps_leave(z, x);
 }
 
 // ------------------------------------------------------------------ resident standalone LSE
@@ -3129,8 +3156,8 @@ __global__ void __launch_bounds__(256 * NQ) k_lse(LseArgs A, StepsX* __restrict_
     __shared__ StepsShared<NQ * TP> sh;
 
     const Work& w = A.w;
-    const StepSize z(w);
-    const bool fin_wg = (int)blockIdx.x < z.nvb;
+    const StepSize z(w, blockIdx.x, gridDim.x);
+    const bool fin_wg = z.blk < z.nvb;
     if (threadIdx.x == 0) {
         sh.T = Trial{};
         sh.T.ls_phase = LS_STANDALONE;
@@ -3142,7 +3169,7 @@ __global__ void __launch_bounds__(256 * NQ) k_lse(LseArgs A, StepsX* __restrict_
     {
         const Lane me;
 #pragma unroll
-        for (int u = 0; u < TP; ++u) t[u].set(w, NQ * TP, me.q * TP + u);
+        for (int u = 0; u < TP; ++u) t[u].set(w, z.blk, NQ * TP, me.q * TP + u);
     }
     // ---- empty the slots, announce this workgroup, load
     const int ntiles = z.nrt * z.nct;
@@ -3180,7 +3207,7 @@ __global__ void __launch_bounds__(256 * NQ) k_lse(LseArgs A, StepsX* __restrict_
         const FinEntry f(z, me);
         if (f.own) sh.fp[me.t] = sh.flz[me.t] = sh.flt[me.t] = sh.frt[me.t] = sh.fg[me.t] = 0.0;
     }
-    if (threadIdx.x == 0) sh.go = steps_wait_all(x);
+    if (threadIdx.x == 0) sh.go = steps_wait_all(z, x);
     __syncthreads();
     const bool started = sh.go != 0;
     Wait wait(x);
@@ -3317,7 +3344,7 @@ __global__ void __launch_bounds__(256 * NQ) k_lse(LseArgs A, StepsX* __restrict_
             e64 = true;
         }
         // ---- outputs, if every entry of the scaled cost lies in [0, 1]
-        if (fin_wg || blockIdx.x == 0) {
+        if (fin_wg || z.blk == 0) {
             double lo, hi;
             lse_range(x, sh, ntiles, NQ, wait, &lo, &hi);
             const bool dead = __syncthreads_or(wait.dead), valid = range_valid(scale, lo, hi);
@@ -3327,7 +3354,7 @@ __global__ void __launch_bounds__(256 * NQ) k_lse(LseArgs A, StepsX* __restrict_
                 if (f.own) (f.row ? A.lr_out : A.lc_out)[f.k] = sh.fl[me.t];
             }
             if (dead && threadIdx.x == 0) A.out->retry = 1;
-            if (blockIdx.x == 0 && threadIdx.x == 0 && !dead) {
+            if (z.blk == 0 && threadIdx.x == 0 && !dead) {
                 A.out->valid = valid;
                 A.out->status = any ? MDOT_W_RANGE : MDOT_OK;
                 A.out->scale = scale;
@@ -3335,21 +3362,10 @@ __global__ void __launch_bounds__(256 * NQ) k_lse(LseArgs A, StepsX* __restrict_
             }
         }
     }
-    steps_leave(x);
+    steps_leave(z, x);
 }
 
 // ------------------------------------------------------------------ batched kernels
-__device__ __forceinline__ int batch_item(const int32_t* prefix, int nitems, int g)
-{
-    int lo = 0, hi = nitems - 1;  // largest b with prefix[b] <= g
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (prefix[mid] <= g) lo = mid;
-        else hi = mid - 1;
-    }
-    return lo;
-}
-
 // Batched sweep: one workgroup per tile of the problems in flight that need this kernel
 // instance (the descriptor's tiles [tile_begin, tile_end), launched exactly), tiles of problems
 // that share a cost interleaved so that they meet in one XCD's L2 (ranges start at multiples of
@@ -3387,7 +3403,22 @@ __global__ void __launch_bounds__(kDecideWG) k_decide_batch(const BatchDesc* __r
     for (int b = blockIdx.x; b < bd->nitems; b += gridDim.x) decide_body(*bd->items[b], parity, parity ^ 1);
 }
 
-// End-of-chunk done flags, written straight into pinned host memory (a stream-ordered copy
+// k_settle of every item. A wait that ran out (StepsX::abort) ends its solve with an error.
+__global__ void __launch_bounds__(kDecideWG) k_settle_batch(const BatchDesc* __restrict__ bd, StepsX* __restrict__ x)
+{
+    const int b = blockIdx.x;
+    if (b >= bd->nitems) return;
+    State* S = state_slot(*bd->items[b], 0);
+    const bool dead = x[b].abort != 0;
+    if (!dead && S->undecided) decide_body(*bd->items[b], 0, 0);
+    if (dead && threadIdx.x == 0) {
+        x[b].abort = 0;
+        S->done = 1;
+        S->status = MDOT_E_DEVICE;
+    }
+}
+
+// End-of-chunk done flags and step counts, written straight into pinned host memory (a stream-ordered copy
 // between chunks would stall the stream for tens of microseconds). The chunk counter *seq,
 // kept on the device, picks the host buffer: chunk s writes buffer s & 1, so the chunk queued
 // behind it never overwrites flags the host has not read yet.
@@ -3395,7 +3426,11 @@ __global__ void k_gather_done(const BatchDesc* __restrict__ bd, int* out, int* s
 {
     const int b = threadIdx.x;  // one wave: every lane reads the counter before lane 0 advances it
     const int s = *seq;
-    if (b < bd->nitems) out[(s & 1) * kMaxBatch + b] = bd->items[b]->st[0].done;
+    if (b < bd->nitems) {
+        const State& S = bd->items[b]->st[0];
+        out[(s & 1) * kMaxBatch + b] = S.done;
+        out[(2 + (s & 1)) * kMaxBatch + b] = (int)(S.sweeps + S.cert_sweeps);
+    }
     if (b == 0) *seq = s + 1;
 }
 
@@ -3993,35 +4028,45 @@ int launch_sweep(const Work& hw, const Work* wd, int parity, void* stream)
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-// Tiles per workgroup of the resident-steps kernel for hw on a GPU of `cus` compute units, 0 if it
-// does not apply: at most one workgroup per unit, one finalize block each. Up to one tile per unit
+// Tiles per workgroup of the resident-steps kernel for these problems, all in one launch, on a GPU of
+// `cus` compute units, 0 if it does not apply: one cost type, at most one workgroup per unit in all, one
+// finalize block each. Up to one tile per unit
 // the workgroup is one quad; two tiles take two quads, four take two quads of two tiles (as four
 // quads of 16 waves, with 128 registers a thread, the cost does not fit them). Sizes past 8192 have a
 // finalize layout of their own, clouds of more than 3 coordinates more registers per column.
-int steps_tiles(const Work& hw, int cus)
+int steps_tiles(const Work* const* hw, int count, int cus)
 {
-    const int tiles = hw.nrt * hw.nct, most = std::min(cus, kStepsMaxGrid);
-    if (hw.fin_per != 8 || hw.nrt > kStepsMaxRowTiles || hw.fin_nvb > most) return 0;
-    if (hw.cost_kind != MDOT_COST_DENSE && hw.d > 3) return 0;
-    if (tiles <= most) return 1;
-    if (tiles <= 2 * most) return 2;
-    return tiles <= 4 * most ? 4 : 0;
+    const int most = std::min(cus, kStepsMaxGrid);
+    for (int k = 0; k < count; ++k) {
+        const Work& w = *hw[k];
+        if (w.fin_per != 8 || w.nrt > kStepsMaxRowTiles) return 0;
+        if (w.cost_kind != MDOT_COST_DENSE && w.d > 3) return 0;
+        if (base_code_of(w) != base_code_of(*hw[0])) return 0;
+    }
+    for (int nt : {1, 2, 4}) {
+        int blocks = 0;
+        for (int k = 0; k < count; ++k) blocks += steps_blocks(*hw[k], nt);
+        if (blocks <= most) return nt;
+    }
+    return 0;
 }
 
 template <int CC>
-static void launch_steps_as(int nt, int grid, const Work* wd, StepsX* x, int max_steps, hipStream_t s)
+static void launch_steps_as(int nt, int grid, const Work* wd, const BatchDesc* bd, StepsX* x, int max_steps, hipStream_t s)
 {
-    if (nt == 1) hipLaunchKernelGGL((k_steps<CC, 1, 1>), dim3(grid), dim3(256), 0, s, wd, x, max_steps);
-    else if (nt == 2) hipLaunchKernelGGL((k_steps<CC, 2, 1>), dim3(grid), dim3(512), 0, s, wd, x, max_steps);
-    else hipLaunchKernelGGL((k_steps<CC, 2, 2>), dim3(grid), dim3(512), 0, s, wd, x, max_steps);
+    if (nt == 1) hipLaunchKernelGGL((k_steps<CC, 1, 1>), dim3(grid), dim3(256), 0, s, wd, bd, x, max_steps);
+    else if (nt == 2) hipLaunchKernelGGL((k_steps<CC, 2, 1>), dim3(grid), dim3(512), 0, s, wd, bd, x, max_steps);
+    else hipLaunchKernelGGL((k_steps<CC, 2, 2>), dim3(grid), dim3(512), 0, s, wd, bd, x, max_steps);
 }
 
-int launch_steps(const Work& hw, const Work* wd, StepsX* x, int nt, int max_steps, void* stream)
+int base_code_of(const Work& hw) { return base_code(cost_code(hw)); }
+
+int steps_blocks(const Work& hw, int nt) { return std::max((hw.nrt * hw.nct + nt - 1) / nt, hw.fin_nvb); }
+
+static int launch_steps_of(int code, int nt, int grid, const Work* wd, const BatchDesc* bd, StepsX* x, int max_steps, hipStream_t s)
 {
-    const int tiles = hw.nrt * hw.nct, grid = std::max((tiles + nt - 1) / nt, hw.fin_nvb);
-    hipStream_t s = (hipStream_t)stream;
-#define L_(CC) launch_steps_as<CC>(nt, grid, wd, x, max_steps, s)
-    switch (base_code(cost_code(hw))) {
+#define L_(CC) launch_steps_as<CC>(nt, grid, wd, bd, x, max_steps, s)
+    switch (code) {
         case CC_F64: L_(CC_F64); break;
         case CC_F32: L_(CC_F32); break;
         case CC_F16: L_(CC_F16); break;
@@ -4068,6 +4113,19 @@ int launch_lse(const LseArgs& a, StepsX* x, int nt, void* stream)
     }
 #undef L_
     return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+int launch_steps(const Work& hw, const Work* wd, StepsX* x, int nt, int max_steps, void* stream)
+{
+    return launch_steps_of(base_code(cost_code(hw)), nt, steps_blocks(hw, nt), wd, nullptr, x, max_steps, (hipStream_t)stream);
+}
+
+int launch_steps_batch(const BatchDesc& hb, const BatchDesc* bd, StepsX* x, int max_steps, void* stream)
+{
+    hipStream_t s = (hipStream_t)stream;
+    const int rc = launch_steps_of(hb.steps_code, hb.steps_nt, hb.steps_prefix[hb.nitems], nullptr, bd, x, max_steps, s);
+    hipLaunchKernelGGL(k_settle_batch, dim3(kMaxBatch), dim3(kDecideWG), 0, s, bd, x);
+    return rc || hipGetLastError() != hipSuccess ? -1 : 0;
 }
 
 int launch_settle(const Work* wd, void* stream)

@@ -1,5 +1,6 @@
 """Solves whose line-search trials run inside one kernel (at most 1024 tiles) against the serving
-engine, whose steps are one kernel each: the same bits, at the edges of the workgroup layouts."""
+engine, whose steps are kernels of their own where a solve in flight has another cost type: the same
+bits, at the edges of the workgroup layouts. Then the engine with its solves' trials in one kernel."""
 from __future__ import annotations
 
 import numpy as np
@@ -18,7 +19,7 @@ def ctxs():
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     a, b = M.Context(0), M.Context(0)
-    yield a, b
+    yield a, b, Company(b)
     a.close()
     b.close()
 
@@ -32,16 +33,36 @@ COUNTS = ("status", "primal_cost", "dual_bound", "gap", "gamma_final", "marg_err
           "prec_switches")
 
 
+class Company:
+    """Solves of a cost type (5-D clouds) that keeps the engine on one-step kernels."""
+
+    def __init__(self, eng):
+        self.eng, self.n, self.tickets = eng, 48, []
+        self.xy = dev(np.random.default_rng(3).random(2 * 48 * 5), torch.float32)
+        self.r, self.c = dev(W.dirichlet_marginal(48, 1)), dev(W.dirichlet_marginal(48, 2))
+
+    def keep(self):
+        self.tickets = [t for t in self.tickets if self.eng.poll(t[0]) is None]
+        while len(self.tickets) < 3:
+            u, v = torch.empty_like(self.r), torch.empty_like(self.c)
+            desc = M.point_cost(self.xy, 48, 5, "sqeuclid")
+            self.tickets.append((self.eng.submit(desc, self.r, self.c, 1e-9, M.default_params(precision="f64"), u, v), u, v))
+
+
 def _same(ctxs, desc, m, n, seed, gap, **kw):
     r, c = dev(W.dirichlet_marginal(m, seed)), dev(W.dirichlet_marginal(n, seed + 1))
     prm = M.default_params(**kw)
-    outs = []
+    outs, company = [], ctxs[2]
     for solve in (True, False):
         u, v = torch.empty_like(r), torch.empty_like(c)
         if solve:
             res = ctxs[0].solve(desc, r, c, gap, prm, u, v)
         else:
-            res = ctxs[1].poll(ctxs[1].submit(desc, r, c, gap, prm, u, v), wait=True)
+            company.keep()
+            t = ctxs[1].submit(desc, r, c, gap, prm, u, v)
+            while (res := ctxs[1].poll(t)) is None:
+                ctxs[1].run(16)
+                company.keep()
         outs.append((res, u.cpu().numpy(), v.cpu().numpy()))
     (a, ua, va), (b, ub, vb) = outs
     for f in COUNTS:
@@ -124,3 +145,61 @@ def test_many_contexts_on_streams_and_threads(ctxs):
     for o in outs[1:]:
         assert o[:2] == outs[0][:2]
         assert np.array_equal(o[2], outs[0][2]) and np.array_equal(o[3], outs[0][3])
+
+
+# Solves in flight together: one, two and four tiles per workgroup, more tiles than fit, a batch that
+# fits only when some have finished, and small solves in every slot
+BATCHES = {"one": [(1, 1), (64, 257), (300, 300), (130, 67)], "two": [(1000, 1000), (700, 1300), (900, 512)],
+           "four": [(584, 584), (761, 761), (991, 991), (1291, 1291), (1682, 1682), (2191, 2191)],
+           "past": [(2500, 2500), (2200, 2600), (2400, 2300)], "slots": [(90 + k, 150 - k) for k in range(64)]}
+
+
+@pytest.mark.parametrize("name", list(BATCHES))
+@pytest.mark.parametrize("kind", ["points", "f32", "f64"])
+def test_engine_batches_equal_the_solves(ctxs, name, kind):
+    print(f"resident batch {name} {kind}", flush=True)
+    probs = []
+    for k, (m, n) in enumerate(BATCHES[name]):
+        r, c = dev(W.dirichlet_marginal(m, 7 + k)), dev(W.dirichlet_marginal(n, 70 + k))
+        if kind == "points":
+            desc = M.point_cost(dev(np.random.default_rng(k).random((m + n) * 3), torch.float32), n, 3, "sqeuclid", m=m)
+        else:
+            desc = M.dense_cost(torch.rand(m, n, device="cuda", dtype=torch.float32 if kind == "f32" else torch.float64))
+        probs.append((desc, r, c))
+    prm = M.default_params(precision="f64" if kind == "f64" else "f32")
+    eng = M.Context(0)
+    try:
+        held = []
+        for desc, r, c in probs:
+            u, v = torch.empty_like(r), torch.empty_like(c)
+            held.append((eng.submit(desc, r, c, 1e-3, prm, u, v), u, v))
+        assert all(h[0] is not None for h in held)
+        while eng.inflight()[0]:
+            eng.run(64)
+        for (desc, r, c), (t, u, v) in zip(probs, held):
+            u1, v1 = torch.empty_like(r), torch.empty_like(c)
+            a, b = ctxs[0].solve(desc, r, c, 1e-3, prm, u1, v1), eng.poll(t)
+            for f in COUNTS:
+                assert getattr(a, f) == getattr(b, f), f
+            assert torch.equal(u, u1) and torch.equal(v, v1)
+    finally:
+        eng.close()
+
+
+def test_engine_advances_the_steps_asked_for(ctxs):
+    # stages of few steps, so that resident chunks end early: one call of as many steps as the solve
+    # takes (and the rest of a chunk) still ends it; the next call reads that chunk back
+    n = 200
+    desc = M.dense_cost(torch.rand(n, n, device="cuda", dtype=torch.float32))
+    r, c = dev(W.dirichlet_marginal(n, 1)), dev(W.dirichlet_marginal(n, 2))
+    prm = M.default_params()
+    u, v = torch.empty_like(r), torch.empty_like(c)
+    a = ctxs[0].solve(desc, r, c, 1e-2, prm, u, v)
+    eng = M.Context(0)
+    try:
+        t = eng.submit(desc, r, c, 1e-2, prm, u, v)
+        eng.run(a.sweeps + a.cert_sweeps + 32)
+        eng.run(1)
+        assert eng.poll(t) is not None
+    finally:
+        eng.close()
