@@ -2162,7 +2162,7 @@ __global__ void __launch_bounds__(kDecideWG) k_settle(const Work* __restrict__ w
 // finalize block and its dots 1.7, the second exchange 1.4, the decision 1.0.
 //
 // Every workgroup holds up to four tiles (a quad of four waves takes one or two: n = 4096 is 256
-// workgroups of two quads, one per compute unit) with their rows' and columns' vector entries in
+// workgroups, one per compute unit, of two quads, or of four for a point cloud) with their rows' and columns' vector entries in
 // LDS, and does the work of the finalize block of its own number if there is one. Arithmetic and orders are those of
 // k_sweep, k_fin and k_decide, so the results are the same bits. Per step:
 //   1. sweep: tile partials and row-tile shifts are stored for the finalize blocks;
@@ -4030,10 +4030,13 @@ int launch_sweep(const Work& hw, const Work* wd, int parity, void* stream)
 
 // Tiles per workgroup of the resident-steps kernel for these problems, all in one launch, on a GPU of
 // `cus` compute units, 0 if it does not apply: one cost type, at most one workgroup per unit in all, one
-// finalize block each. Up to one tile per unit
-// the workgroup is one quad; two tiles take two quads, four take two quads of two tiles (as four
-// quads of 16 waves, with 128 registers a thread, the cost does not fit them). Sizes past 8192 have a
-// finalize layout of their own, clouds of more than 3 coordinates more registers per column.
+// finalize block each. Up to one tile per unit the workgroup is one quad; two tiles take two quads.
+// Four take two quads of two tiles where the cost is held, which does not fit the 128 registers a
+// thread of four quads has, and four quads for a point cloud, whose sweep is bound by its FP64
+// arithmetic and wants four waves per SIMD in flight (n = 4096 in the plane 20.99 -> 19.22 us per step
+// of a schedule with FP32 exponentials, 30.2 -> 27.1 with FP64; six 3-D clouds in the engine 27.0 ->
+// 23.9 ms). Sizes past 8192 have a finalize layout of their own, clouds of more than 3 coordinates
+// more registers per column.
 int steps_tiles(const Work* const* hw, int count, int cus)
 {
     const int most = std::min(cus, kStepsMaxGrid);
@@ -4056,7 +4059,10 @@ static void launch_steps_as(int nt, int grid, const Work* wd, const BatchDesc* b
 {
     if (nt == 1) hipLaunchKernelGGL((k_steps<CC, 1, 1>), dim3(grid), dim3(256), 0, s, wd, bd, x, max_steps);
     else if (nt == 2) hipLaunchKernelGGL((k_steps<CC, 2, 1>), dim3(grid), dim3(512), 0, s, wd, bd, x, max_steps);
-    else hipLaunchKernelGGL((k_steps<CC, 2, 2>), dim3(grid), dim3(512), 0, s, wd, bd, x, max_steps);
+    else if constexpr (StepKind<typename CostOf<CC>::T, 1>::kPoints)
+        hipLaunchKernelGGL((k_steps<CC, 4, 1>), dim3(grid), dim3(1024), 0, s, wd, bd, x, max_steps);
+    else
+        hipLaunchKernelGGL((k_steps<CC, 2, 2>), dim3(grid), dim3(512), 0, s, wd, bd, x, max_steps);
 }
 
 int base_code_of(const Work& hw) { return base_code(cost_code(hw)); }
