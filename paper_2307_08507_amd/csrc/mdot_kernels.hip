@@ -970,21 +970,28 @@ __device__ __forceinline__ double round_reduce(const double* region, int lane)
     const int slot = min(lane >> 2, (NS + NM) * B - 1);
     const double* src = region + slot * kRoundPad + (lane & 3) * 16;
     const bool sum = slot < NS * B;
-    double v[16];
+    double v[16], r;
 #pragma unroll
     for (int k = 0; k < 16; ++k) v[k] = src[k];
+    // lanes of sums and of minima in turn: both for every lane and a choice between them is 96 more
+    // instructions
+    if (NS > 0 && sum) {
 #pragma unroll
-    for (int w = 1; w < 16; w *= 2)
+        for (int w = 1; w < 16; w *= 2)
 #pragma unroll
-        for (int k = 0; k < 16; k += 2 * w) {
-            const double a = v[k] + v[k + w], b = fmin(v[k], v[k + w]);
-            v[k] = NS == 0 ? b : (sum ? a : b);
-        }
-    double r = v[0];
-    const double x1 = dpp_d<0xb1>(0.0, r);  // quad_perm [1,0,3,2]
-    r = (NS == 0 || !sum) ? fmin(r, x1) : r + x1;
-    const double x2 = dpp_d<0x4e>(0.0, r);  // quad_perm [2,3,0,1]
-    r = (NS == 0 || !sum) ? fmin(r, x2) : r + x2;
+            for (int k = 0; k < 16; k += 2 * w) v[k] += v[k + w];
+        r = v[0];
+        r += dpp_d<0xb1>(0.0, r);  // quad_perm [1,0,3,2]
+        r += dpp_d<0x4e>(0.0, r);  // quad_perm [2,3,0,1]
+    } else {
+#pragma unroll
+        for (int w = 1; w < 16; w *= 2)
+#pragma unroll
+            for (int k = 0; k < 16; k += 2 * w) v[k] = fmin(v[k], v[k + w]);
+        r = v[0];
+        r = fmin(r, dpp_d<0xb1>(0.0, r));
+        r = fmin(r, dpp_d<0x4e>(0.0, r));
+    }
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     return r;
