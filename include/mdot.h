@@ -192,7 +192,8 @@ int mdot_lse2(mdot_ctx* ctx, const mdot_cost_desc* cost, const double* u, const 
  *     not run), else MDOT_E_ARG.
  * Its partials, state and control block live in one static device array per GPU (about
  * 9.7 MB, held from library load until the process ends), not in the context's workspace;
- * the context supplies only its stream and the pinned host block created by mdot_ctx_create.
+ * the context supplies its stream, and the exchange memory and the pinned host block created by
+ * mdot_ctx_create.
  * It calls no hipMalloc/hipFree and no allocating library routine. Every call on one GPU
  * uses that GPU's array, so calls that overlap on one GPU (two contexts or threads, or
  * streams that run concurrently) race and must be serialised by the caller; the array keeps
@@ -232,8 +233,9 @@ int mdot_submit(mdot_ctx* ctx, const mdot_cost_desc* cost, const double* r, cons
                 double target_gap, const mdot_params* params, double* u_out, double* v_out,
                 uint64_t* ticket);
 
-/* Advance every solve in flight by `steps` solver steps (rounded up to whole chunks of 16) and
- * retire the finished ones (potentials written to their u_out/v_out, results kept for
+/* Advance every solve in flight by `steps` solver steps (rounded up to whole chunks of 16; a chunk
+ * may take a solve up to 16 further where all in flight have one cost type and fit the GPU
+ * together) and retire the finished ones (potentials written to their u_out/v_out, results kept for
  * mdot_poll). Chunks are pipelined: each chunk is launched before the previous one is read
  * back, so a call retires the solves finished by the chunks read back during it, and the last
  * chunk it launched is read back by the next call (or by mdot_poll with wait != 0). A solve

@@ -1,12 +1,14 @@
 // C ABI of libmdot (include/mdot.h): context, workspace, intake validation and the host
 // side of the solve loop. All solver decisions are taken on the device (mdot_kernels.hip);
-// the host replays a captured graph of solver steps and polls a done flag once per chunk,
-// keeping two chunks in flight so the GPU never waits for the host.
+// the host replays a captured graph of solver steps (resident ones, a stage's trials in one kernel,
+// where the problem fits the chip) and polls a done flag once per chunk, keeping two chunks in
+// flight so the GPU never waits for the host. Standalone sweeps are launched directly, one wait each.
 //
 // The serving engine (mdot_submit / mdot_run / mdot_poll) keeps up to kMaxBatch solves in
 // flight. Every engine step advances all of them with one launch per kernel, one workgroup per
 // tile and per finalize block of the solves in flight (a device batch descriptor maps
-// workgroups to solves; the graph is captured again when the batch changes). A finished solve
+// workgroups to solves; the graph is captured again when the batch changes); solves of one cost type
+// that fit the chip together take resident steps, each at its own pace within a chunk. A finished solve
 // frees its slot when its chunk is read back, where new requests can be admitted if a slot and
 // the HBM budget allow. Neither an admission nor a retirement waits for the chunk in flight:
 // intake runs on a side stream, a retiring solve's potentials and state are copied out behind

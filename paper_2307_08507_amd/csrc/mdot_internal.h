@@ -121,7 +121,7 @@ struct DevParams {
     int32_t projector, precond, smooth_fixed, pad_;
 };
 
-// Scalar solver state in device memory. Written only by the last workgroup of a sweep
+// Scalar solver state in device memory. Written only by the decision of a step
 // (one thread), read by every thread of the next kernels.
 struct State {
     int32_t done, status, sweep_mode, vec_action;

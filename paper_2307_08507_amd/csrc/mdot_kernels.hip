@@ -1,7 +1,7 @@
 // HIP kernels of the MDOT-PNCG hot path for gfx950 (MI355X).
 //
 // One solver step is three kernels on the context stream, with no synchronisation between
-// workgroups inside the O(n^2) kernels:
+// workgroups inside them:
 //   k_sweep : one fused pass over the cost for a line-search trial: every workgroup forms
 //             X_ij = u_i + v_j - gamma C_ij for a BR x BC tile (FP64 argument), takes one exp
 //             per element and accumulates BOTH the row sums and the column sums from that
@@ -16,6 +16,9 @@
 //   k_decide: one wave: reduces those dots in a fixed order and runs the scalar logic of
 //             the line search (App. B), PNCG (Alg. 2) and the annealing loop (Alg. 1), then
 //             stores the next state. Kernel boundaries order the three; no atomics or fences.
+// Problems of at most 1024 tiles run the steps between a stage's start and its end in one kernel,
+// k_steps, whose workgroups exchange the same values through memory; mdot_lse2 up to 512 tiles is one
+// kernel, k_lse. Both give the bits of the three kernels, which run everything else.
 // The sweeps evaluate the pending vector update on the fly for their own rows and columns
 // with the same function k_fin uses to store it (explicit fma, so both are bit-identical).
 // The host never reads a value between steps; it replays a captured graph of steps and
@@ -950,7 +953,7 @@ __device__ void tile_lse(const Work& w, const SweepArgs& S, const TileCtx& t, do
 // lanes per slot: one write and about three operations per row and quantity, where a reduction
 // across the lanes of each by itself takes 18. The sums are added in the same balanced tree over
 // the lanes as wave_sum. Returns slot (lane >> 2)'s value in all four of its lanes. With the rows'
-// loads issued four rows ahead as well, n = 4096 FP32: R1 41 -> 31.5 us, R2 47 -> 44 us. (With the
+// loads issued four rows ahead as well, n = 4096 FP32: R1 41 -> 32 us, R2 47 -> 42.5 us. (With the
 // column values in registers, at 166 VGPRs and three waves per SIMD, R1 33.5 and R2 38 us, but the LSE
 // path shares the kernel and needs four.)
 constexpr int kRoundPad = 65;       // doubles: the four lanes' reads of 16 slots hit distinct banks
@@ -2169,9 +2172,10 @@ __global__ void __launch_bounds__(kDecideWG) k_settle(const Work* __restrict__ w
 // finalize block and its dots 1.7, the second exchange 1.4, the decision 1.0.
 //
 // Every workgroup holds up to four tiles (a quad of four waves takes one or two: n = 4096 is 256
-// workgroups, one per compute unit, of two quads, or of four for a point cloud) with their rows' and columns' vector entries in
-// LDS, and does the work of the finalize block of its own number if there is one. Arithmetic and orders are those of
-// k_sweep, k_fin and k_decide, so the results are the same bits. Per step:
+// workgroups, one per compute unit, of two quads, or of four for a point cloud) with their rows' and
+// columns' vector entries in LDS, and does the work of the finalize block of its own number if there is
+// one. Arithmetic and orders are those of k_sweep, k_fin and k_decide, so the results are the same bits.
+// Per step:
 //   1. sweep: tile partials and row-tile shifts are stored for the finalize blocks;
 //   2. the finalize blocks fold them and store log-sums and dots;
 //   3. every workgroup reads all dots, takes the decision (the same in each; anything but the
