@@ -1569,9 +1569,11 @@ int mdot_run(mdot_ctx* ctx, int steps, int* n_done)
     int rc = collect_retired(ctx, false, &completed);
     if (rc) return rc;
     const int chunks = std::max(1, (steps + kBatchChunk - 1) / kBatchChunk);
-    // a resident chunk is short of its steps where a stage ends early: more chunks make up for it
+    // a resident chunk is short of its steps where a stage ends early: more chunks make up for it, at
+    // most so many that its single steps alone would
+    constexpr int kMost = kBatchChunk / kResidentSingles;
     int owed = 0, least = 0;
-    for (int ch = 0; ch < chunks || owed > 0; ++ch) {
+    for (int64_t ch = 0; ch < chunks || (owed > 0 && ch < (int64_t)kMost * chunks); ++ch) {
         int active = 0;
         for (const Slot& sl : ctx->slots) active += sl.used;
         if (active == 0 && ctx->eng_pending < 0) break;
