@@ -150,16 +150,20 @@ struct DenseCost {
     __amdgpu_buffer_rsrc_t rs;
     int n;
     int odd;  // 16-bit types: 2 when the tile's first row starts in the upper half of a dword
-    __device__ __forceinline__ DenseCost(const Work& w, int i0) : n(w.n), odd(0)
+    int end;  // 16-bit types: where the matrix ends, in bytes like at(), if that is inside a dword
+    __device__ __forceinline__ DenseCost(const Work& w, int i0) : n(w.n), odd(0), end(0x7fffffff)
     {
         const char* base = (const char*)w.cost + (size_t)i0 * w.n * kBytes;
         size_t rem = ((size_t)w.m - i0) * w.n * kBytes;
         if constexpr (kBytes == 2) {
             // based at the dword that holds the first element and ending with the dword that
-            // holds the last one, so that no valid element fails the per-dword range check
+            // holds the last one, so that no valid element fails the per-dword range check. The
+            // half of that dword behind the last element is not the matrix's: load() clears it.
             odd = (int)((uintptr_t)base & 2);
             base -= odd;
-            rem = (rem + odd + 3) & ~(size_t)3;
+            rem += odd;
+            if ((rem & 2) && rem < 0x7ffffff0u) end = (int)rem;
+            rem = (rem + 3) & ~(size_t)3;
         }
         rs = __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, (int)(rem > 0x7ffffffcu ? 0x7ffffffcu : rem),
                                                kBufDword3);
@@ -170,7 +174,9 @@ struct DenseCost {
     // past the end. The loads need dword alignment only, which every FP32 and FP64 row and every
     // 16-bit row of even length in a matrix that starts on a dword has; the range check is per dword.
     // Other 16-bit rows read the three dwords around their 8 bytes and shift, all loads of the batch
-    // before the first shift (one branch per row instead makes every row wait for its own load).
+    // before the first shift (one branch per row instead makes every row wait for its own load). Where
+    // a lane's batch reaches past a matrix that ends inside a dword, the half behind the end is cleared
+    // first: a padding column, or the row past the last one, would decode it.
     // n = 8191 BF16 sweep: 64.8 us with four 2-byte loads per lane and row, 35.4 us so; 32 us at 8192.
     // FP32 and FP64 rows from `rows` on may be left out.
     template <int B>
@@ -205,6 +211,13 @@ struct DenseCost {
             for (int u = 0; u < B; ++u) {
                 auto a = __builtin_amdgcn_raw_buffer_load_b96(rs, at(u) & ~3, 0, 0);
                 d[u][0] = a[0]; d[u][1] = a[1]; d[u][2] = a[2];
+            }
+            if (at(B - 1) + 8 > end) {
+#pragma unroll
+                for (int u = 0; u < B; ++u)
+#pragma unroll
+                    for (int k = 0; k < 3; ++k)
+                        if ((at(u) & ~3) + 4 * k + 2 == end) d[u][k] &= 0xffffu;
             }
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
