@@ -233,15 +233,17 @@ int mdot_submit(mdot_ctx* ctx, const mdot_cost_desc* cost, const double* r, cons
                 double target_gap, const mdot_params* params, double* u_out, double* v_out,
                 uint64_t* ticket);
 
-/* Advance every solve in flight by `steps` solver steps (rounded up to whole chunks of 16; a chunk
- * may take a solve up to 16 further where all in flight have one cost type and fit the GPU
- * together) and retire the finished ones (potentials written to their u_out/v_out, results kept for
+/* Advance every solve in flight by `steps` solver steps (rounded up to whole chunks of 16) and
+ * retire the finished ones (potentials written to their u_out/v_out, results kept for
  * mdot_poll). Chunks are pipelined: each chunk is launched before the previous one is read
  * back, so a call retires the solves finished by the chunks read back during it, and the last
- * chunk it launched is read back by the next call (or by mdot_poll with wait != 0). A solve
- * that finished stays in flight, doing nothing, until its chunk is read back. *n_done (host,
- * may be NULL) receives the number retired. Returns after the chunks it read back have
- * completed; the last chunk launched may still be running. */
+ * chunk it launched is read back by the next call (or by mdot_poll with wait != 0). Where all
+ * solves in flight have one cost type and fit the GPU together, a chunk advances each of them by
+ * 2 to 32 steps (it ends at the end of a stage): chunks are then launched until none is behind the
+ * steps asked for, so that others are further (at most 8 times the chunks, which 2 steps each
+ * would need). A solve that finished stays in flight, doing nothing, until its chunk is read back.
+ * *n_done (host, may be NULL) receives the number retired. Returns after the chunks it read back
+ * have completed; the last chunk launched may still be running. */
 int mdot_run(mdot_ctx* ctx, int steps, int* n_done);
 
 /* Result of a submitted solve. Returns MDOT_OK (res filled, ticket released) or 2 when still in

@@ -89,7 +89,8 @@ struct Slot {
     const double* c = nullptr;
     int64_t resumed_at = -1;  // engine chunks up to this sequence number ran the paused state
     bool resident = false;    // resident steps know its variant
-    int steps = 0;            // solver steps taken, by the chunks read back
+    int steps = 0;            // the solve's own count of its steps, by the chunks read back
+    int64_t taken = 0;        // steps these chunks advanced it by (kBatchChunk each unless resident)
 };
 
 }  // namespace
@@ -1518,6 +1519,7 @@ int mdot_submit(mdot_ctx* ctx, const mdot_cost_desc* cost, const double* r, cons
     sl.resumed_at = -1;
     sl.resident = !prm.projector && !prm.precond;
     sl.steps = 0;
+    sl.taken = 0;
     ctx->bytes_in_use += sl.footprint;
     ctx->batch_dirty = true;
     *ticket = sl.ticket;
@@ -1525,19 +1527,18 @@ int mdot_submit(mdot_ctx* ctx, const mdot_cost_desc* cost, const double* r, cons
 }
 
 // Read back an engine chunk: retire the solves it finished (their slots may already hold newer
-// solves, admitted after the chunk was launched: those are told apart by the ticket). *least: the
-// fewest steps a solve still running has taken in it.
-static int process_chunk(mdot_ctx* ctx, int buf, int* least)
+// solves, admitted after the chunk was launched: those are told apart by the ticket).
+static int process_chunk(mdot_ctx* ctx, int buf)
 {
     HIPCHK(ctx, hipEventSynchronize(ctx->eng_ev[buf]));
     bury_graphs(ctx, ctx->chunk_seq[buf]);
     const int* done = ctx->h_done + 2 + buf * kMaxBatch;
     const int* steps = done + 2 * kMaxBatch;
-    *least = kBatchChunk;
     for (int m = 0; m < ctx->chunk_m[buf]; ++m) {
         Slot& sl = ctx->slots[ctx->chunk_slot[buf][m]];
         if (!sl.used || sl.ticket != ctx->chunk_ticket[buf][m]) continue;
-        if (!done[m]) *least = std::min(*least, steps[m] - sl.steps);
+        // (a pause for the exact cost uses its chunk up)
+        sl.taken += ctx->chunk_resident[buf] && done[m] != 2 ? steps[m] - sl.steps : kBatchChunk;
         sl.steps = steps[m];
         if (!done[m]) continue;
         if (done[m] == 2) {  // MIXED: paused at the switch to the exact cost
@@ -1569,14 +1570,27 @@ int mdot_run(mdot_ctx* ctx, int steps, int* n_done)
     int rc = collect_retired(ctx, false, &completed);
     if (rc) return rc;
     const int chunks = std::max(1, (steps + kBatchChunk - 1) / kBatchChunk);
-    // a resident chunk is short of its steps where a stage ends early: more chunks make up for it, at
-    // most so many that its single steps alone would
+    // A resident chunk is short of its steps where a stage ends early, and past them where none does.
+    // The chunk in flight counts as kBatchChunk steps until it is read back; chunks are launched until
+    // no solve is behind the steps asked for, at most so many that their single steps alone would do.
     constexpr int kMost = kBatchChunk / kResidentSingles;
-    int owed = 0, least = 0;
-    for (int64_t ch = 0; ch < chunks || (owed > 0 && ch < (int64_t)kMost * chunks); ++ch) {
+    int64_t due[kMaxBatch];
+    for (int s = 0; s < kMaxBatch; ++s) {
+        const Slot& sl = ctx->slots[s];
+        bool in_flight = false;
+        for (int m = 0; ctx->eng_pending >= 0 && m < ctx->chunk_m[ctx->eng_pending]; ++m)
+            in_flight |= sl.used && ctx->chunk_ticket[ctx->eng_pending][m] == sl.ticket;
+        due[s] = sl.taken + (in_flight ? kBatchChunk : 0) + (int64_t)kBatchChunk * chunks;
+    }
+    for (int64_t ch = 0;; ++ch) {
         int active = 0;
-        for (const Slot& sl : ctx->slots) active += sl.used;
+        bool behind = false;  // (after the first, every solve in flight is in the chunk in flight)
+        for (int s = 0; s < kMaxBatch; ++s) {
+            active += ctx->slots[s].used;
+            behind |= ctx->slots[s].used && ctx->slots[s].taken + kBatchChunk < due[s];
+        }
         if (active == 0 && ctx->eng_pending < 0) break;
+        if (ch > 0 && (active > 0 ? !behind || ch >= (int64_t)kMost * chunks : ch >= chunks)) break;
         if (active > 0) {  // launch the next chunk before reading the previous one back
             if (ctx->batch_dirty) {
                 rc = rebuild_batch(ctx);
@@ -1600,14 +1614,13 @@ int mdot_run(mdot_ctx* ctx, int steps, int* n_done)
             HIPCHK(ctx, hipGraphLaunch(ctx->bgraph, ctx->stream));
             HIPCHK(ctx, hipEventRecord(ctx->eng_ev[buf], ctx->stream));
             if (ctx->eng_pending >= 0) {
-                rc = process_chunk(ctx, ctx->eng_pending, &least);
+                rc = process_chunk(ctx, ctx->eng_pending);
                 if (rc) return rc;
-                if (ctx->chunk_resident[ctx->eng_pending]) owed += kBatchChunk - least;
             }
             ctx->eng_pending = buf;
             ctx->eng_next = buf ^ 1;
         } else {  // nothing left to advance: read the last chunk back
-            rc = process_chunk(ctx, ctx->eng_pending, &least);
+            rc = process_chunk(ctx, ctx->eng_pending);
             if (rc) return rc;
             ctx->eng_pending = -1;
         }

@@ -3453,7 +3453,7 @@ __global__ void k_gather_done(const BatchDesc* __restrict__ bd, int* out, int* s
     if (b < bd->nitems) {
         const State& S = bd->items[b]->st[0];
         out[(s & 1) * kMaxBatch + b] = S.done;
-        out[(2 + (s & 1)) * kMaxBatch + b] = (int)(S.sweeps + S.cert_sweeps);
+        out[(2 + (s & 1)) * kMaxBatch + b] = (int)(S.sweeps + S.fallbacks + S.cert_sweeps);
     }
     if (b == 0) *seq = s + 1;
 }
