@@ -3104,6 +3104,12 @@ __global__ void __launch_bounds__(256 * NQ) k_steps(const Work* __restrict__ wp,
 // out->done stays 0 if the workgroups could not meet, and out->retry is set if a wait ran out; the
 // caller then takes the kernels.
 
+// A caller's u, v or shift entry. Arithmetic hands the payload of a NaN on, and kEmpty is one: every
+// NaN that comes in is replaced by the one arithmetic makes, or a reader would wait for a value that is
+// there. So is the smallest entry of a tile of nothing but NaNs. (Other values made of a cost with NaNs
+// lose them in minima, maxima and exponentials; a solve's vectors are made by the library.)
+__device__ __forceinline__ double plain_nan(double v) { return v == v ? v : NAN; }
+
 // Raw entries of row r of the tile (columns j0 ..): held, or recomputed from points.
 template <class Cost, class K>
 __device__ __forceinline__ void lse_row(const Cost& c, const StepTile& t, typename Cost::Raw (&raw)[K::kTiles][K::RB], int u,
@@ -3223,8 +3229,8 @@ __global__ void __launch_bounds__(256 * NQ) k_lse(LseArgs A, StepsX* __restrict_
         if constexpr (K::kHold) {
             c.template load<K::RB>(t[u].rbase, j0, raw[u]);
         }
-        if (t[u].has_col(me)) sh.cz[t[u].at][me.t] = A.in.v[t[u].J * kBC + me.t];
-        if (t[u].has_row(me)) sh.rz[t[u].at][me.t] = A.in.u[t[u].i0 + me.t];
+        if (t[u].has_col(me)) sh.cz[t[u].at][me.t] = plain_nan(A.in.v[t[u].J * kBC + me.t]);
+        if (t[u].has_row(me)) sh.rz[t[u].at][me.t] = plain_nan(A.in.u[t[u].i0 + me.t]);
     }
     if (fin_wg) {
         const Lane me;
@@ -3270,7 +3276,7 @@ __global__ void __launch_bounds__(256 * NQ) k_lse(LseArgs A, StepsX* __restrict_
                     c = (c != c || hi[q] != hi[q]) ? NAN : fmax(c, hi[q]);
                 }
                 double* dst = x->range[t[u].I * z.nct + t[u].J];
-                xstore(dst, a);
+                xstore(dst, plain_nan(a));
                 xstore(dst + 1, c);
             }
         }
@@ -3286,7 +3292,7 @@ __global__ void __launch_bounds__(256 * NQ) k_lse(LseArgs A, StepsX* __restrict_
 #pragma unroll
             for (int u = 0; u < TP; ++u) {
                 const Lane me;
-                if (t[u].has_row(me)) sh.rlz[t[u].at][me.t] = A.in.shift[t[u].i0 + me.t];
+                if (t[u].has_row(me)) sh.rlz[t[u].at][me.t] = plain_nan(A.in.shift[t[u].i0 + me.t]);
             }
         } else {
 #pragma unroll
@@ -3335,7 +3341,7 @@ __global__ void __launch_bounds__(256 * NQ) k_lse(LseArgs A, StepsX* __restrict_
         if (fin_wg) {
             const Lane me;
             const FinEntry f(z, me);
-            if (f.own && f.row) sh.flz[me.t] = A.in.shift ? A.in.shift[f.k] : lse_shift(w, z, f.k, wait);
+            if (f.own && f.row) sh.flz[me.t] = A.in.shift ? plain_nan(A.in.shift[f.k]) : lse_shift(w, z, f.k, wait);
         }
         // ---- tile set-up (steps_update with z = (u, v), p = 0)
         __syncthreads();
