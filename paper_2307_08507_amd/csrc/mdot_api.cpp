@@ -1208,8 +1208,14 @@ static int run_alone(mdot_ctx* ctx, ProblemBufs& pb, const mdot_cost_desc* cost,
         hout->retry = 0;
         if (launch_lse(A, ctx->d_steps, nt, st)) return fail(ctx, MDOT_E_DEVICE, "standalone sweep launch failed");
         HIPCHK(ctx, hipStreamSynchronize(st));
-        if (hout->retry) ctx->steps_off = true;  // a wait ran out: the kernels from here on
-        else if (hout->done && hout->valid) {
+        if (hout->retry) {  // a wait ran out: the kernels from here on, if the inputs are as they were
+            ctx->steps_off = true;
+            auto in_outputs = [&](const double* p, int k) {
+                return p && ((p < lr_out + m && lr_out < p + k) || (p < lc_out + n && lc_out < p + k));
+            };
+            if (in_outputs(in.u, m) || in_outputs(in.v, n) || in_outputs(in.shift, m))
+                return fail(ctx, MDOT_E_DEVICE, "a wait between the workgroups of a resident sweep ran out");
+        } else if (hout->done && hout->valid) {
             memcpy(res, const_cast<const AloneOut*>(hout), sizeof *res);
             return MDOT_OK;
         } else if (hout->done) {  // the exact range, for the message

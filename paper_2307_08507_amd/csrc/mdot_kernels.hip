@@ -2653,6 +2653,7 @@ __device__ __forceinline__ void steps_finalize(const StepSize& z, StepsX* x, Ste
                     if (is_empty(xs[u])) xs[u] = xload(base + (size_t)(f.l + u * f.L) * st);
             }
             wave_drain();  // the emptied slots of the next turn
+            if (wait.dead) sh.dead = 1;
             if (!f.row) {
                 M = wave_max(fmax(ts[0], ts[1]));
                 if (me.t < nrt) sh.fac[me.t] = exp((me.t < 64 ? ts[0] : ts[1]) - M);
@@ -2698,7 +2699,8 @@ __device__ __forceinline__ void steps_finalize(const StepSize& z, StepsX* x, Ste
     static_assert(D_BAD == kStepDots, "the dots of a step are the first ones");
     __syncthreads();
     const Lane me;
-    if (me.q == 0 && me.t <= kStepDots)
+    // without its dots nobody takes the step, or results made of a value that never came
+    if (me.q == 0 && me.t <= kStepDots && !sh.dead)
         xstore(&x->dots[b][z.blk][me.t], (sh.red[me.t * 4 + 0] + sh.red[me.t * 4 + 1]) + (sh.red[me.t * 4 + 2] + sh.red[me.t * 4 + 3]));
 }
 
@@ -3101,8 +3103,9 @@ __global__ void __launch_bounds__(256 * NQ) k_steps(const Work* __restrict__ wp,
 // with FP64 exponentials where FP32 rows or columns left the range, outputs. As six kernels (n = 256)
 // it is bound by their boundaries, and the cost is read twice; here the tiles are loaded once and the
 // workgroups exchange row maxima, partials and dots as in k_steps. Same arithmetic, same bits.
-// out->done stays 0 if the workgroups could not meet, and out->retry is set if a wait ran out; the
-// caller then takes the kernels.
+// out->done stays 0 if the workgroups could not meet, and out->retry is set by any workgroup whose wait
+// ran out (it leaves at once, so that no step is completed with what it did not get); the caller then
+// takes the kernels.
 
 // A caller's u, v or shift entry. Arithmetic hands the payload of a NaN on, and kEmpty is one: every
 // NaN that comes in is replaced by the one arithmetic makes, or a reader would wait for a value that is
@@ -3176,6 +3179,13 @@ __device__ __forceinline__ void lse_range(StepsX* x, StepsShared<NT>& sh, int nt
     __syncthreads();
     *lo = a;
     *hi = bad ? NAN : b;
+}
+
+// The end of a workgroup whose wait ran out.
+__device__ __forceinline__ void lse_give_up(const StepSize& z, StepsX* x, AloneOut* out)
+{
+    if (threadIdx.x == 0) out->retry = 1;
+    steps_leave(z, x);
 }
 
 template <int CC, int NQ, int TP>
@@ -3344,7 +3354,10 @@ __global__ void __launch_bounds__(256 * NQ) k_lse(LseArgs A, StepsX* __restrict_
             if (f.own && f.row) sh.flz[me.t] = A.in.shift ? plain_nan(A.in.shift[f.k]) : lse_shift(w, z, f.k, wait);
         }
         // ---- tile set-up (steps_update with z = (u, v), p = 0)
-        __syncthreads();
+        if (__syncthreads_or(wait.dead)) {
+            lse_give_up(z, x, A.out);
+            return;
+        }
 #pragma unroll
         for (int u = 0; u < TP; ++u) {
             const Lane me;
@@ -3366,7 +3379,10 @@ __global__ void __launch_bounds__(256 * NQ) k_lse(LseArgs A, StepsX* __restrict_
             StepDots dots;
             dots.ask(z, x, b);
             dots.take(z, x, sh, b, wait);
-            __syncthreads();
+            if (__syncthreads_or(wait.dead)) {
+                lse_give_up(z, x, A.out);
+                return;
+            }
             any = false;
             for (int i = threadIdx.x; i < z.nvb; i += blockDim.x) any |= sh.y[kStepDots][i] != 0.0;
             any = __syncthreads_or(any);
