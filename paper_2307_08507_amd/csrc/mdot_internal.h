@@ -217,6 +217,23 @@ constexpr bool range_valid(double scale, double lo, double hi)
     return scale * lo >= -kRangeSlack && scale * hi <= 1.0 + kRangeSlack;
 }
 
+// How long a wait inside a resident kernel has lasted, in 10 ns ticks of a clock that is looked at about
+// every millisecond. A gap between two looks counts for at most kWaitGap: while a queue is preempted
+// (another process, a debugger) its clock goes on and its workgroups do not, which is no reason to give
+// a solve up.
+constexpr uint32_t kWaitTicks = 400000000;  // 4 s
+constexpr uint32_t kWaitGap = 1000000;      // 10 ms
+struct WaitClock {
+    uint32_t last = 0, spent = 0;
+    constexpr bool ran_out(uint32_t now)  // (differences of the low words: the clock wraps in 43 s)
+    {
+        const uint32_t gap = now - last;
+        last = now;
+        spent += gap < kWaitGap ? gap : kWaitGap;
+        return spent > kWaitTicks;
+    }
+};
+
 // Exchange memory of the resident-steps kernel (k_steps), in device memory: zeroed once.
 constexpr int kStepsMaxGrid = 256;      // workgroups
 constexpr int kStepsMaxRowTiles = 128;  // row tiles (8192 rows)

@@ -2206,11 +2206,10 @@ __global__ void __launch_bounds__(kDecideWG) k_settle(const Work* __restrict__ w
 // All workgroups have to run at the same time. They meet once at the start, with a limit of
 // kStartTicks: if the GPU is shared and some cannot start, all of them leave with nothing
 // changed and the one-step kernels that follow carry on. Later waits cannot starve; they have a
-// limit all the same, after which the solve ends with an error.
+// limit all the same (WaitClock), after which the solve ends with an error.
 constexpr uint64_t kEmpty = 0x7ff8dead0000beefull;
 constexpr uint32_t kStepsAbort = 0x80000000u;
-constexpr uint64_t kStartTicks = 5000;       // 50 us of the 100 MHz wall clock
-constexpr uint64_t kWaitTicks = 400000000;   // 4 s
+constexpr uint64_t kStartTicks = 5000;  // 50 us of the 100 MHz wall clock
 
 template <class T>
 __device__ __forceinline__ T xload(const T* p)
@@ -2231,15 +2230,13 @@ __device__ __forceinline__ void wave_drain() { asm volatile("s_waitcnt vmcnt(0)"
 struct Wait {
     StepsX* x;
     uint32_t n = 0;
-    uint64_t t0 = 0;
+    WaitClock clock;
     bool dead = false;
     __device__ __forceinline__ explicit Wait(StepsX* x_) : x(x_) {}
     __device__ __forceinline__ bool again()
     {
         if ((++n & 1023) == 0) {
-            const uint64_t t = wall_clock64();
-            if (t0 == 0) t0 = t;
-            if (t - t0 > kWaitTicks) xstore(&x->abort, 1u);
+            if (clock.ran_out((uint32_t)wall_clock64())) xstore(&x->abort, 1u);
             dead = xload(&x->abort) != 0;
         }
         return !dead;
