@@ -51,7 +51,7 @@ enum {
     MDOT_E_MARGINAL = -2, /* r or c negative, non-finite, or |sum - 1| > 1e-9 max(m, n) */
     MDOT_E_COST = -3,     /* scaled cost outside [0, 1] or non-finite */
     MDOT_E_NOMEM = -4,    /* device allocation failed, or the request exceeds the HBM budget */
-    MDOT_E_DEVICE = -5,   /* a HIP call failed, or workgroups of one kernel waited 4 s for each other */
+    MDOT_E_DEVICE = -5,   /* a HIP call failed, or one kernel's workgroups waited in vain for each other */
     MDOT_E_BUSY = -6      /* no free serving slot */
 };
 

@@ -217,22 +217,13 @@ constexpr bool range_valid(double scale, double lo, double hi)
     return scale * lo >= -kRangeSlack && scale * hi <= 1.0 + kRangeSlack;
 }
 
-// How long a wait inside a resident kernel has lasted, in 10 ns ticks of a clock that is looked at about
-// every millisecond. A gap between two looks counts for at most kWaitGap: while a queue is preempted
-// (another process, a debugger) its clock goes on and its workgroups do not, which is no reason to give
-// a solve up.
-constexpr uint32_t kWaitTicks = 400000000;  // 4 s
-constexpr uint32_t kWaitGap = 1000000;      // 10 ms
-struct WaitClock {
-    uint32_t last = 0, spent = 0;
-    constexpr bool ran_out(uint32_t now)  // (differences of the low words: the clock wraps in 43 s)
-    {
-        const uint32_t gap = now - last;
-        last = now;
-        spent += gap < kWaitGap ? gap : kWaitGap;
-        return spent > kWaitTicks;
-    }
-};
+// The limit of a wait inside a resident kernel, in looks at memory (0.1 to 1 us each: one to eight
+// seconds), with the abort flag read every kWaitFlag of them. A count and not a time: while a queue is
+// preempted (another process, a debugger) the clock goes on and its workgroups do not, which is no
+// reason to give a solve up. (With the clock read at every kWaitFlag-th look instead and long gaps
+// capped, solve of n = 256 7.77 ms, six clouds in flight 24.8; counted 7.72 and 24.5.)
+constexpr uint32_t kWaitFlag = 1024;
+constexpr uint32_t kWaitLooks = 1u << 23;
 
 // Exchange memory of the resident-steps kernel (k_steps), in device memory: zeroed once.
 constexpr int kStepsMaxGrid = 256;      // workgroups

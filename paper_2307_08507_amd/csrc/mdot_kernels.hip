@@ -2206,7 +2206,7 @@ __global__ void __launch_bounds__(kDecideWG) k_settle(const Work* __restrict__ w
 // All workgroups have to run at the same time. They meet once at the start, with a limit of
 // kStartTicks: if the GPU is shared and some cannot start, all of them leave with nothing
 // changed and the one-step kernels that follow carry on. Later waits cannot starve; they have a
-// limit all the same (WaitClock), after which the solve ends with an error.
+// limit all the same (kWaitLooks), after which the solve ends with an error.
 constexpr uint64_t kEmpty = 0x7ff8dead0000beefull;
 constexpr uint32_t kStepsAbort = 0x80000000u;
 constexpr uint64_t kStartTicks = 5000;  // 50 us of the 100 MHz wall clock
@@ -2230,13 +2230,12 @@ __device__ __forceinline__ void wave_drain() { asm volatile("s_waitcnt vmcnt(0)"
 struct Wait {
     StepsX* x;
     uint32_t n = 0;
-    WaitClock clock;
     bool dead = false;
     __device__ __forceinline__ explicit Wait(StepsX* x_) : x(x_) {}
     __device__ __forceinline__ bool again()
     {
-        if ((++n & 1023) == 0) {
-            if (clock.ran_out((uint32_t)wall_clock64())) xstore(&x->abort, 1u);
+        if (++n % kWaitFlag == 0) {
+            if (n >= kWaitLooks) xstore(&x->abort, 1u);
             dead = xload(&x->abort) != 0;
         }
         return !dead;
@@ -2608,8 +2607,10 @@ __device__ __forceinline__ void steps_update(StepsShared<NT>& sh, const StepTile
 }
 
 // One finalize block (fin_lse_entry<8>): the pending update of its entries while the partials are
-// on their way, then fold them and store log-sums and dots.
-template <int NT>
+// on their way, then fold them and store log-sums and dots. kGuard: after a wait that ran out the dots are
+// not stored, so that nobody takes results made of a value that never came (k_steps looks at the abort
+// flag behind its last step instead; the flag in LDS costs it 1.5 % of a step).
+template <bool kGuard, int NT>
 __device__ __forceinline__ void steps_finalize(const StepSize& z, StepsX* x, StepsShared<NT>& sh, int b, bool e64, Wait& wait)
 {
     double M = 0.0, xs[8];
@@ -2650,7 +2651,7 @@ __device__ __forceinline__ void steps_finalize(const StepSize& z, StepsX* x, Ste
                     if (is_empty(xs[u])) xs[u] = xload(base + (size_t)(f.l + u * f.L) * st);
             }
             wave_drain();  // the emptied slots of the next turn
-            if (wait.dead) sh.dead = 1;
+            if (kGuard && wait.dead) sh.dead = 1;
             if (!f.row) {
                 M = wave_max(fmax(ts[0], ts[1]));
                 if (me.t < nrt) sh.fac[me.t] = exp((me.t < 64 ? ts[0] : ts[1]) - M);
@@ -2696,8 +2697,7 @@ __device__ __forceinline__ void steps_finalize(const StepSize& z, StepsX* x, Ste
     static_assert(D_BAD == kStepDots, "the dots of a step are the first ones");
     __syncthreads();
     const Lane me;
-    // without its dots nobody takes the step, or results made of a value that never came
-    if (me.q == 0 && me.t <= kStepDots && !sh.dead)
+    if (me.q == 0 && me.t <= kStepDots && !(kGuard && sh.dead))
         xstore(&x->dots[b][z.blk][me.t], (sh.red[me.t * 4 + 0] + sh.red[me.t * 4 + 1]) + (sh.red[me.t * 4 + 2] + sh.red[me.t * 4 + 3]));
 }
 
@@ -3029,7 +3029,7 @@ __global__ void __launch_bounds__(256 * NQ) k_steps(const Work* __restrict__ wp,
         steps_sweep<Cost, NQ, TP>(sh, x, t, cost.c, raw, g2, e64, b);
         // ---- finalize, decide
         Wait wait(x);
-        if (fin_wg) steps_finalize(z, x, sh, b, e64, wait);
+        if (fin_wg) steps_finalize<false>(z, x, sh, b, e64, wait);
         // the dots and this thread's log-sums are asked for first and looked at after the work that
         // need not wait for them
         StepDots dots;
@@ -3372,7 +3372,7 @@ __global__ void __launch_bounds__(256 * NQ) k_lse(LseArgs A, StepsX* __restrict_
         bool e64 = A.e64 != 0, any = false;
         for (int b = 0;; ++b) {
             steps_sweep<Cost, NQ, TP>(sh, x, t, cost.c, raw, g2, e64, b);
-            if (fin_wg) steps_finalize(z, x, sh, b, e64, wait);
+            if (fin_wg) steps_finalize<true>(z, x, sh, b, e64, wait);
             StepDots dots;
             dots.ask(z, x, b);
             dots.take(z, x, sh, b, wait);
