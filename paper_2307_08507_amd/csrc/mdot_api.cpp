@@ -93,6 +93,21 @@ struct Slot {
     int64_t taken = 0;        // steps these chunks advanced it by (kBatchChunk each unless resident)
 };
 
+// A captured chunk of `main`'s steps and what it was captured with: m, n, the sweep kernel instance (cost
+// code, which also tells the point dimension classes apart) and the kind of steps (steps_mode).
+struct SoloGraph {
+    hipGraphExec_t exec = nullptr;
+    int m = 0, n = 0, code = -1, steps = 0;
+};
+
+// A captured chunk of engine steps and what it was captured with: its sweep instances and their tile
+// ranges, the finalize grid and instance, the resident steps' instance and grid.
+struct BatchGraph {
+    hipGraphExec_t exec = nullptr;
+    int ncodes = 0, code[kMaxCodes] = {}, begin[kMaxCodes + 1] = {};
+    int fin = -1, fin_v = -1, steps_nt = 0, steps_code = 0, steps_blocks = 0;
+};
+
 }  // namespace
 
 // One entry of the launch-variant table (written by paper_2307_08507_amd/tune.py): for cost
@@ -128,16 +143,14 @@ struct mdot_ctx {
     DevParams* h_prm = nullptr;   // pinned
     hipEvent_t ev[2] = {nullptr, nullptr};
     hipEvent_t t0 = nullptr, t1 = nullptr;
-    hipGraphExec_t graph = nullptr;  // captured chunk of solver steps for `main`
-    // what the graph was captured with: m, n and the sweep kernel instance (cost code, which also
-    // tells the point dimension classes apart)
-    int graph_m = 0, graph_n = 0, graph_code = -1, graph_steps = 0;
+    SoloGraph solo[2];  // captured chunks of solver steps for `main`: one-step kernels, resident steps
     // resident steps and sweeps: the GPU's compute units, the exchange memory, and whether a wait
     // inside them has ever run out
     int cus = 0;
     StepsX* d_steps = nullptr;
     StepsX* d_bsteps = nullptr;  // the same for the engine, one per item, from its first resident chunk on
     bool steps_off = false;
+    Backoff solo_backoff, lse_backoff, eng_backoff;  // attempts at resident kernels on a shared GPU
     // serving engine
     hipStream_t side = nullptr;     // intake of admitted solves (does not wait for the chunk in flight)
     Slot slots[kMaxBatch];
@@ -151,15 +164,9 @@ struct mdot_ctx {
     int hb_cur = 0;                 // buffer holding the current descriptor
     BatchDesc* d_batch = nullptr;
     bool batch_dirty = true;
-    hipGraphExec_t bgraph = nullptr;
+    BatchGraph bgraph[2];  // captured chunks of engine steps: one-step kernels, resident steps
     // replaced batch graphs, destroyed once the last chunk launched from them has been read back
     std::vector<std::pair<hipGraphExec_t, int64_t>> graveyard;
-    // what the batch graph was captured with: its sweep instances and their tile ranges, the
-    // finalize grid and finalize instance, the resident steps' instance and grid
-    int bgraph_ncodes = 0, bgraph_code[kMaxCodes] = {}, bgraph_begin[kMaxCodes + 1] = {};
-    int bgraph_fin = -1;
-    int bgraph_fin_v = -1;
-    int bgraph_steps_nt = 0, bgraph_steps_code = 0, bgraph_steps_blocks = 0;
     int batch_fin_v = kFinSmall;  // the finalize instance the batch needs (fin_instance)
     // engine chunks in flight: the next chunk is launched before the previous one's done flags
     // are read; each remembers the slots and tickets it advanced, in descriptor order
@@ -258,10 +265,9 @@ static int ensure_workspace(mdot_ctx* ctx, ProblemBufs& pb, int m, int n, hipStr
         pb.ws_bytes = 0;
         pb.cap_n = 0;
     }
-    if (ctx->graph) {  // the captured graph may reference the old sizes
-        (void)hipGraphExecDestroy(ctx->graph);
-        ctx->graph = nullptr;
-        ctx->graph_m = ctx->graph_n = 0;
+    for (SoloGraph& g : ctx->solo) {  // the captured graphs may reference the old sizes
+        if (g.exec) (void)hipGraphExecDestroy(g.exec);
+        g = SoloGraph{};
     }
     hipError_t e = hipMalloc(&pb.ws, need);
     if (e != hipSuccess) {
@@ -629,15 +635,16 @@ static int steps_mode(const mdot_ctx* ctx, const mdot_params& prm)
     return nt ? nt + (prm.gamma_f > 0.0 ? 8 : 0) : 0;
 }
 
+// The chunk of steps of this kind, in ctx->solo[steps != 0].
 static int ensure_graph(mdot_ctx* ctx, int steps)
 {
     const Work& hw = ctx->main.host_work;
     const int code = cost_code(hw);
-    if (ctx->graph && ctx->graph_m == hw.m && ctx->graph_n == hw.n && ctx->graph_code == code && ctx->graph_steps == steps)
-        return MDOT_OK;
-    if (ctx->graph) {
-        (void)hipGraphExecDestroy(ctx->graph);
-        ctx->graph = nullptr;
+    SoloGraph& sg = ctx->solo[steps != 0];
+    if (sg.exec && sg.m == hw.m && sg.n == hw.n && sg.code == code && sg.steps == steps) return MDOT_OK;
+    if (sg.exec) {
+        (void)hipGraphExecDestroy(sg.exec);
+        sg.exec = nullptr;
     }
     hipStream_t cap;
     HIPCHK(ctx, hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
@@ -657,20 +664,20 @@ static int ensure_graph(mdot_ctx* ctx, int steps)
         } else {
             for (int k = 0; k < kChunk; ++k) bad |= launch_step(hw, wd, k & 1, cap);
         }
-        bad |= launch_chunk_done(wd, ctx->d_hdone, ctx->d_seq, cap);
+        bad |= launch_chunk_done(wd, steps ? ctx->d_steps : nullptr, ctx->d_hdone, ctx->d_seq, cap);
         e = hipStreamEndCapture(cap, &g);
     }
-    if (e == hipSuccess && !bad) e = hipGraphInstantiate(&ctx->graph, g, nullptr, nullptr, 0);
+    if (e == hipSuccess && !bad) e = hipGraphInstantiate(&sg.exec, g, nullptr, nullptr, 0);
     if (g) (void)hipGraphDestroy(g);
     (void)hipStreamDestroy(cap);
     if (e != hipSuccess || bad) {
-        ctx->graph = nullptr;
+        sg.exec = nullptr;
         return fail(ctx, MDOT_E_DEVICE, "graph capture failed: %s", hipGetErrorString(e));
     }
-    ctx->graph_m = hw.m;
-    ctx->graph_n = hw.n;
-    ctx->graph_code = code;
-    ctx->graph_steps = steps;
+    sg.m = hw.m;
+    sg.n = hw.n;
+    sg.code = code;
+    sg.steps = steps;
     return MDOT_OK;
 }
 
@@ -678,26 +685,30 @@ static int ensure_graph(mdot_ctx* ctx, int steps)
 static int run_steps(mdot_ctx* ctx, const mdot_params& prm, int64_t max_steps)
 {
     const int steps = steps_mode(ctx, prm);
-    int rc = ensure_graph(ctx, steps);
-    if (rc) return rc;
     const int per_chunk = steps ? kResidentRounds * kResidentSingles : kChunk;  // the least a chunk advances
     const int max_chunks = (int)std::min<int64_t>(max_steps / per_chunk + 1, 1 << 30);
     // slot 0 holds the newest state after an even chunk; the graph's last kernel copies its
     // done flag to h_done[chunk number & 1]
     const uint64_t base = ctx->solo_seq;
     int launched = 0, checked = 0;
+    bool resident[2] = {false, false};
     for (;;) {
         while (launched < checked + 2 && launched < max_chunks) {
-            HIPCHK(ctx, hipGraphLaunch(ctx->graph, ctx->stream));
+            const bool res = resident[launched & 1] = steps && ctx->solo_backoff.resident();
+            int rc = ensure_graph(ctx, res ? steps : 0);
+            if (rc) return rc;
+            HIPCHK(ctx, hipGraphLaunch(ctx->solo[res].exec, ctx->stream));
             HIPCHK(ctx, hipEventRecord(ctx->ev[launched & 1], ctx->stream));
             ++launched;
             ++ctx->solo_seq;
         }
         if (checked == launched) break;
         HIPCHK(ctx, hipEventSynchronize(ctx->ev[checked & 1]));
-        const int done = ctx->h_done[(base + checked) & 1];
+        const int flag = ctx->h_done[(base + checked) & 1];
+        if (flag & kChunkMissed) ctx->solo_backoff.missed();
+        else if (resident[checked & 1]) ctx->solo_backoff.met();
         ++checked;
-        if (done) break;
+        if (flag & ~kChunkMissed) break;
     }
     uint32_t* aborted = reinterpret_cast<uint32_t*>(ctx->h_state + 1);
     *aborted = 0;
@@ -824,20 +835,21 @@ static int rebuild_batch(mdot_ctx* ctx)
 // problems in flight, one sweep launch per kernel instance, so it is captured again whenever
 // the instances, their tile ranges or the totals change (admissions and completions, between
 // chunks).
-static int ensure_batch_graph(mdot_ctx* ctx)
+static int ensure_batch_graph(mdot_ctx* ctx, bool resident)
 {
     const BatchDesc& hb = *ctx->h_batch[ctx->hb_cur];
     const int fin = std::max(1, hb.total_fin);
     const int fin_v = ctx->batch_fin_v;
-    bool same = ctx->bgraph && ctx->bgraph_ncodes == hb.ncodes && ctx->bgraph_fin == fin && ctx->bgraph_fin_v == fin_v &&
-                ctx->bgraph_steps_nt == hb.steps_nt && ctx->bgraph_steps_blocks == hb.steps_prefix[hb.nitems] &&
-                ctx->bgraph_steps_code == hb.steps_code;
+    BatchGraph& bg = ctx->bgraph[resident];
+    bool same = bg.exec && bg.ncodes == hb.ncodes && bg.fin == fin && bg.fin_v == fin_v &&
+                (!resident || (bg.steps_nt == hb.steps_nt && bg.steps_blocks == hb.steps_prefix[hb.nitems] &&
+                               bg.steps_code == hb.steps_code));
     for (int c = 0; same && c < hb.ncodes; ++c)
-        same = ctx->bgraph_code[c] == hb.code[c] && ctx->bgraph_begin[c + 1] == hb.code_begin[c + 1];
+        same = bg.code[c] == hb.code[c] && bg.begin[c + 1] == hb.code_begin[c + 1];
     if (same) return MDOT_OK;
-    if (ctx->bgraph) {  // a chunk launched from it may still run: destroy it once that is read back
-        ctx->graveyard.emplace_back(ctx->bgraph, ctx->eng_seq);
-        ctx->bgraph = nullptr;
+    if (bg.exec) {  // a chunk launched from it may still run: destroy it once that is read back
+        ctx->graveyard.emplace_back(bg.exec, ctx->eng_seq);
+        bg.exec = nullptr;
     }
     hipStream_t cap;
     HIPCHK(ctx, hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
@@ -846,30 +858,30 @@ static int ensure_batch_graph(mdot_ctx* ctx)
     hipError_t e = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
         // resident: as many steps as a stage allows, then Round's two sweeps where its end has come
-        if (hb.steps_nt) bad |= launch_steps_batch(hb, ctx->d_batch, ctx->d_bsteps, kBatchResident, cap);
-        for (int k = 0; k < (hb.steps_nt ? kResidentSingles : kBatchChunk); ++k)
+        if (resident) bad |= launch_steps_batch(hb, ctx->d_batch, ctx->d_bsteps, kBatchResident, cap);
+        for (int k = 0; k < (resident ? kResidentSingles : kBatchChunk); ++k)
             bad |= launch_step_batch(hb, ctx->d_batch, k & 1, fin, fin_v, cap);
-        launch_gather_done(ctx->d_batch, ctx->d_hdone + 2, ctx->d_seq + 1, cap);
+        bad |= launch_gather_done(ctx->d_batch, resident ? ctx->d_bsteps : nullptr, ctx->d_hdone + 2, ctx->d_seq + 1, cap);
         e = hipStreamEndCapture(cap, &g);
     }
     if (e == hipSuccess && bad) e = hipErrorLaunchFailure;
-    if (e == hipSuccess) e = hipGraphInstantiate(&ctx->bgraph, g, nullptr, nullptr, 0);
+    if (e == hipSuccess) e = hipGraphInstantiate(&bg.exec, g, nullptr, nullptr, 0);
     if (g) (void)hipGraphDestroy(g);
     (void)hipStreamDestroy(cap);
     if (e != hipSuccess) {
-        ctx->bgraph = nullptr;
+        bg.exec = nullptr;
         return fail(ctx, MDOT_E_DEVICE, "batch graph capture failed: %s", hipGetErrorString(e));
     }
-    ctx->bgraph_ncodes = hb.ncodes;
+    bg.ncodes = hb.ncodes;
     for (int c = 0; c < hb.ncodes; ++c) {
-        ctx->bgraph_code[c] = hb.code[c];
-        ctx->bgraph_begin[c + 1] = hb.code_begin[c + 1];
+        bg.code[c] = hb.code[c];
+        bg.begin[c + 1] = hb.code_begin[c + 1];
     }
-    ctx->bgraph_fin = fin;
-    ctx->bgraph_fin_v = fin_v;
-    ctx->bgraph_steps_nt = hb.steps_nt;
-    ctx->bgraph_steps_code = hb.steps_code;
-    ctx->bgraph_steps_blocks = hb.steps_prefix[hb.nitems];
+    bg.fin = fin;
+    bg.fin_v = fin_v;
+    bg.steps_nt = hb.steps_nt;
+    bg.steps_code = hb.steps_code;
+    bg.steps_blocks = hb.steps_prefix[hb.nitems];
     return MDOT_OK;
 }
 
@@ -1055,8 +1067,10 @@ int mdot_ctx_destroy(mdot_ctx* ctx)
     if (ctx->stream) (void)hipStreamSynchronize(ctx->stream);
     else (void)hipDeviceSynchronize();
     if (ctx->side) (void)hipStreamSynchronize(ctx->side);
-    if (ctx->graph) (void)hipGraphExecDestroy(ctx->graph);
-    if (ctx->bgraph) (void)hipGraphExecDestroy(ctx->bgraph);
+    for (SoloGraph& g : ctx->solo)
+        if (g.exec) (void)hipGraphExecDestroy(g.exec);
+    for (BatchGraph& g : ctx->bgraph)
+        if (g.exec) (void)hipGraphExecDestroy(g.exec);
     for (auto& g : ctx->graveyard) (void)hipGraphExecDestroy(g.first);
     free_bufs(ctx->main);
     for (auto& sl : ctx->slots)
@@ -1194,7 +1208,7 @@ static int run_alone(mdot_ctx* ctx, ProblemBufs& pb, const mdot_cost_desc* cost,
     volatile AloneOut* hout = reinterpret_cast<volatile AloneOut*>(ctx->h_done + kDoneInts);
     const Work* hw = &w;
     const int nt = (round || !lr_out || ctx->steps_off) ? 0 : steps_tiles(&hw, 1, ctx->cus);
-    if (lse_resident(nt)) {
+    if (lse_resident(nt) && ctx->lse_backoff.resident()) {
         LseArgs A;
         A.w = w;
         A.in = vec;
@@ -1208,6 +1222,8 @@ static int run_alone(mdot_ctx* ctx, ProblemBufs& pb, const mdot_cost_desc* cost,
         hout->retry = 0;
         if (launch_lse(A, ctx->d_steps, nt, st)) return fail(ctx, MDOT_E_DEVICE, "standalone sweep launch failed");
         HIPCHK(ctx, hipStreamSynchronize(st));
+        if (hout->done) ctx->lse_backoff.met();
+        else ctx->lse_backoff.missed();
         if (hout->retry) {  // a wait ran out: the kernels from here on, if the inputs are as they were
             ctx->steps_off = true;
             auto in_outputs = [&](const double* p, int k) {
@@ -1538,8 +1554,15 @@ static int process_chunk(mdot_ctx* ctx, int buf)
 {
     HIPCHK(ctx, hipEventSynchronize(ctx->eng_ev[buf]));
     bury_graphs(ctx, ctx->chunk_seq[buf]);
-    const int* done = ctx->h_done + 2 + buf * kMaxBatch;
-    const int* steps = done + 2 * kMaxBatch;
+    const int* flags = ctx->h_done + 2 + buf * kMaxBatch;
+    const int* steps = flags + 2 * kMaxBatch;
+    int done[kMaxBatch], missed = 0;
+    for (int m = 0; m < ctx->chunk_m[buf]; ++m) {
+        done[m] = flags[m] & ~kChunkMissed;
+        missed |= flags[m] & kChunkMissed;
+    }
+    if (missed) ctx->eng_backoff.missed();
+    else if (ctx->chunk_resident[buf]) ctx->eng_backoff.met();
     for (int m = 0; m < ctx->chunk_m[buf]; ++m) {
         Slot& sl = ctx->slots[ctx->chunk_slot[buf][m]];
         if (!sl.used || sl.ticket != ctx->chunk_ticket[buf][m]) continue;
@@ -1602,7 +1625,8 @@ int mdot_run(mdot_ctx* ctx, int steps, int* n_done)
                 rc = rebuild_batch(ctx);
                 if (rc) return rc;
             }
-            rc = ensure_batch_graph(ctx);
+            const bool resident = ctx->h_batch[ctx->hb_cur]->steps_nt && ctx->eng_backoff.resident();
+            rc = ensure_batch_graph(ctx, resident);
             if (rc) return rc;
             const int buf = ctx->eng_next;
             int m = 0;
@@ -1613,11 +1637,11 @@ int mdot_run(mdot_ctx* ctx, int steps, int* n_done)
                 ++m;
             }
             ctx->chunk_m[buf] = m;
-            ctx->chunk_resident[buf] = ctx->bgraph_steps_nt != 0;
+            ctx->chunk_resident[buf] = resident;
             ctx->chunk_seq[buf] = ++ctx->eng_seq;
             // the graph's last kernel writes this chunk's done flags to host buffer `buf` (engine
             // chunks alternate buffers in launch order, as the device counter does)
-            HIPCHK(ctx, hipGraphLaunch(ctx->bgraph, ctx->stream));
+            HIPCHK(ctx, hipGraphLaunch(ctx->bgraph[resident].exec, ctx->stream));
             HIPCHK(ctx, hipEventRecord(ctx->eng_ev[buf], ctx->stream));
             if (ctx->eng_pending >= 0) {
                 rc = process_chunk(ctx, ctx->eng_pending);

@@ -225,6 +225,28 @@ constexpr bool range_valid(double scale, double lo, double hi)
 constexpr uint32_t kWaitFlag = 1024;
 constexpr uint32_t kWaitLooks = 1u << 23;
 
+// Whether the next chunk (or standalone LSE) is a resident one. Where the workgroups of one could not
+// meet, because the GPU is shared, the one-step kernels run the next kFirst chunks, and twice as many
+// after each further attempt that fails. An attempt costs up to 50 us, so beside a stream that keeps the
+// compute units busy for good it is seldom made. n = 4096 FP32 schedule of 78 sweeps beside a stream of
+// cumulative sums: 3.7 ms by the one-step kernels, 17 to 22 ms with an attempt before every two steps.
+struct Backoff {
+    static constexpr int kFirst = 2, kMost = 16;
+    int left = 0, len = 0;
+    constexpr bool resident()
+    {
+        if (left == 0) return true;
+        --left;
+        return false;
+    }
+    constexpr void met() { len = 0; }
+    constexpr void missed()
+    {
+        len = len == 0 ? kFirst : (2 * len < kMost ? 2 * len : kMost);
+        left = len;
+    }
+};
+
 // Exchange memory of the resident-steps kernel (k_steps), in device memory: zeroed once.
 constexpr int kStepsMaxGrid = 256;      // workgroups
 constexpr int kStepsMaxRowTiles = 128;  // row tiles (8192 rows)
@@ -232,6 +254,7 @@ struct StepsX {
     uint32_t arrive, pad0[31];  // workgroups that have started (kStepsAbort: start given up)
     uint32_t leave, pad1[31];   // workgroups that have ended; the last one clears both
     uint32_t abort, pad2[31];   // a wait inside the steps ran into its limit (never cleared)
+    uint32_t skip, pad3[31];    // the workgroups could not meet: no further attempt in this chunk
     double shift[3][kStepsMaxRowTiles];   // S_I of the row tiles, three steps in turn
     double dots[3][kStepsMaxGrid][16];    // dots of the finalize blocks, one 128-byte line each
     double range[4 * kStepsMaxGrid][2];   // standalone LSE: raw cost range of the tiles
@@ -374,8 +397,10 @@ int cost_code(const Work& hw);
 int launch_step_batch(const BatchDesc& hb, const BatchDesc* bd, int parity, int fin_grid, int fin_v, void* stream);
 // End-of-chunk done flags into host-visible memory: chunk number *seq (a device counter, advanced
 // here) writes out[(seq & 1) * kMaxBatch + item] (batch, and the steps the solve has taken so far
-// 2 kMaxBatch entries behind) or out[seq & 1] (single problem).
-int launch_gather_done(const BatchDesc* bd, int* out, int* seq, void* stream);
-int launch_chunk_done(const Work* wd, int* out, int* seq, void* stream);
+// 2 kMaxBatch entries behind) or out[seq & 1] (single problem). kChunkMissed is added where the
+// workgroups of resident steps (x, null in a chunk of one-step kernels) could not meet.
+constexpr int kChunkMissed = 256;
+int launch_gather_done(const BatchDesc* bd, StepsX* x, int* out, int* seq, void* stream);
+int launch_chunk_done(const Work* wd, StepsX* x, int* out, int* seq, void* stream);
 
 }  // namespace mdot

@@ -2543,13 +2543,15 @@ __device__ __forceinline__ bool steps_meet(const StepSize& z, StepsX* x)
     __hip_atomic_fetch_add(&x->arrive, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return steps_wait_all(z, x);
 }
-// The last workgroup to end clears both counts for the next kernel.
-__device__ __forceinline__ void steps_leave(const StepSize& z, StepsX* x)
+// The last workgroup to end clears both counts for the next kernel, and notes a meeting that failed (not
+// before: a workgroup that starts late must not find the note and leave without being counted).
+__device__ __forceinline__ void steps_leave(const StepSize& z, StepsX* x, bool missed = false)
 {
     if (threadIdx.x == 0 &&
         __hip_atomic_fetch_add(&x->leave, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == (uint32_t)z.nblk) {
         xstore(&x->leave, 0u);
         xstore(&x->arrive, 0u);
+        if (missed) xstore(&x->skip, 1u);
     }
 }
 
@@ -2965,7 +2967,7 @@ __global__ void __launch_bounds__(256 * NQ) k_steps(const Work* __restrict__ wp,
         x += item;
     }
     State* const S0 = state_slot(*wp, 0);
-    if (!steps_go(*S0)) return;  // the same in every workgroup
+    if (!steps_go(*S0) || x->skip) return;  // the same in every workgroup
 
     // Work never changes while a kernel runs. Said so, its fields are read as scalars, which the
     // compiler otherwise gives up for a pointer that comes out of memory (+40 registers).
@@ -3091,7 +3093,7 @@ __global__ void __launch_bounds__(256 * NQ) k_steps(const Work* __restrict__ wp,
             }
         }
     }
-    steps_leave(z, x);
+    steps_leave(z, x, !started);
 }
 
 // ------------------------------------------------------------------ resident standalone LSE
@@ -3461,26 +3463,34 @@ __global__ void __launch_bounds__(kDecideWG) k_settle_batch(const BatchDesc* __r
     }
 }
 
+// kChunkMissed if a meeting failed in this chunk; the next one may try again.
+__device__ __forceinline__ int chunk_missed(StepsX* x)
+{
+    if (!x || !x->skip) return 0;
+    x->skip = 0;
+    return kChunkMissed;
+}
+
 // End-of-chunk done flags and step counts, written straight into pinned host memory (a stream-ordered copy
 // between chunks would stall the stream for tens of microseconds). The chunk counter *seq,
 // kept on the device, picks the host buffer: chunk s writes buffer s & 1, so the chunk queued
 // behind it never overwrites flags the host has not read yet.
-__global__ void k_gather_done(const BatchDesc* __restrict__ bd, int* out, int* seq)
+__global__ void k_gather_done(const BatchDesc* __restrict__ bd, StepsX* x, int* out, int* seq)
 {
     const int b = threadIdx.x;  // one wave: every lane reads the counter before lane 0 advances it
     const int s = *seq;
     if (b < bd->nitems) {
         const State& S = bd->items[b]->st[0];
-        out[(s & 1) * kMaxBatch + b] = S.done;
+        out[(s & 1) * kMaxBatch + b] = S.done + chunk_missed(x ? x + b : nullptr);
         out[(2 + (s & 1)) * kMaxBatch + b] = (int)(S.sweeps + S.fallbacks + S.cert_sweeps);
     }
     if (b == 0) *seq = s + 1;
 }
 
-__global__ void k_chunk_done(const Work* __restrict__ wp, int* out, int* seq)
+__global__ void k_chunk_done(const Work* __restrict__ wp, StepsX* x, int* out, int* seq)
 {
     const int s = *seq;
-    out[s & 1] = ctl_of(*wp).st[0].done;
+    out[s & 1] = ctl_of(*wp).st[0].done + chunk_missed(x);
     *seq = s + 1;
 }
 
@@ -4249,15 +4259,15 @@ int launch_step_batch(const BatchDesc& hb, const BatchDesc* bd, int parity, int 
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-int launch_gather_done(const BatchDesc* bd, int* out, int* seq, void* stream)
+int launch_gather_done(const BatchDesc* bd, StepsX* x, int* out, int* seq, void* stream)
 {
-    hipLaunchKernelGGL(k_gather_done, dim3(1), dim3(kMaxBatch), 0, (hipStream_t)stream, bd, out, seq);
+    hipLaunchKernelGGL(k_gather_done, dim3(1), dim3(kMaxBatch), 0, (hipStream_t)stream, bd, x, out, seq);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-int launch_chunk_done(const Work* wd, int* out, int* seq, void* stream)
+int launch_chunk_done(const Work* wd, StepsX* x, int* out, int* seq, void* stream)
 {
-    hipLaunchKernelGGL(k_chunk_done, dim3(1), dim3(1), 0, (hipStream_t)stream, wd, out, seq);
+    hipLaunchKernelGGL(k_chunk_done, dim3(1), dim3(1), 0, (hipStream_t)stream, wd, x, out, seq);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
