@@ -37,7 +37,11 @@ constexpr int kChunk = 32;       // solver steps per graph launch (even: the sta
 constexpr int kResidentRounds = 3;    // rounds per graph launch: resident steps (once, or in schedule
 constexpr int kResidentRuns = 3;      // mode, where stages follow each other, so often), then two
 constexpr int kResidentSingles = 2;   // single steps (an even number: Round's two sweeps)
-constexpr int kResidentMax = 4096;    // steps of one resident launch (tens of milliseconds)
+// Steps of one resident launch. It leaves other streams no room on its compute units for kernels that need
+// much LDS: 256 steps are 2 ms at n = 256, 4 ms at n = 4096 FP32 and 8 ms in FP64, where a stage of tight
+// gaps may take thousands. Solves of n = 4096 to gap 1e-6 (135 sweeps a stage): 86.0 ms without a limit,
+// 86.3 with 512 steps, 86.7 with 256, 87.7 with 128.
+constexpr int kResidentMax = 256;
 constexpr int kBatchChunk = 16;  // engine steps per graph launch (admission granularity, even)
 // Where all solves in flight take resident steps, a chunk is at most this many of them (the solves
 // wait for the slowest) and the single steps: about as long as kBatchChunk steps of three kernels.

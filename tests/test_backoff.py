@@ -1,6 +1,7 @@
 """When resident kernels are attempted on a shared GPU (Backoff in mdot_internal.h), on the CPU: a program
 built from the header plays chunks whose attempts succeed or fail."""
 import os
+import re
 import subprocess
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -56,3 +57,9 @@ def test_attempts_are_seldom_made_where_they_fail(tmp_path):
     assert 10000 // 17 <= tries <= 10000 // 17 + 8 and gap == 17
     assert out[2][0] <= 16
     assert out[3] == (100, 2)
+
+
+def test_a_resident_launch_ends_within_milliseconds():
+    src = open(os.path.join(ROOT, "paper_2307_08507_amd", "csrc", "mdot_api.cpp")).read()
+    steps = int(re.search(r"kResidentMax = (\d+);", src).group(1))
+    assert steps * 33e-6 < 10e-3  # at the slowest step, n = 4096 in FP64
