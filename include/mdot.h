@@ -147,7 +147,8 @@ typedef struct mdot_ctx mdot_ctx;
 
 /* Create a context on HIP device `device`, issuing work on `hip_stream` (a hipStream_t,
  * NULL = the default stream). hbm_budget_bytes bounds the workspace the context may hold
- * (0 = no bound). Returns MDOT_OK, MDOT_E_ARG or MDOT_E_DEVICE. */
+ * for submitted solves (0 = no bound), with 7.6 MB through which solves in flight together exchange
+ * values where the budget has room for them (they only make such solves faster). Returns MDOT_OK, MDOT_E_ARG or MDOT_E_DEVICE. */
 int mdot_ctx_create(int device, void* hip_stream, size_t hbm_budget_bytes, mdot_ctx** out);
 
 /* Free the context and its workspace. NULL is accepted. */

@@ -46,6 +46,7 @@ constexpr int kBatchChunk = 16;  // engine steps per graph launch (admission gra
 // Where all solves in flight take resident steps, a chunk is at most this many of them (the solves
 // wait for the slowest) and the single steps: about as long as kBatchChunk steps of three kernels.
 constexpr int kBatchResident = 30;
+constexpr size_t kEngineExchange = kMaxBatch * sizeof(StepsX);  // exchange memory of its resident chunks
 constexpr int kMaxN = MDOT_MAX_N;
 constexpr int kConvBlocks = 1024; // workgroups of the FP16 conversion (MIXED)
 constexpr int kDoneInts = 4 * kMaxBatch + 2;  // done flags and step counts in mapped host memory
@@ -732,6 +733,19 @@ static int read_state(mdot_ctx* ctx, const ProblemBufs& pb)
     return MDOT_OK;
 }
 
+static size_t pool_bytes(const mdot_ctx* ctx)
+{
+    size_t b = 0;
+    for (const ProblemBufs& pb : ctx->pool) b += bufs_bytes(pb);
+    return b;
+}
+
+// Device bytes the engine holds: what hbm_budget_bytes bounds.
+static size_t engine_bytes(const mdot_ctx* ctx)
+{
+    return ctx->bytes_in_use + pool_bytes(ctx) + (ctx->d_bsteps ? kEngineExchange : 0);
+}
+
 // ---------------------------------------------------------------- serving engine helpers
 static int rebuild_batch(mdot_ctx* ctx)
 {
@@ -814,9 +828,11 @@ static int rebuild_batch(mdot_ctx* ctx)
     B.grp_prefix[ng] = nt;
     B.total_tiles = nt;
     if (resident && m > 0) B.steps_nt = steps_tiles(hw, m, ctx->cus);
-    if (B.steps_nt && !ctx->d_bsteps) {
-        if (hipMalloc(&ctx->d_bsteps, kMaxBatch * sizeof(StepsX)) == hipSuccess) {
-            HIPCHK(ctx, hipMemsetAsync(ctx->d_bsteps, 0, kMaxBatch * sizeof(StepsX), ctx->stream));
+    if (B.steps_nt && !ctx->d_bsteps) {  // it counts against the budget; without it, the one-step kernels
+        if (ctx->budget && engine_bytes(ctx) + kEngineExchange > ctx->budget) {
+            B.steps_nt = 0;
+        } else if (hipMalloc(&ctx->d_bsteps, kEngineExchange) == hipSuccess) {
+            HIPCHK(ctx, hipMemsetAsync(ctx->d_bsteps, 0, kEngineExchange, ctx->stream));
         } else {
             (void)hipGetLastError();
             ctx->d_bsteps = nullptr;
@@ -889,6 +905,19 @@ static int ensure_batch_graph(mdot_ctx* ctx, bool resident)
     return MDOT_OK;
 }
 
+// Give the engine's exchange memory back (a request needs the room): the chunk in flight is waited for,
+// and the batch is described again, without resident steps where the budget has no room for them.
+static int free_exchange(mdot_ctx* ctx)
+{
+    HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+    if (ctx->bgraph[1].exec) (void)hipGraphExecDestroy(ctx->bgraph[1].exec);
+    ctx->bgraph[1] = BatchGraph{};
+    (void)hipFree(ctx->d_bsteps);
+    ctx->d_bsteps = nullptr;
+    ctx->batch_dirty = true;
+    return MDOT_OK;
+}
+
 // Destroy the replaced batch graphs whose last chunk has been read back (chunk `seq` and
 // everything launched before it have completed).
 static void bury_graphs(mdot_ctx* ctx, int64_t seq)
@@ -913,13 +942,6 @@ static void pool_put(mdot_ctx* ctx, const ProblemBufs& pb)
         free_bufs(*it);
         ctx->pool.erase(it);
     }
-}
-
-static size_t pool_bytes(const mdot_ctx* ctx)
-{
-    size_t b = 0;
-    for (const ProblemBufs& pb : ctx->pool) b += bufs_bytes(pb);
-    return b;
 }
 
 // Results of retiring solves whose state copies have completed (all of them with wait): the
@@ -1496,14 +1518,15 @@ int mdot_submit(mdot_ctx* ctx, const mdot_cost_desc* cost, const double* r, cons
         return best;
     };
     auto held_after = [&](int cand) {
-        const size_t held = ctx->bytes_in_use + pool_bytes(ctx);
+        const size_t held = engine_bytes(ctx);
         if (cand < 0) return held + fp;
         const ProblemBufs& pb = ctx->pool[cand];
         return held - bufs_bytes(pb) + sizeof(Control) + pb.ws_bytes + std::max(pb.proxy_bytes, proxy_need);
     };
     int best = pick();
     if (ctx->budget && held_after(best) > ctx->budget) {
-        // the pool is idle memory: free it (all but the candidate, then the candidate too) before refusing
+        // the pool is idle memory: free it (all but the candidate, then the candidate too) before refusing,
+        // and the resident chunks' exchange memory, which only makes them faster
         for (int k = (int)ctx->pool.size() - 1; k >= 0; --k) {
             if (k == best) continue;
             free_bufs(ctx->pool[k]);
@@ -1514,6 +1537,10 @@ int mdot_submit(mdot_ctx* ctx, const mdot_cost_desc* cost, const double* r, cons
             free_bufs(ctx->pool[best]);
             ctx->pool.erase(ctx->pool.begin() + best);
             best = -1;
+        }
+        if (held_after(best) > ctx->budget && ctx->d_bsteps) {
+            rc = free_exchange(ctx);
+            if (rc) return rc;
         }
         if (held_after(best) > ctx->budget)
             return fail(ctx, MDOT_E_BUSY, "HBM budget: %zu of %zu bytes in use, m=%d n=%d needs %zu",
