@@ -274,12 +274,14 @@ int mdot_bench_sweep_flushed(mdot_ctx* ctx, const mdot_cost_desc* cost, const do
 
 /* ---- Launch-variant tuning ----
  * The sweep kernel exists in variants that compute the same values bit for bit and differ only
- * in speed: capped at 4 waves per SIMD (128 VGPRs) or 2 (256 VGPRs), and, for FP32 costs, with or
- * without staging its second batch of cost rows in LDS. mdot_ctx_create reads the choice per
- * cost type and size from a table: the file named by the environment variable MDOT_TUNING, else
- * tuning.json in the directory above the one holding libmdot.so (written by the package's
- * tuner, tune.py, from measurements on the GPU); without a table every size uses 4 waves per
- * SIMD and staging above 2048 tiles.
+ * in speed: capped at 4 waves per SIMD (128 VGPRs) or 2 (256 VGPRs; clouds of more than 3
+ * coordinates only, elsewhere both are one kernel that fits the first cap), and, for FP32 costs,
+ * with or without staging its second batch of cost rows in LDS. (Solver steps that run inside one
+ * kernel, of problems of at most 1024 tiles of 64 x 256, have no variants.) mdot_ctx_create reads
+ * the choice per cost type and size from a table: the file named by the environment variable
+ * MDOT_TUNING, else tuning.json in the directory above the one holding libmdot.so (written by the
+ * package's tuner, tune.py, from measurements on the GPU); without a table every size uses 4 waves
+ * per SIMD (2 for clouds of more than 3 coordinates) and staging above 2048 tiles.
  *
  * mdot_tune_override: force a variant for the later calls on this context (the tuner uses it):
  * occ = 2 or 4 (0 = the table's), stage = 0 (never stage), 1 (always stage) or -1 (the

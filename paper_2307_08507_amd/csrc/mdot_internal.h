@@ -151,8 +151,9 @@ struct Work {
     int32_t fin_Lr, fin_lgLr, fin_nvbr;  // fin_lanes_r(m, n), log2 of it, fin_vblocks_r(m, n)
     int32_t fin_L, fin_lgL, fin_nvb, fin_nblk;  // fin_lanes_c(m, n), log2 of it, fin_vblocks(m, n), fin_grid(m, n)
     // launch variant from the tuning table (neither changes any arithmetic): occ2 = 1 runs the
-    // sweep instance capped at 2 waves per SIMD (256 VGPRs) instead of 4 (128 VGPRs); FP32 sweeps
-    // of more than stage_min_tiles tiles stage their second row batch in LDS
+    // sweep instance capped at 2 waves per SIMD (256 VGPRs) instead of 4 (128 VGPRs), where there
+    // are two (clouds of more than 3 coordinates); FP32 sweeps of more than stage_min_tiles tiles
+    // stage their second row batch in LDS
     int32_t occ2, stage_min_tiles;
     const void* cost;        // dense cost or coordinates X then Y
     double scale;            // C = scale * raw

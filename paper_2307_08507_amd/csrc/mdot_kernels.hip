@@ -1831,7 +1831,7 @@ __device__ __forceinline__ void sweep_tiles(const Work& w, const SweepArgs& a, c
     }
 }
 
-// Body of the sweep kernel for one tile. ROUND = false: LSE and max sweeps (the hot path);
+// Body of the sweep kernel for one tile. ROUND = false: LSE sweeps (the hot path);
 // ROUND = true: the two Round/certificate sweeps (twice per stage).
 template <int CC, bool ROUND>
 __device__ __forceinline__ void sweep_kernel_body(const Work& w, const SweepArgs& a, int mode, bool e64, int blk,
@@ -1843,11 +1843,10 @@ __device__ __forceinline__ void sweep_kernel_body(const Work& w, const SweepArgs
 }
 
 // One kernel for every sweep mode, so a step is a fixed sequence of launches. The register
-// cap keeps four workgroups per CU (the LDS limit is five): the LSE path needs 84 VGPRs, the
-// Round paths (twice per stage) spill a few values. Point-cost codes with kOccHi set are the
-// same kernel capped at two waves per SIMD (up to 256 VGPRs: their Round paths then need no
-// spills, at lower occupancy); the tuning table picks between them per cost type and size. The
-// dense instances fit the cap without spills, so their kOccHi codes launch the same kernel.
+// cap keeps four workgroups per CU (the LDS limit is five). Every instance but the 8-coordinate ones
+// fits it without spills (114 to 128 VGPRs), so their kOccHi codes launch the same kernel; the
+// 8-coordinate clouds spill some 190 values under it and have an instance capped at two waves per SIMD
+// (162 and 165 VGPRs, no spills), which they take unless the tuning table says otherwise.
 template <int CC>
 __device__ __forceinline__ void sweep_any(const Work& w, int parity, int blk, double* smem)
 {
@@ -4004,7 +4003,8 @@ int cost_code_dim(int cc, int d)
 }
 
 // Kernel instance of a launch: point clouds take the instance for their dimension, and the
-// tuning table's 2-waves-per-SIMD variant adds kOccHi.
+// tuning table's 2-waves-per-SIMD variant adds kOccHi (of the 8-coordinate instances the one without
+// spills; elsewhere the same kernel).
 int cost_code(const Work& w)
 {
     return cost_code_dim(cost_code_of(w.cost_kind, w.dtype), w.d) + (w.occ2 ? kOccHi : 0);
@@ -4040,11 +4040,11 @@ int cost_code(const Work& w)
         case kOccHi + CC_F32: F(CC_F32); break;                        \
         case kOccHi + CC_F16: F(CC_F16); break;                        \
         case kOccHi + CC_BF16: F(CC_BF16); break;                      \
-        case kOccHi + CC_PTS_SQ: F(kOccHi + CC_PTS_SQ); break;         \
-        case kOccHi + CC_PTS_SQ2: F(kOccHi + CC_PTS_SQ2); break;       \
-        case kOccHi + CC_PTS_L12: F(kOccHi + CC_PTS_L12); break;       \
+        case kOccHi + CC_PTS_SQ: F(CC_PTS_SQ); break;                  \
+        case kOccHi + CC_PTS_SQ2: F(CC_PTS_SQ2); break;                \
+        case kOccHi + CC_PTS_L12: F(CC_PTS_L12); break;                \
+        case kOccHi + CC_PTS_L1: F(CC_PTS_L1); break;                  \
         case kOccHi + CC_PTS_SQ8: F(kOccHi + CC_PTS_SQ8); break;       \
-        case kOccHi + CC_PTS_L1: F(kOccHi + CC_PTS_L1); break;         \
         default: F(kOccHi + CC_PTS_L18); break;                        \
     }
 
