@@ -255,7 +255,8 @@ int mdot_poll(mdot_ctx* ctx, uint64_t ticket, int wait, mdot_result* res);
 /* Number of solves in flight and the workspace bytes they hold (host pointers, may be NULL). */
 int mdot_inflight(mdot_ctx* ctx, int* n_active, size_t* bytes_in_use);
 
-/* Measurement hook: run the solver's fused LSE sweep kernel `iters` times back-to-back on the
+/* Measurement hook: run the fused LSE sweep kernel (which solves of more than 1024 tiles of 64 x 256
+ * run; smaller ones run its tiles inside the kernel of their steps) `iters` times back-to-back on the
  * context stream at the potentials (u, v) and gamma (shifts set to the exact log-sums first,
  * as in a line-search trial near the solution) and return the mean duration per sweep in
  * milliseconds, taken with HIP events on that stream. u, v: device FP64[m], FP64[n]; ms_per_sweep: host.

@@ -38,8 +38,11 @@ def build(verbose: bool = False) -> str:
             # kernel's first dependent load does not wait for a kernarg-segment fetch
             cmd += [f"--offload-arch={ARCH}", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
                     "-munsafe-fp-atomics", "-mllvm", "-amdgpu-kernarg-preload-count=16",
-                    # the constants of exp and log stay where they are used: hoisted out of the loop of
-                    # the resident-steps kernel they take 60 registers and spill
+                    # the constants of exp and log stay where they are used: hoisted out of the loops of
+                    # the resident kernels they take 30 to 80 registers and spill (k_steps on FP32 costs 256
+                    # and 21 to 28 spilled, now 220 to 225 and none; on clouds 128 and 26 to 46, now 108 to
+                    # 124 and none). k_fin falls from 232 and 256 registers to 194 and 226; sweeps keep
+                    # theirs within 3
                     "-mllvm", "-disable-machine-licm"]
         else:
             pass

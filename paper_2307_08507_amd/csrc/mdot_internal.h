@@ -334,9 +334,6 @@ constexpr size_t kNoAllocBytes = kNoAllocCtl + ws_offset(kWsBuffers, kNoAllocMax
 // Device address of that array on the current device (hipGetSymbolAddress, taken once per
 // device and cached). Returns 0 or a hipError_t code.
 int noalloc_scratch(int device, void** out);
-// Fill count doubles at dst with val (a kernel, so the fill is an ordinary kernel node if the
-// caller's stream is being captured).
-int launch_fill(double* dst, size_t count, double val, void* stream);
 // Read count doubles at src (cache eviction for cold-cache timing); sink[0] is written only if
 // their sum is -1.2345e300.
 int launch_touch(const double* src, size_t count, double* sink, void* stream);

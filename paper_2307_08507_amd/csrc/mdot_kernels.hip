@@ -108,9 +108,8 @@ __device__ __forceinline__ double wave_reduce(double v)
     v = red_op<OP>(v, dpp_d<0x143, 0xc>(id, v));
     return readlane_d(v, 63);
 }
-__device__ __forceinline__ double wave_sum(double v) { return wave_reduce<0>(v); }
 // N sums at once, stage by stage: the same operations in the same order per value as
-// wave_sum, with the independent chains interleaved (one after another they run at the
+// wave_reduce<0>, with the independent chains interleaved (one after another they run at the
 // latency of the DPP moves).
 template <int N>
 __device__ __forceinline__ void wave_sums(double v[N])
@@ -965,7 +964,7 @@ __device__ void tile_lse(const Work& w, const SweepArgs& S, const TileCtx& t, do
 // its LDS region (slot (quantity * B + row) at kRoundPad apart) and reduces them all at once, four
 // lanes per slot: one write and about three operations per row and quantity, where a reduction
 // across the lanes of each by itself takes 18. The sums are added in the same balanced tree over
-// the lanes as wave_sum. Returns slot (lane >> 2)'s value in all four of its lanes. With the rows'
+// the lanes as wave_reduce<0>. Returns slot (lane >> 2)'s value in all four of its lanes. With the rows'
 // loads issued four rows ahead as well, n = 4096 FP32: R1 41 -> 32 us, R2 47 -> 42.5 us. (With the
 // column values in registers, at 166 VGPRs and three waves per SIMD, R1 33.5 and R2 38 us, but the LSE
 // path shares the kernel and needs four.)
@@ -3577,7 +3576,7 @@ __device__ __forceinline__ bool box_settles(const double* box, int d, int kind, 
         const double t = fmax(fabs(xhi - ylo), fabs(yhi - xlo));
         s = kind == MDOT_COST_POINTS_SQEUCLID ? fma(t, t, s) : s + t;
     }
-    return scale * s <= 1.0;  // false for NaN (a non-finite coordinate makes its box NaN)
+    return scale * s <= 1.0;  // false for infinity (a non-finite coordinate makes its box infinite) and NaN
 }
 
 __global__ void __launch_bounds__(256) k_alone_setup(Control* __restrict__ ctl, Work w, State s, DevParams prm, AloneIn in,
@@ -4359,11 +4358,6 @@ int noalloc_scratch(int device, void** out)
     return 0;
 }
 
-__global__ void __launch_bounds__(256) k_fill(double* __restrict__ dst, size_t count, double val)
-{
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < count; i += (size_t)gridDim.x * 256) dst[i] = val;
-}
-
 // Read `count` doubles (used to evict a matrix from the L2 and last-level caches between timed
 // sweeps by filling them with other, clean lines); the sum is stored only if it equals `never`,
 // which keeps the loads without writing anything in practice.
@@ -4379,14 +4373,6 @@ int launch_touch(const double* src, size_t count, double* sink, void* stream)
 {
     if (count == 0) return 0;
     hipLaunchKernelGGL(k_touch, dim3(4096), dim3(256), 0, (hipStream_t)stream, src, count, -1.2345e300, sink);
-    return hipGetLastError() == hipSuccess ? 0 : -1;
-}
-
-int launch_fill(double* dst, size_t count, double val, void* stream)
-{
-    if (count == 0) return 0;
-    const size_t blocks = std::min<size_t>((count + 255) / 256, 1024);
-    hipLaunchKernelGGL(k_fill, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, dst, count, val);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
