@@ -1621,19 +1621,18 @@ static int process_chunk(mdot_ctx* ctx, int buf)
     return MDOT_OK;
 }
 
-int mdot_run(mdot_ctx* ctx, int steps, int* n_done)
+// Launch `chunks` engine chunks (with make_up: until every solve in flight has their steps) and retire the
+// solves finished by the chunks read back meanwhile.
+static int advance(mdot_ctx* ctx, int chunks, bool make_up, int* n_done)
 {
-    if (!ctx) return MDOT_E_ARG;
-    if (n_done) *n_done = 0;
     HIPCHK(ctx, hipSetDevice(ctx->device));
     int completed = 0;
     int rc = collect_retired(ctx, false, &completed);
     if (rc) return rc;
-    const int chunks = std::max(1, (steps + kBatchChunk - 1) / kBatchChunk);
     // A resident chunk is short of its steps where a stage ends early, and past them where none does.
     // The chunk in flight counts as kBatchChunk steps until it is read back; chunks are launched until
     // no solve is behind the steps asked for, at most so many that their single steps alone would do.
-    constexpr int kMost = kBatchChunk / kResidentSingles;
+    const int64_t most = make_up ? (int64_t)(kBatchChunk / kResidentSingles) * chunks : chunks;
     int64_t due[kMaxBatch];
     for (int s = 0; s < kMaxBatch; ++s) {
         const Slot& sl = ctx->slots[s];
@@ -1650,7 +1649,7 @@ int mdot_run(mdot_ctx* ctx, int steps, int* n_done)
             behind |= ctx->slots[s].used && ctx->slots[s].taken + kBatchChunk < due[s];
         }
         if (active == 0 && ctx->eng_pending < 0) break;
-        if (ch > 0 && (active > 0 ? !behind || ch >= (int64_t)kMost * chunks : ch >= chunks)) break;
+        if (ch > 0 && (active > 0 ? !behind || ch >= most : ch >= chunks)) break;
         if (active > 0) {  // launch the next chunk before reading the previous one back
             if (ctx->batch_dirty) {
                 rc = rebuild_batch(ctx);
@@ -1695,9 +1694,17 @@ int mdot_run(mdot_ctx* ctx, int steps, int* n_done)
     return MDOT_OK;
 }
 
+int mdot_run(mdot_ctx* ctx, int steps, int* n_done)
+{
+    if (!ctx) return MDOT_E_ARG;
+    if (n_done) *n_done = 0;
+    return advance(ctx, std::max(1, (steps + kBatchChunk - 1) / kBatchChunk), true, n_done);
+}
+
 int mdot_poll(mdot_ctx* ctx, uint64_t ticket, int wait, mdot_result* res)
 {
     if (!ctx) return MDOT_E_ARG;
+    bool queued = false;
     for (;;) {
         auto it = ctx->finished.find(ticket);
         if (it != ctx->finished.end()) {
@@ -1709,6 +1716,16 @@ int mdot_poll(mdot_ctx* ctx, uint64_t ticket, int wait, mdot_result* res)
         for (const Retiring& x : ctx->retiring)
             if (x.ticket == ticket) rt = &x;
         if (rt) {  // finished: its result lands with the copy queued at its retirement
+            bool others = false;
+            for (const Slot& sl : ctx->slots) others |= sl.used;
+            if (wait && others && !queued) {
+                // that copy is queued behind the chunk in flight: the others' next one is launched before
+                // it is waited for, or the GPU is idle until the caller's next call has captured it
+                queued = true;
+                int rc = advance(ctx, 1, false, nullptr);
+                if (rc) return rc;
+                continue;
+            }
             if (wait) HIPCHK(ctx, hipEventSynchronize(ctx->ret_ev[rt->hs]));
             int rc = collect_retired(ctx, false, nullptr);
             if (rc) return rc;
