@@ -3178,13 +3178,6 @@ __device__ __forceinline__ void lse_range(StepsX* x, StepsShared<NT>& sh, int nt
     *hi = bad ? NAN : b;
 }
 
-// The end of a workgroup whose wait ran out.
-__device__ __forceinline__ void lse_give_up(const StepSize& z, StepsX* x, AloneOut* out)
-{
-    if (threadIdx.x == 0) out->retry = 1;
-    steps_leave(z, x);
-}
-
 template <int CC, int NQ, int TP>
 __global__ void __launch_bounds__(256 * NQ) k_lse(LseArgs A, StepsX* __restrict__ x)
 {
@@ -3351,10 +3344,11 @@ __global__ void __launch_bounds__(256 * NQ) k_lse(LseArgs A, StepsX* __restrict_
             if (f.own && f.row) sh.flz[me.t] = A.in.shift ? plain_nan(A.in.shift[f.k]) : lse_shift(w, z, f.k, wait);
         }
         // ---- tile set-up (steps_update with z = (u, v), p = 0)
-        if (__syncthreads_or(wait.dead)) {
-            lse_give_up(z, x, A.out);
-            return;
-        }
+        // a wait that ran out ends the workgroup's part: it publishes nothing from here on (the flag is set
+        // again only behind the barriers of a sweep)
+        if (wait.dead) sh.dead = 1;
+        __syncthreads();
+        bool e64 = A.e64 != 0, any = false, more = !sh.dead;
 #pragma unroll
         for (int u = 0; u < TP; ++u) {
             const Lane me;
@@ -3369,34 +3363,32 @@ __global__ void __launch_bounds__(256 * NQ) k_lse(LseArgs A, StepsX* __restrict_
         }
         __syncthreads();
         // ---- sweep, at most twice
-        bool e64 = A.e64 != 0, any = false;
-        for (int b = 0;; ++b) {
+        for (int b = 0; more; ++b) {
             steps_sweep<Cost, NQ, TP>(sh, x, t, cost.c, raw, g2, e64, b);
             if (fin_wg) steps_finalize<true>(z, x, sh, b, e64, wait);
             StepDots dots;
             dots.ask(z, x, b);
             dots.take(z, x, sh, b, wait);
-            if (__syncthreads_or(wait.dead)) {
-                lse_give_up(z, x, A.out);
-                return;
-            }
+            if (wait.dead) sh.dead = 1;
+            __syncthreads();
             any = false;
             for (int i = threadIdx.x; i < z.nvb; i += blockDim.x) any |= sh.y[kStepDots][i] != 0.0;
             any = __syncthreads_or(any);
-            if (!any || e64) break;
+            more = any && !e64 && !sh.dead;
             e64 = true;
         }
         // ---- outputs, if every entry of the scaled cost lies in [0, 1]
-        if (fin_wg || z.blk == 0) {
+        if ((fin_wg || z.blk == 0) && !sh.dead) {
             double lo, hi;
             lse_range(x, sh, ntiles, NQ, wait, &lo, &hi);
-            const bool dead = __syncthreads_or(wait.dead), valid = range_valid(scale, lo, hi);
+            if (wait.dead) sh.dead = 1;
+            __syncthreads();
+            const bool dead = sh.dead != 0, valid = range_valid(scale, lo, hi);
             if (fin_wg && valid && !dead) {
                 const Lane me;
                 const FinEntry f(z, me);
                 if (f.own) (f.row ? A.lr_out : A.lc_out)[f.k] = sh.fl[me.t];
             }
-            if (dead && threadIdx.x == 0) A.out->retry = 1;
             if (z.blk == 0 && threadIdx.x == 0 && !dead) {
                 A.out->valid = valid;
                 A.out->status = any ? MDOT_W_RANGE : MDOT_OK;
@@ -3404,6 +3396,7 @@ __global__ void __launch_bounds__(256 * NQ) k_lse(LseArgs A, StepsX* __restrict_
                 A.out->done = 1;
             }
         }
+        if (threadIdx.x == 0 && sh.dead) A.out->retry = 1;
     }
     steps_leave(z, x);
 }
