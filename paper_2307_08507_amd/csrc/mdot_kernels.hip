@@ -176,7 +176,8 @@ struct DenseCost {
     // before the first shift (one branch per row instead makes every row wait for its own load). Where
     // a lane's batch reaches past a matrix that ends inside a dword, the half behind the end is cleared
     // first: a padding column, or the row past the last one, would decode it.
-    // n = 8191 BF16 sweep: 64.8 us with four 2-byte loads per lane and row, 35.4 us so; 32 us at 8192.
+    // n = 8191 BF16 sweep: 64.8 us with four 2-byte loads per lane and row, 36.6 us so and 37.7 us with
+    // the clearing; 30 us at 8192.
     // FP32 and FP64 rows from `rows` on may be left out.
     template <int B>
     __device__ __forceinline__ void load(int r, int j0, Raw* v, int rows = B) const
